@@ -29,7 +29,7 @@
 #include <string>
 #include <type_traits>
 
-#include "conv_mfma.h"
+#include "conv_split.h"
 #include "plan.h"
 
 namespace syno {
@@ -255,16 +255,10 @@ int pick_w_row(int need, int kstep, int multiple_of) {
 // bf16 tile variants whose backward-data instantiation reads forward-layout 3x3 weights itself (the others pack)
 bool bf16_adjoint_direct(int vi) { return vi == 1 || vi == 8 || vi == 9; }
 
-// Parameter record of contraction `which` (forward, or backward-data as its adjoint) for tile variant vi
-// and TR output rows per block.  False when the combination does not fit the kernel's static limits.
-bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaParams& p, int ksplit = 1) {
+// The part of the parameter record that names the problem: contraction `which` (forward, or backward-data as its adjoint).
+void fill_problem(const syno_plan* plan, int which, MfmaParams& p) {
   const ConvLike& c = plan->conv;
   const bool bf = plan->in_dtype == SYNO_BF16;
-  if (vi < 0 || vi >= num_variants(bf) || TR < 1) return false;
-  // the kernel addresses its source tensor with 32-bit byte offsets
-  if ((which == SYNO_FWD ? plan->x_elems : plan->out_elems) * (bf ? 2 : 4) >= (1ll << 32)) return false;
-  const Variant& v = variant_of(bf, vi);
-  p = MfmaParams{};
   p.G = c.G; p.Ho = c.Ho; p.Wo = c.Wo; p.Hi = c.Hi; p.Wi = c.Wi;
   p.KH = c.KH; p.KW = c.KW;
   p.rows_total = c.N * c.Ho;
@@ -295,6 +289,50 @@ bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaParams& p
       p.w_base = 0;
     }
   }
+}
+
+// The tiles of one (group, split) plane dealt to the 8 XCDs.
+// Which tiles share an XCD's L2: with the tiles of a plane dealt as xcd_m x xcd_n rectangles the XCDs together fetch
+// the source xcd_n times and the weights xcd_m times; take the split with the fewest bytes that divides both counts.
+// An XCD walks its rectangle either one row of tiles after the other, coming back to the same weight panels in each
+// row, or one panel after the other, coming back to the same source rows: unless the whole rectangle is resident at
+// once, the operand it comes back to has to stay in that XCD's L2 (4 MB, half of it left to the streaming one), or
+// every pass fetches it again.
+void deal_to_xcds(const ConvLike& c, bool bf, MfmaParams& p) {
+  const int plane = c.Hi * c.Wi, KHW = c.KH * c.KW;
+  p.xcd_m = p.xcd_n = p.xcd_rows_first = 0;
+  if (((int64_t)p.n_mblocks * p.n_nblocks) % 8 == 0) {
+    const double esize = bf ? 2.0 : 4.0, fits = 2.0 * 1024 * 1024;
+    const double src = esize * c.N * p.Cg * plane / p.ksplit, wts = esize * p.Og * p.Cg * KHW / p.ksplit;
+    const int64_t resident = 32 * std::max(1, std::min(2, kMaxLdsBytes / std::max(p.lds_bytes, 1)));
+    double fewest = 0;
+    for (int a = 1; a <= 8; a *= 2) {
+      const int b = 8 / a;
+      if (p.n_mblocks % a != 0 || p.n_nblocks % b != 0) continue;
+      const int64_t sm = p.n_mblocks / a, sn = p.n_nblocks / b;
+      for (int rows_first = 0; rows_first < 2; ++rows_first) {
+        double bytes = b * src + a * wts;
+        if (sm * sn > resident) {
+          if (!rows_first && wts / b > fits) bytes += a * wts * (sm - 1);
+          if (rows_first && src / a > fits) bytes += b * src * (sn - 1);
+        }
+        if (p.xcd_m == 0 || bytes < fewest) { fewest = bytes; p.xcd_m = a; p.xcd_n = b; p.xcd_rows_first = rows_first; }
+      }
+    }
+  }
+}
+
+// Parameter record of contraction `which` for tile variant vi and TR output rows per block.  False when the combination
+// does not fit the kernel's static limits.
+bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaParams& p, int ksplit = 1) {
+  const ConvLike& c = plan->conv;
+  const bool bf = plan->in_dtype == SYNO_BF16;
+  if (vi < 0 || vi >= num_variants(bf) || TR < 1) return false;
+  // the kernel addresses its source tensor with 32-bit byte offsets
+  if ((which == SYNO_FWD ? plan->x_elems : plan->out_elems) * (bf ? 2 : 4) >= (1ll << 32)) return false;
+  const Variant& v = variant_of(bf, vi);
+  p = MfmaParams{};
+  fill_problem(plan, which, p);
   p.TR = TR;
   p.BN = v.BN();
   const int KHW = c.KH * c.KW;
@@ -379,33 +417,71 @@ bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaParams& p
     p.ksplit = ksplit;
     p.split_stride = (int32_t)((result + 3) & ~3ll);
   }
-  // Which tiles share an XCD's L2: with the tiles of a plane dealt as xcd_m x xcd_n rectangles the XCDs together fetch
-  // the source xcd_n times and the weights xcd_m times; take the split with the fewest bytes that divides both counts.
-  // An XCD walks its rectangle either one row of tiles after the other, coming back to the same weight panels in each
-  // row, or one panel after the other, coming back to the same source rows: unless the whole rectangle is resident at
-  // once, the operand it comes back to has to stay in that XCD's L2 (4 MB, half of it left to the streaming one), or
-  // every pass fetches it again.
-  p.xcd_m = p.xcd_n = p.xcd_rows_first = 0;
-  if (((int64_t)p.n_mblocks * p.n_nblocks) % 8 == 0) {
-    const double esize = bf ? 2.0 : 4.0, fits = 2.0 * 1024 * 1024;
-    const double src = esize * c.N * p.Cg * plane / p.ksplit, wts = esize * p.Og * p.Cg * KHW / p.ksplit;
-    const int64_t resident = 32 * std::max(1, std::min(2, kMaxLdsBytes / std::max(p.lds_bytes, 1)));
-    double fewest = 0;
-    for (int a = 1; a <= 8; a *= 2) {
-      const int b = 8 / a;
-      if (p.n_mblocks % a != 0 || p.n_nblocks % b != 0) continue;
-      const int64_t sm = p.n_mblocks / a, sn = p.n_nblocks / b;
-      for (int rows_first = 0; rows_first < 2; ++rows_first) {
-        double bytes = b * src + a * wts;
-        if (sm * sn > resident) {
-          if (!rows_first && wts / b > fits) bytes += a * wts * (sm - 1);
-          if (rows_first && src / a > fits) bytes += b * src * (sn - 1);
-        }
-        if (p.xcd_m == 0 || bytes < fewest) { fewest = bytes; p.xcd_m = a; p.xcd_n = b; p.xcd_rows_first = rows_first; }
-      }
-    }
-  }
+  deal_to_xcds(c, bf, p);
   return p.lds_bytes <= kMaxLdsBytes;
+}
+
+// ---- fp32 on the bf16 matrix cores (conv_split.h): the record of one tile configuration
+struct SplitConfig { int WM, WN, WK, TN, mode, max_tiles; };
+constexpr int kNumSplitConfigs = 4;
+constexpr SplitConfig kSplitConfigs[kNumSplitConfigs] = {{4, 2, 1, 2, 0, 7}, {4, 1, 2, 2, 1, 7}, {2, 1, 4, 2, 2, 7}, {4, 2, 1, 4, 2, 4}};
+
+void launch_split(int cfg, int T, int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s) {
+  if (cfg == 0) (T == 9 ? launch_split_0_9 : launch_split_0_3)(tiles, p, X, W, out, s);
+  else if (cfg == 1) (T == 9 ? launch_split_1_9 : launch_split_1_3)(tiles, p, X, W, out, s);
+  else if (cfg == 2) launch_split_2_9(tiles, p, X, W, out, s);
+  else launch_split_3_1(tiles, p, X, W, out, s);
+}
+
+bool fill_split(const syno_plan* plan, int which, int cfg, int TR, SplitParams& p) {
+  const ConvLike& c = plan->conv;
+  if (plan->in_dtype != SYNO_F32 || plan->out_dtype != SYNO_F32 || cfg < 0 || cfg >= kNumSplitConfigs || TR < 1) return false;
+  if ((which == SYNO_FWD ? plan->x_elems : plan->out_elems) * 4 >= (1ll << 32)) return false;
+  const SplitConfig& v = kSplitConfigs[cfg];
+  const int T = c.KH * c.KW;
+  if ((c.KH != 1 && c.KH != 3) || (c.KW != 1 && c.KW != 3)) return false;
+  if ((cfg == 3) != (T == 1) || (v.WK == 4 && T < 9)) return false;      // (every wave needs a tap in every stage)
+  // weights in the forward layout, whole weight items
+  if ((c.KW > 1 && c.ws_kw != 1) || (c.KH > 1 && c.ws_kh != c.KW) || c.ws_c != T) return false;
+  p = SplitParams{};
+  fill_problem(plan, which, p);
+  p.wt = 0;
+  p.adjoint = which != SYNO_FWD;
+  if (p.adjoint) { p.ws_g = c.ws_g; p.ws_o = T; p.ws_c = c.ws_o; p.ws_kh = c.KW; p.ws_kw = 1; p.w_base = 0; }
+  p.TR = TR;
+  p.BN = v.WN * v.TN * 16;
+  if (p.Cg < kSplitChannels || p.Cg % (p.BN / 16) != 0) return false;
+  p.KC = kSplitChannels;
+  p.cgrps = 4;
+  p.n_chunks = (p.Cg + p.KC - 1) / p.KC;
+  p.U = 1;
+  p.n_mblocks = (p.rows_total + TR - 1) / TR;
+  p.n_nblocks = (p.Og + p.BN - 1) / p.BN;
+  p.n_slots = row_slots(c, p.sh, TR);
+  p.Wp = c.Wi + c.KW - 1;
+  const int64_t MT = ((int64_t)TR * c.Wo + 15) / 16;
+  if (MT > v.WM * v.max_tiles) return false;
+  const int64_t per_cg = (int64_t)p.n_slots * c.Wi;
+  if (4 * per_cg > 4 * 512) return false;
+  p.x_items = (int)((4 * per_cg + 511) / 512);
+  p.m_wp = (uint32_t)(((1ull << 32) + p.Wp - 1) / p.Wp);
+  p.octet = (p.n_slots * p.Wp + 15) & ~15;
+  p.x_bytes = 4 * p.octet * 48;
+  p.w_bytes = split_taps(T) * kPlanes * 4 * p.BN * 16;
+  p.lds_w_off = (v.mode == 2 ? 2 : 1) * p.x_bytes;
+  p.lds_tab_off = p.lds_w_off + (v.mode >= 1 ? 2 : 1) * p.w_bytes;
+  p.lds_bytes = p.lds_tab_off + ((p.n_slots * 4 + 15) & ~15);
+  if (v.WK > 1) p.lds_bytes = std::max<int>(p.lds_bytes, 8 * (int)((MT + v.WM - 1) / v.WM) * v.TN * 1024);
+  if (p.lds_bytes > kMaxLdsBytes) return false;
+  auto magic = [](int64_t d) { return (uint32_t)(((1ull << 32) + d - 1) / std::max<int64_t>(d, 1)); };
+  if (2048 * per_cg >= (1ll << 32) || (int64_t)p.rows_total * c.Ho >= (1ll << 32)) return false;
+  p.m_wo = magic(c.Wo); p.m_ho = magic(c.Ho); p.m_vpr = magic(c.Wi); p.m_pcg = magic(per_cg);
+  p.ksplit = 1; p.chunks_per_split = p.n_chunks; p.split_stride = 0;
+  deal_to_xcds(c, false, p);
+  // (tiles that are all resident at once come back to neither operand: those that start together share the larger one)
+  if (p.xcd_m > 0 && (p.n_mblocks / p.xcd_m) * (p.n_nblocks / p.xcd_n) <= 32)
+    p.xcd_rows_first = (double)p.Og * p.Cg * T > (double)c.N * p.Cg * c.Hi * c.Wi;
+  return true;
 }
 
 // Estimated duration of the launch in SIMD cycles.  Row tiles are dealt evenly to the WM wave rows, wave
@@ -440,6 +516,32 @@ double tile_cost(const MfmaParams& p, const Variant& v, const ConvLike& c, bool 
   const int resident = (v.NT() <= 256 && p.lds_bytes <= kMaxLdsBytes / 2) ? 2 : 1;
   const double per_cu_wgs = std::ceil((double)wgs / kNumCU);
   return per_cu_wgs * steps * step + std::ceil(per_cu_wgs / resident) * overhead + split_cost;
+}
+
+// The same for conv_split.  Per stage the busiest SIMD's products (96 cycles per 16 x 16 tile and tap), or twice that for a
+// wave alone with its LDS reads, and what barriers and staging leave uncovered; per workgroup the first loads and the
+// stores.  The constants are from timestamps in the kernel at the 3x3 stages of the benchmark (cycles at 2.4 GHz).
+double split_cost(const SplitParams& p, int cfg, const ConvLike& c) {
+  const SplitConfig& v = kSplitConfigs[cfg];
+  const int T = c.KH * c.KW, TS = split_taps(T), subs = split_subs(T);
+  const int MT = (std::min(p.TR, p.rows_total) * c.Wo + 15) / 16, base = MT / v.WM, extra = MT % v.WM;
+  double chunk = 0;
+  for (int sub = 0; sub < subs; ++sub) {
+    const int n = sub ? T - TS : TS;
+    double simd[4] = {0, 0, 0, 0}, longest = 0;
+    for (int w = 0; w < 8; ++w) {
+      const int wm = v.WM == 4 ? (w + 2 * (w >> 2)) & 3 : w >> 2, wk = v.WK == 1 ? 0 : v.WM == 4 ? w >> 2 : (w + wm) & 3;
+      const int taps = (wk + 1) * n / v.WK - wk * n / v.WK, tiles = std::max(1, base + (wm < extra ? 1 : 0));
+      const double cycles = (double)taps * tiles * v.TN * 96.0;
+      simd[w & 3] += cycles;
+      longest = std::max(longest, cycles);
+    }
+    chunk += std::max(*std::max_element(simd, simd + 4), 1.3 * longest) + (v.mode == 0 ? 4500.0 : 2000.0);
+  }
+  chunk += v.mode == 1 ? 1500.0 : 0.0;
+  chunk = std::max(chunk, 3900.0);      // (a memory round trip over the two chunks that are on their way)
+  const double wgs = (double)p.n_mblocks * p.n_nblocks * c.G * p.ksplit;
+  return std::ceil(wgs / kNumCU) * (p.chunks_per_split * chunk + 22000.0);
 }
 
 size_t packed_weight_bytes(const MfmaParams& p) {
@@ -515,6 +617,31 @@ void mfma_configure(syno_plan* plan, int which) {
         const double cost = tile_cost(mp, variant_of(bf, vi), c, bf);
         if (cost < best) { best = cost; best_v = vi; best_tr = TR; best_ks = 1; }
       }
+  // fp32: the bf16-parts kernel where the operator fits it and it is estimated to be faster; the options name it too
+  if (!bf && plan->opt.mfma_variant <= 0 && !forced && plan->opt.mfma_rows >= 0) {
+    const int named = plan->opt.mfma_variant <= -2 ? -2 - plan->opt.mfma_variant : -1;
+    int best_cfg = -1, cfg_tr = 0;
+    double cfg_cost = named >= 0 ? 1e300 : best;
+    SplitParams sp;
+    for (int cfg = 0; cfg < kNumSplitConfigs; ++cfg)
+      for (int TR = 1; TR <= c.N * c.Ho && TR * c.Wo <= 16 * 28; ++TR) {
+        if (named >= 0 && (cfg != named || (plan->opt.mfma_rows > 0 && TR != plan->opt.mfma_rows))) continue;
+        if (!fill_split(plan, which, cfg, TR, sp)) continue;
+        const double cost = split_cost(sp, cfg, c);
+        if (cost < cfg_cost) { cfg_cost = cost; best_cfg = cfg; cfg_tr = TR; }
+      }
+    if (best_cfg >= 0) {
+      fill_split(plan, which, best_cfg, cfg_tr, sp);
+      sp.probe_lo = (uint32_t)reinterpret_cast<uintptr_t>(plan->opt.clock_probe);
+      sp.probe_hi = (uint32_t)(reinterpret_cast<uintptr_t>(plan->opt.clock_probe) >> 32);
+      static_assert(sizeof(SplitParams) <= sizeof(plan->launch[which].params), "parameter record does not fit");
+      memcpy(plan->launch[which].params, &sp, sizeof sp);
+      plan->launch[which].params_ready = true;
+      plan->launch[which].variant = -2 - best_cfg;
+      plan->launch[which].workspace = 0;
+      return;
+    }
+  }
   fill_params(plan, which, best_v, best_tr, mp, best_ks);
   if (plan->opt.mfma_taps == 1) mp.U = 1;     // (option: the one-tap-per-row-step instantiation)
   mp.probe_lo = (uint32_t)reinterpret_cast<uintptr_t>(plan->opt.clock_probe);
@@ -528,6 +655,19 @@ void mfma_configure(syno_plan* plan, int which) {
 
 std::string mfma_describe(const syno_plan* plan, int which) {
   if (plan->launch[which].variant == -1) return rows_describe(plan, which);
+  if (plan->launch[which].variant <= -2) {
+    SplitParams p;
+    memcpy(&p, plan->launch[which].params, sizeof p);
+    const SplitConfig& v = kSplitConfigs[-2 - plan->launch[which].variant];
+    char b[256];
+    snprintf(b, sizeof b, "bf16-parts tiles=%d rows/block=%d BN=%d KC=%d weights=%s waves=%dx%dx%d grid=%d lds=%dB slots=%d", -2 - plan->launch[which].variant, p.TR,
+             p.BN, p.KC, p.adjoint ? "turned-while-staged" : "direct", v.WM, v.WN, v.WK, p.n_mblocks * p.n_nblocks * p.G * p.ksplit, p.lds_bytes, p.n_slots);
+    std::string d = b;
+    if (p.xcd_m > 0)
+      d += " tiles-per-xcd=" + std::to_string(p.n_mblocks / p.xcd_m) + "x" + std::to_string(p.n_nblocks / p.xcd_n) +
+           (p.xcd_rows_first ? "(rows first)" : "");
+    return d;
+  }
   const int vi = plan->launch[which].variant / 4096, TR = plan->launch[which].variant % 4096;
   MfmaParams p;
   if (!fill_params(plan, which, vi, TR, p)) return "unconfigured";
@@ -549,6 +689,14 @@ syno_status launch_mfma(const syno_plan* plan, int which, const void* A, const v
   const int vi = plan->launch[which].variant / 4096;
   if (!plan->launch[which].params_ready) return SYNO_ERR_UNSUPPORTED;
   if (plan->launch[which].variant == -1) return launch_rows(plan, which, A, B, out, ws, stream);
+  if (plan->launch[which].variant <= -2) {
+    SplitParams sp;
+    memcpy(&sp, plan->launch[which].params, sizeof sp);
+    const int cfg = -2 - plan->launch[which].variant;
+    const int MT = (sp.TR * sp.Wo + 15) / 16, tiles = (MT + kSplitConfigs[cfg].WM - 1) / kSplitConfigs[cfg].WM;
+    launch_split(cfg, sp.KH * sp.KW, tiles, sp, static_cast<const float*>(A), static_cast<const float*>(B), static_cast<float*>(out), stream);
+    return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
+  }
   MfmaParams p;
   memcpy(&p, plan->launch[which].params, sizeof p);
   const bool obf = plan->out_dtype == SYNO_BF16;

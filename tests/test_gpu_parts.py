@@ -1,0 +1,80 @@
+"""The fp32 contraction on the bf16 matrix cores (every value split into three bf16 parts): parity with the checker at the
+edges of its tiles, chunks and stages, and the values that parts cannot stand for."""
+import numpy as np
+import pytest
+import torch
+
+from syno_inputs import F32, workloads as wl
+from test_gpu_parity import run_all, syno  # noqa: F401  (fixture)
+
+# tile configurations: 0 = 64 output channels, 1 = 32 with the taps of a window dealt to two waves, 2 = to four,
+# 3 = 128 output channels of a 1x1 window
+CASES = {
+    # 40 channels: a last chunk that starts early; blocks that cross images; 72 output channels: a block of 8
+    "3x3_ragged": (lambda: wl.make_conv(3, 40, 13, seed=31, Co=72, Wd=19, with_grad=True), ((0, 5), (1, 7), (2, 4), (2, 1)), (0, 1)),
+    # one chunk, an image narrower than a quad of pixels, one pixel tile for four rows of waves
+    "3x3_narrow": (lambda: wl.make_conv(5, 32, 6, seed=32, Co=36, Wd=2, with_grad=True), ((0, 1), (0, 30), (1, 11), (2, 12)), (0, 1)),
+    # the most pixel tiles per wave, the last of them missing in some waves
+    "3x3_full_tiles": (lambda: wl.make_conv(2, 96, 28, seed=33, Co=64, with_grad=True), ((0, 14), (1, 14), (2, 4)), (0, 1)),
+    # channel counts that are only even
+    "3x3_even_channels": (lambda: wl.make_conv(2, 34, 9, seed=34, Co=38, Wd=11, with_grad=True), ((1, 9), (2, 4)), (0, 1)),
+    "3x3_stride2": (lambda: wl.make_conv(2, 64, 9, seed=35, Co=72, Wd=12, stride=2, with_grad=True), ((0, 5), (1, 4), (2, 3)), (0,)),
+    "1x1": (lambda: wl.make_conv(3, 72, 10, seed=36, Co=136, Wd=15, K=1, with_grad=True), ((3, 1), (3, 13)), (0, 1)),
+    # cyclic rows whose shift depends on the group, 1x3 window
+    "cyclic_1x3": (lambda: wl.make_gshift(3, seeds=(37, 37, 37), with_grad=True, C=144, H=9, Wd=11, bf16=False), ((0, 4), (1, 9)), (0, 1)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,cfg,rows", [(n, c, r) for n, v in CASES.items() for c, r in v[1]])
+def test_parity_at_the_edges(syno, oracle, name, cfg, rows):  # noqa: F811
+    make, _, directions = CASES[name]
+    w = make()
+    plan = syno.Plan(w.desc, mfma_variant=-2 - cfg, mfma_rows=rows)
+    for which in directions:
+        assert f"bf16-parts tiles={cfg} rows/block={rows} " in plan.describe(which), plan.describe(which)
+        assert plan.workspace_bytes(which) == 0
+    run_all(syno, oracle, w, 0, directions=directions, mfma_variant=-2 - cfg, mfma_rows=rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg", (0, 1, 2))
+def test_values_that_parts_do_not_stand_for(syno, cfg):  # noqa: F811
+    """Infinities, NaNs, values near the largest float, subnormal operands and results: as the index-program kernel has them."""
+    d = wl.conv2d(2, 40, 48, 10, 12)
+    parts, plain = syno.Plan(d, mfma_variant=-2 - cfg), syno.Plan(d, kernel_policy=1)
+    assert "bf16-parts" in parts.describe(0) and "bf16-parts" in parts.describe(1)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    X, W = torch.randn(parts.x_shape, generator=gen, device="cuda"), torch.randn(parts.w_shape, generator=gen, device="cuda") / 20
+
+    def agree(x, w):
+        for a, b in ((parts.forward(x, w), plain.forward(x, w)),):
+            assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.isposinf(a), torch.isposinf(b))
+            assert torch.equal(torch.isneginf(a), torch.isneginf(b))
+            fine = torch.isfinite(b)
+            # 360 terms in fp32 on either side; the largest subnormal step for results that are subnormal themselves
+            err, bound = (a - b)[fine].double().abs(), 2e-5 * b[fine].double().abs().max() + 2e-45 * 400
+            assert float(err.max()) <= float(bound)
+
+    Y, V = X.clone(), W.clone()
+    Y[0, 3, 5, 5], Y[0, 39, 0, 0], Y[1, 7, 9, 11], Y[1, 8, 4, 4], Y[1, 9, 4, 4] = float("inf"), float("-inf"), float("nan"), float("inf"), float("-inf")
+    agree(Y, W)
+    V[3, 4, 1, 1], V[40, 0, 0, 2] = float("inf"), float("nan")
+    agree(X, V)
+    Z = X.clone()
+    Z[0, 0, 2, 2] = 3.4e38            # rounds to infinity as a bf16 value
+    agree(Z, W * 1e-3)
+    for scale in (1e30, 1e-30, 1e-36, 1e-41):
+        agree(X * scale, W)
+    agree(torch.zeros_like(X), W)
+
+
+def test_where_the_planner_takes_it():
+    import paper_2410_23745_amd as s
+    for C, H in wl.RESNET18_STAGES:
+        p = s.Plan(wl.conv2d(32, C, C, H, H))
+        assert all("bf16-parts" in p.describe(which) for which in (0, 1))
+    # too little work for it, a window or weight layout that it does not have, a named variant of the other kernel
+    for p in (s.Plan(wl.conv2d(1, 16, 16, 16, 16)), s.Plan(wl.conv2d(32, 64, 64, 56, 56, 5, 5)),
+              s.Plan(wl.conv2d(32, 64, 64, 28, 28, 3, 3, F32, F32, (1, 0, 2, 3))), s.Plan(wl.conv2d(32, 64, 64, 28, 28), mfma_variant=4, mfma_rows=7)):
+        assert all("bf16-parts" not in p.describe(which) for which in (0, 1))
