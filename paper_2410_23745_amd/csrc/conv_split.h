@@ -1,11 +1,8 @@
 // fp32 contraction on the bf16 matrix cores, device side: parameter record, kernel template and launch helper.
-//
-// An fp32 value is the exact sum of three bf16 values (8 significant bits each): x = h + m + l with h = bf16(x),
-// m = bf16(x - h), l = x - h - m.  A product of two fp32 values is then nine bf16 products, each exact in fp32, of which
-// the three smallest (m*l, l*m, l*l: below 2^-24 of the product) are left out; the six others are accumulated in fp32 by
-// v_mfma_f32_16x16x32_bf16.  Six of them take 96 cycles for 32 channels where v_mfma_f32_16x16x4_f32 takes 256.
+// (fp32_parts.h: how a value is split, and which results are summed again.)
 #pragma once
 #include "conv_mfma.h"
+#include "fp32_parts.h"
 
 namespace syno {
 
@@ -20,35 +17,9 @@ struct SplitParams : MfmaParams {
 namespace {
 
 constexpr int kSplitChannels = 32;   // channels per chunk = one MFMA k-step per tap
-constexpr int kPlanes = 3;
 // taps whose weights lie in LDS at a time: the nine of a 3x3 window go in as five and four
 constexpr int split_taps(int T) { return T == 9 ? 5 : T; }
 constexpr int split_subs(int T) { return T == 9 ? 2 : 1; }
-
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t round_pair(float lo, float hi) {      // v_cvt_pk_bf16_f32: to nearest even
-  const f32x2_t v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
-
-// (x0, x1) -> the two values' parts, packed pairwise, times 2^24: the bf16 matrix instructions take subnormal operands for
-// zero, and this keeps the smallest part of every normal fp32 value normal (and the largest one of a subnormal).  The last
-// remainder has at most 8 significant bits: its upper half is the value itself.  An infinity, a NaN or a value above 2^104
-// leaves a NaN in m or l, so every result that it takes part in is a NaN and is summed again when it is stored; so
-// are sums beyond 2^80, and results below 2^-80, which subnormal operands may have had a part in.
-constexpr float kPartScale = 16777216.f, kResultScale = 1.f / (16777216.f * 16777216.f);
-constexpr float kLeastResult = 8.271806125530277e-25f;      // 2^-80
-__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
-  x0 *= kPartScale;
-  x1 *= kPartScale;
-  h = round_pair(x0, x1);
-  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
-  m = round_pair(r0, r1);
-  const float s0 = r0 - __uint_as_float(m << 16), s1 = r1 - __uint_as_float(m & 0xffff0000u);
-  l = __builtin_amdgcn_perm(__float_as_uint(s1), __float_as_uint(s0), 0x07060302u);
-}
 
 // slot_source without divisions: first row n0*Ho + h0 of the block given, the images walked one after the other
 __device__ __forceinline__ int split_slot(const SplitParams& p, int R0, int rows, int n, int h, int g, int s) {
@@ -469,7 +440,6 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   float* const op = out + (int64_t)ksp * p.split_stride;
   const int c_begin = ch_begin * kSplitChannels, c_end = min(p.Cg, ch_end * kSplitChannels);
   bool odd = false;                // some result of this lane is none that the parts can give
-  auto trusted = [](float v) { return v == 0.f || (fabsf(v) >= kLeastResult && fabsf(v) <= 3.4028234663852886e38f); };
   auto element = [&](int m, int o) -> int64_t {       // pixel m of the block, output channel o -> element of the result
     const int i = fdiv(m, p.m_wo), r = R0 + i, n = fdiv(r, p.m_ho);
     return (int64_t)n * p.os_n + (int64_t)(g * p.Og + o) * p.os_o + (r - n * p.Ho) * p.Wo + (m - i * p.Wo);
@@ -486,7 +456,7 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     const float sum = fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]);
     const float least = fminf(fminf(fabsf(v[0]), fabsf(v[1])), fminf(fabsf(v[2]), fabsf(v[3])));
     if (!(sum <= 3.4028234663852886e38f && least >= kLeastResult))
-      odd |= !(trusted(v[0]) && trusted(v[1]) && trusted(v[2]) && trusted(v[3]));
+      odd |= !(trusted_result(v[0]) && trusted_result(v[1]) && trusted_result(v[2]) && trusted_result(v[3]));
     if (m0 + 3 < block_px && px + 3 < img_px && (off & 3) == 0) {
       *reinterpret_cast<float4*>(op + off) = make_float4(v[0], v[1], v[2], v[3]);
     } else {
@@ -527,7 +497,7 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
         if (t >= my_tiles || o >= p.Og || m >= block_px) continue;
         float* const at = op + element(m, o);
         const int row = fdiv(m, p.m_wo);
-        if (!trusted(*at)) *at = split_exact(p, X, W, g, o, R0 + row, m - row * p.Wo, c_begin, c_end, ADJ);
+        if (!trusted_result(*at)) *at = split_exact(p, X, W, g, o, R0 + row, m - row * p.Wo, c_begin, c_end, ADJ);
       }
     }
   }

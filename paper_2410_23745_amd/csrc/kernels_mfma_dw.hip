@@ -29,6 +29,7 @@
 #include <string>
 #include <type_traits>
 
+#include "fp32_parts.h"
 #include "plan.h"
 
 namespace syno {
@@ -57,12 +58,26 @@ struct DwParams {
   int32_t mode;                        // pixels per staging item: 4, 2, 1, or a whole row of 7 or 14
   int32_t lds_buf;                     // bytes of one LDS buffer (G tile, then X tile at lds_x_off); there are two
   uint32_t magic_cpi;                  // ceil(2^32/d) for d = cpi (0 for d = 1); magic_w2 is for the items per row
+  // fp32 on the bf16 matrix cores (dw_split.h): `pitch` pixels per stream row, CPp LDS elements per X channel
+  int32_t parts;                       // that kernel takes this plan
+  int32_t stream_reach, stream_ring;   // pixels of X read beyond a chunk on either side; pixels in the ring
+  uint32_t m_pitch, m_rows;            // ceil(2^32/d) for d = pitch and d = H + 1
 };
 
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+// f(integral_constant<int, I>) for I = 0 .. N-1
+template <int I, int N, class F>
+__device__ __forceinline__ void for_blocks(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    for_blocks<I + 1, N>(f);
+  }
+}
 constexpr int kGuard = 8;     // zero elements in front of each X channel row (a tap may reach one element back)
 // staging items per thread, tensor and chunk (256 threads): 26-28 of one or two pixels (a dword), or 18 of four (two
 // dwords) - about the same registers either way
@@ -385,6 +400,8 @@ __device__ __forceinline__ void dw_finish(const DwParams& p, float* __restrict__
 #pragma unroll
       for (int t = 0; t < T; ++t) dst[((ao * CT + i) * T + t) * 64] = acc[ao][i][t];
 }
+
+#include "dw_split.h"
 
 // fp32 inputs: the same contraction with v_mfma_f32_16x16x4_f32, whose K-step is 4 consecutive pixels (lane ->
 // row l%16, pixel l/16).  Operands are single dwords, so a tap is any element shift and nothing has to be cut;
@@ -937,8 +954,9 @@ __global__ __launch_bounds__(kRowsThreads) void dw_rows_bf16(const DwParams p, c
 // splits, in order, for taps j, j+4, ...; then the threads walk the tile in (o, c, tap) order, which is contiguous in
 // dW for the usual weight layouts, so dW is written in whole lines.
 constexpr int kMaxTaps = 9;
+// (Gt, Xt: read again where the sum of parts is none, p.parts only)
 __global__ __launch_bounds__(256) void dw_reduce_tiles(const DwParams p, const float4* __restrict__ partial,
-                                                       float* __restrict__ dW) {
+                                                       float* __restrict__ dW, const float* __restrict__ Gt, const float* __restrict__ Xt) {
   __shared__ float sums[kMaxTaps][64][4];
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int T = p.KH * p.KW;
@@ -971,14 +989,16 @@ __global__ __launch_bounds__(256) void dw_reduce_tiles(const DwParams p, const f
     const int c = c0 + cl;
     if (c >= p.Cg) continue;
     const int kh = t / p.KW;
-    dW[row + (int64_t)c * p.ws_c + kh * p.ws_kh + (t - kh * p.KW) * p.ws_kw] = sums[t][(ol >> 2) * 16 + cl][ol & 3];
+    float v = sums[t][(ol >> 2) * 16 + cl][ol & 3];
+    if (p.parts && !trusted_result(v)) v = dw_exact(p, Gt, Xt, g, o, c, kh, t - kh * p.KW);
+    dW[row + (int64_t)c * p.ws_c + kh * p.ws_kh + (t - kh * p.KW) * p.ws_kw] = v;
   }
 }
 
 // The same sums for many splits and few tiles: a block owns one slot (64 quadruples, one tap of a 16x16 tile), which
 // keeps enough blocks in flight when dW is small; the stores are scattered, which does not matter at that size.
 __global__ __launch_bounds__(256) void dw_reduce_slots(const DwParams p, const float4* __restrict__ partial,
-                                                       float* __restrict__ dW) {
+                                                       float* __restrict__ dW, const float* __restrict__ Gt, const float* __restrict__ Xt) {
   __shared__ float4 sums[4][64];
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int64_t n4 = (int64_t)p.n_tiles * p.slots * 64;
@@ -1009,7 +1029,7 @@ __global__ __launch_bounds__(256) void dw_reduce_slots(const DwParams p, const f
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int o = ob * 64 + (2 * (wave >> 1) + ao) * 16 + 4 * (lane >> 4) + v;
-    if (o < p.Og) dW[base + (int64_t)o * p.ws_o] = r[v];
+    if (o < p.Og) dW[base + (int64_t)o * p.ws_o] = p.parts && !trusted_result(r[v]) ? dw_exact(p, Gt, Xt, g, o, c, t / p.KW, t % p.KW) : r[v];
   }
 }
 
@@ -1255,8 +1275,56 @@ bool fill_dw_f32(const syno_plan* plan, DwParams& p) {
   return fill_dw_f32_as(plan, p, false);
 }
 
+// fp32 on the bf16 matrix cores: windows of 1 or 3 along either axis, rows not cyclic.  Images of up to 4 columns, of whose
+// rows at least half would be filling, and a single chunk of pixels, where there is nothing to overlap the splitting with,
+// stay with the fp32 instructions: 64x256x256 64x1 3x1 86 us against 52, 1x1024x1024 7x7 50.5 against 45; from 7 columns
+// and two chunks on this one is ahead (2x512x512 7x7 26.5 against 26.4, 4x512x512 29.9 against 31.1, 32x64x64 56x56 59 against 86).
+bool fill_dw_split(const syno_plan* plan, DwParams& p) {
+  const ConvLike& c = plan->conv;
+  if (c.h_wrap || (c.KH != 1 && c.KH != 3) || (c.KW != 1 && c.KW != 3) || c.Wo <= 4) return false;
+  if (std::max(plan->x_elems, plan->out_elems) * 4 >= kNoPixel) return false;        // byte offsets
+  p = DwParams{};
+  p.G = c.G; p.Og = c.Og; p.Cg = c.Cg; p.H = c.Ho; p.W = c.Wo; p.KH = c.KH; p.KW = c.KW; p.ph = c.ph; p.pw = c.pw;
+  p.rows_total = c.N * c.Ho; p.n_images = c.N;
+  p.plane = c.Ho * c.Wo;
+  p.gs_n = c.G * c.Og * p.plane; p.xs_n = c.G * c.Cg * p.plane;
+  p.ws_g = c.ws_g; p.ws_o = c.ws_o; p.ws_c = c.ws_c; p.ws_kh = c.ws_kh; p.ws_kw = c.ws_kw;
+  p.w_elems = (int32_t)plan->w_elems;
+  p.parts = 1;
+  p.pitch = (c.Wo + 7) & ~7;
+  p.TRK = 1;
+  const int T = c.KH * c.KW;
+  p.ct = T == 9 ? 1 : 2;
+  const int cx = 32 * p.ct;
+  p.stream_reach = (c.KH > 1 ? p.pitch : 0) + (c.KW > 1 ? 8 : 0);
+  p.stream_ring = 2 * kStreamChunk + 2 * p.stream_reach;
+  int units = p.stream_ring / 8;
+  while ((units & 3) != 2) ++units;
+  p.CPp = units * 8;
+  const int64_t stream = (int64_t)c.N * (c.Ho + 1) * p.pitch;
+  // (exact quotients, also for the positions that are requested past the end)
+  if ((stream + 4096) * std::max(p.pitch, c.Ho + 1) >= (1ll << 32)) return false;
+  p.m_pitch = magic_of(p.pitch); p.m_rows = magic_of(c.Ho + 1);
+  p.n_chunks = (int)((stream + kStreamChunk - 1) / kStreamChunk);
+  if (p.n_chunks < 2) return false;
+  p.n_oblk = (c.Og + 63) / 64;
+  p.n_cblk = (c.Cg + cx - 1) / cx;
+  const int tiles = c.G * p.n_oblk * p.n_cblk;
+  p.n_tiles = tiles;
+  p.slots = 8 * p.ct * T;
+  const int target = plan->opt.dw_workgroups > 0 ? plan->opt.dw_workgroups : 256;
+  int splits = std::max(1, std::min(p.n_chunks, target / std::max(1, tiles)));
+  while (splits > 1 && (int64_t)splits * tiles * p.slots * 1024 > (40ll << 20)) splits /= 2;
+  p.chunks_per_split = (p.n_chunks + splits - 1) / splits;
+  p.rows_per_split = 0;
+  p.n_splits = (p.n_chunks + p.chunks_per_split - 1) / p.chunks_per_split;
+  p.lds_bytes = std::max(2 * 64 * kGUnits * 16 + kPlanes * cx * p.CPp * 2, 4 * 2 * p.ct * T * 1024);
+  return p.lds_bytes <= 160 * 1024;
+}
+
 bool fill_any(const syno_plan* plan, DwParams& p) {
-  return plan->in_dtype == SYNO_BF16 ? fill_dw(plan, p) : fill_dw_f32(plan, p);
+  if (plan->in_dtype == SYNO_BF16) return fill_dw(plan, p);
+  return fill_dw_split(plan, p) || fill_dw_f32(plan, p);
 }
 
 }  // namespace
@@ -1294,6 +1362,11 @@ std::string mfma_dw_describe(const syno_plan* plan) {
   DwParams p;
   memcpy(&p, plan->launch[SYNO_BWD_WEIGHT].params, sizeof p);
   char b[256];
+  if (p.parts) {
+    snprintf(b, sizeof b, "bf16-parts pixels/chunk=%d pitch=%d chunks=%d splits=%d grid=%d lds=%dB", kStreamChunk, p.pitch, p.n_chunks, p.n_splits,
+             p.G * p.n_oblk * p.n_cblk * p.n_splits, p.lds_bytes);
+    return b;
+  }
   snprintf(b, sizeof b, "rows/chunk=%d(+%d) pitch=%d chunks=%d splits=%d grid=%d lds=%dB", p.TRK, p.KH - 1, p.pitch, p.n_chunks,
            p.n_splits, p.G * p.n_oblk * p.n_cblk * p.n_splits, p.lds_bytes);
   return b;
@@ -1333,7 +1406,14 @@ syno_status launch_mfma_dw(const syno_plan* plan, const void* A, const void* B, 
     const float* Xf = static_cast<const float*>(B);
     by_window([&](auto kh_c, auto kw_c, auto ct_c) {
       constexpr int kh = decltype(kh_c)::value, kw = decltype(kw_c)::value, ct = decltype(ct_c)::value;
-      if (kh == 3 && p.direct) {
+      if (p.parts) {
+        if constexpr (kh <= 3 && kw <= 3) {
+          if (p.W % 8 == 0) launch_dw_kernel(dw_split<kh, kw, ct, 4, true>, grid, p, Gf, Xf, dst, stream, 512);
+          else if (p.W % 4 == 0) launch_dw_kernel(dw_split<kh, kw, ct, 4, false>, grid, p, Gf, Xf, dst, stream, 512);
+          else if (p.W % 2 == 0) launch_dw_kernel(dw_split<kh, kw, ct, 2, false>, grid, p, Gf, Xf, dst, stream, 512);
+          else launch_dw_kernel(dw_split<kh, kw, ct, 1, false>, grid, p, Gf, Xf, dst, stream, 512);
+        }
+      } else if (kh == 3 && p.direct) {
         if constexpr (kh == 3) {
         if (p.mode == 4) launch_dw_kernel(dw_rows_f32<kw, ct, 4>, grid, p, Gf, Xf, dst, stream, kRowsThreads);
         else if (p.mode == 7) launch_dw_kernel(dw_rows_f32<kw, ct, 7>, grid, p, Gf, Xf, dst, stream, kRowsThreads);
@@ -1374,10 +1454,10 @@ syno_status launch_mfma_dw(const syno_plan* plan, const void* A, const void* B, 
     // (written by the contraction itself)
   } else if (p.n_splits > 4 && p.n_tiles * (p.slots / (p.KH * p.KW)) < 256)
     hipLaunchKernelGGL(dw_reduce_slots, dim3(p.n_tiles * p.slots), dim3(256), 0, stream, p,
-                       reinterpret_cast<const float4*>(ws), static_cast<float*>(out));
+                       reinterpret_cast<const float4*>(ws), static_cast<float*>(out), static_cast<const float*>(A), static_cast<const float*>(B));
   else
     hipLaunchKernelGGL(dw_reduce_tiles, dim3(p.n_tiles * (p.slots / (p.KH * p.KW))), dim3(256), 0, stream, p,
-                       reinterpret_cast<const float4*>(ws), static_cast<float*>(out));
+                       reinterpret_cast<const float4*>(ws), static_cast<float*>(out), static_cast<const float*>(A), static_cast<const float*>(B));
   return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
 }
 

@@ -69,11 +69,87 @@ def test_values_that_parts_do_not_stand_for(syno, cfg):  # noqa: F811
     agree(torch.zeros_like(X), W)
 
 
+# backward-weight: widths that divide by 8 (rows without a zero between them), 4, 2 and nothing; one chunk per workgroup and
+# many; images smaller than a chunk; channel counts inside a block; the windows it has; a bound on the workgroups
+DW_CASES = {
+    "3x3_w8": (lambda: wl.make_conv(3, 40, 11, seed=41, Co=72, Wd=8, with_grad=True), (0, 1, 5)),
+    "3x3_w56": (lambda: wl.make_conv(2, 32, 7, seed=42, Co=70, Wd=56, with_grad=True), (0, 3)),
+    "3x3_w20": (lambda: wl.make_conv(3, 33, 6, seed=43, Co=64, Wd=20, with_grad=True), (0, 2)),
+    "3x3_w14": (lambda: wl.make_conv(4, 35, 5, seed=44, Co=65, Wd=14, with_grad=True), (0, 7)),
+    "3x3_w7": (lambda: wl.make_conv(9, 64, 7, seed=45, Co=130, Wd=7, with_grad=True), (0, 4)),
+    "3x3_one_row": (lambda: wl.make_conv(31, 16, 1, seed=46, Co=24, Wd=5, with_grad=True), (0, 1)),
+    "3x3_wide": (lambda: wl.make_conv(1, 24, 3, seed=47, Co=40, Wd=199, with_grad=True), (0, 2)),
+    "1x1_w10": (lambda: wl.make_conv(3, 72, 10, seed=48, Co=136, Wd=10, K=1, with_grad=True), (0, 3)),
+    "1x1_w16": (lambda: wl.make_conv(5, 65, 3, seed=49, Co=63, Wd=16, K=1, with_grad=True), (0, 1)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,groups", [(n, g) for n, v in DW_CASES.items() for g in v[1]])
+def test_weight_gradient_parity_at_the_edges(syno, oracle, name, groups):  # noqa: F811
+    w = DW_CASES[name][0]()
+    assert "bf16-parts" in syno.Plan(w.desc, dw_workgroups=groups).describe(2)
+    run_all(syno, oracle, w, 0, directions=(2,), dw_workgroups=groups)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("KH,KW", ((3, 1), (1, 3)))
+@pytest.mark.parametrize("N,C,O,H,W", ((2, 64, 64, 9, 30), (3, 72, 80, 12, 21), (4, 65, 63, 1, 24), (5, 100, 40, 5, 6)))
+def test_weight_gradient_of_one_sided_windows(syno, N, C, O, H, W, KH, KW):  # noqa: F811
+    """Against the sum of its terms in fp64.  Every term is within 2^-22 of its product's size (nine parts less the three
+    smallest), a chunk's sum of 64 is rounded twice, and the chunks and splits (fewer than 64 here) add up in fp32."""
+    p = syno.Plan(wl.conv2d(N, C, O, H, W, KH, KW))
+    assert "bf16-parts" in p.describe(2)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    X, G = torch.randn(p.x_shape, generator=gen, device="cuda"), torch.randn(p.out_shape, generator=gen, device="cuda")
+    got = p.backward_weight(X, G).double()
+
+    def sums(x, g):
+        x = torch.nn.functional.pad(x, (KW // 2, KW // 2, KH // 2, KH // 2))
+        return torch.stack([torch.stack([g.transpose(0, 1).reshape(O, -1) @ x[:, :, a:a + H, b:b + W].transpose(0, 1).reshape(C, -1).t().contiguous()
+                                         for b in range(KW)], -1) for a in range(KH)], -2)
+    whole, size = sums(X.double(), G.double()), sums(X.double().abs(), G.double().abs())
+    assert bool(((got - whole).abs() <= size * (2.0 ** -22 + 64 * 2.0 ** -24)).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("groups", (0, 1))
+def test_weight_gradient_of_values_that_parts_do_not_stand_for(syno, groups):  # noqa: F811
+    d = wl.conv2d(2, 40, 48, 10, 12)
+    parts, plain = syno.Plan(d, dw_workgroups=groups), syno.Plan(d, kernel_policy=1)
+    assert "bf16-parts" in parts.describe(2)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    X, G = torch.randn(parts.x_shape, generator=gen, device="cuda"), torch.randn(parts.out_shape, generator=gen, device="cuda") / 20
+
+    def agree(x, g):
+        a, b = parts.backward_weight(x, g), plain.backward_weight(x, g)
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.isposinf(a), torch.isposinf(b))
+        assert torch.equal(torch.isneginf(a), torch.isneginf(b))
+        fine = torch.isfinite(b)
+        # 240 terms in fp32 on either side; the largest subnormal step for results that are subnormal themselves
+        assert float((a - b)[fine].double().abs().max()) <= 2e-5 * float(b[fine].double().abs().max()) + 2e-45 * 300
+
+    Y, V = X.clone(), G.clone()
+    Y[0, 3, 5, 5], Y[0, 39, 0, 0], Y[1, 7, 9, 11] = float("inf"), float("-inf"), float("nan")
+    agree(Y, G)
+    V[0, 3, 1, 1], V[1, 40, 0, 2] = float("inf"), float("nan")
+    agree(X, V)
+    Z = X.clone()
+    Z[0, 0, 2, 2] = 3.4e38            # rounds to infinity as a bf16 value
+    agree(Z, G * 1e-3)
+    for scale in (1e30, 1e-30, 1e-36, 1e-41):
+        agree(X * scale, G)
+    agree(torch.zeros_like(X), G)
+
+
 def test_where_the_planner_takes_it():
     import paper_2410_23745_amd as s
     for C, H in wl.RESNET18_STAGES:
         p = s.Plan(wl.conv2d(32, C, C, H, H))
-        assert all("bf16-parts" in p.describe(which) for which in (0, 1))
+        assert all("bf16-parts" in p.describe(which) for which in (0, 1, 2))
+    # rows that would be mostly filling, one chunk of pixels, a window it does not have
+    for d in (wl.conv2d(32, 64, 64, 56, 4), wl.conv2d(1, 1024, 1024, 7, 7), wl.conv2d(32, 64, 64, 56, 56, 1, 5)):
+        assert "bf16-parts" not in s.Plan(d).describe(2)
     # too little work for it, a window or weight layout that it does not have, a named variant of the other kernel
     for p in (s.Plan(wl.conv2d(1, 16, 16, 16, 16)), s.Plan(wl.conv2d(32, 64, 64, 56, 56, 5, 5)),
               s.Plan(wl.conv2d(32, 64, 64, 28, 28, 3, 3, F32, F32, (1, 0, 2, 3))), s.Plan(wl.conv2d(32, 64, 64, 28, 28), mfma_variant=4, mfma_rows=7)):
