@@ -105,6 +105,7 @@ syno_status run(const syno_plan* plan, int which, const void* A, const void* B, 
       if (which == SYNO_BWD_WEIGHT) return syno::launch_mfma_dw(plan, A, B, out, ws, stream);
       return syno::launch_mfma(plan, which, A, B, out, ws, stream);
     case syno::KERNEL_MFMA_TRANSPOSED:
+      if (L.params_ready) return syno::launch_gemm(plan, which, A, B, out, ws, stream);
       // forward: the weight is the image and the input the filter; the gradients keep their operand order
       // (upstream gradient first) and only name the other contraction of the inner plan
       if (which == SYNO_FWD) return run(plan->inner, SYNO_FWD, B, A, out, ws, stream);
@@ -261,6 +262,10 @@ syno_status syno_plan_describe(const syno_plan* plan, int which, char* buf, size
     }
     case syno::KERNEL_MFMA_TRANSPOSED: {
       char inner[400];
+      if (plan->launch[which].params_ready) {
+        d += " " + syno::gemm_describe(plan, which);
+        break;
+      }
       if (plan->launch[which].variant == syno::kViaTransposedCopy) {
         if (syno_plan_describe(plan->inner_dx, SYNO_FWD, inner, sizeof(inner)) == SYNO_OK)
           d += std::string(" as the product G * W^T (transposed copy of W), a 1x1 convolution: ") + inner;

@@ -220,6 +220,11 @@ syno_status launch_rows(const syno_plan* p, int which, const void* A, const void
 // kernels_mfma.hip: dst[c][r] = src[r][c] for a row-major rows x cols matrix of 2- or 4-byte elements
 constexpr int kViaTransposedCopy = 100;
 syno_status launch_transpose_2d(const void* src, void* dst, int64_t rows, int64_t cols, int elem_bytes, hipStream_t stream);
+// kernels_gemm_bf16.hip: contraction `which` of the bf16 product [M x K] * [K x N] on its operands as they lie;
+// gemm_configure fills launch[which].params and sets .workspace
+bool gemm_configure(syno_plan* p, int which, int64_t M, int64_t K, int64_t N);
+std::string gemm_describe(const syno_plan* p, int which);
+syno_status launch_gemm(const syno_plan* p, int which, const void* A, const void* B, void* out, void* ws, hipStream_t stream);
 // kernels_mfma.hip, gradients of a strided convolution through the phase planes:
 // (s = the phases per axis that take part: the stride, or 1 when only phase (0,0) is read)
 // dW[o,c,kh,kw] (any strides) = dWp[o][(c*s+a)*s+b][th][tw] with s*dh+a = kh-p, th = dh+1 (window 3) or 0 (window 1)

@@ -1428,6 +1428,8 @@ syno_status build_plan(const syno_desc* desc, syno_plan* plan, std::string* why)
         }
       }
     }
+    for (int which = 0; which < 3; ++which)
+      if (plan->launch[which].kernel == KERNEL_MFMA_TRANSPOSED) plan->launch[which].params_ready = gemm_configure(plan, which, M, K, N);
   }
   return SYNO_OK;
 }
