@@ -82,7 +82,8 @@ typedef struct {
  * the summation order.  Read once, while the plan is built.
  *   kernel_policy   1: every pass runs on the generic index-program kernels
  *   mfma_variant    1 + index of the contraction kernel's tile variant (forward and backward-data), or -1 for the
- *                   row-streaming member of the family (bf16, at most 64 channels per group);
+ *                   row-streaming member of the family (bf16, at most 64 channels per group), or -2 - index of a tile
+ *                   configuration of the fp32 contraction on the bf16 matrix cores;
  *                   mfma_rows = output rows per workgroup tile.  Ignored unless the pair fits the operator.
  *   mfma_taps       1: one window tap per inner step even where three would be taken
  *   mfma_splits     number of workgroups that share one output tile of the contraction kernel, each summing a
