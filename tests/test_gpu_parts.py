@@ -1,4 +1,4 @@
-"""The fp32 contraction on the bf16 matrix cores (every value split into three bf16 parts): parity with the checker at the
+"""The fp32 contraction on the bf16 matrix cores (every value split into three bf16 parts): parity with the oracle at the
 edges of its tiles, chunks and stages, and the values that parts cannot stand for."""
 import numpy as np
 import pytest
