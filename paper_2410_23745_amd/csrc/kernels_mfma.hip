@@ -451,6 +451,8 @@ bool fill_split(const syno_plan* plan, int which, int cfg, int TR, SplitParams& 
   p.TR = TR;
   p.BN = v.WN * v.TN * 16;
   if (p.Cg < kSplitChannels || p.Cg % (p.BN / 16) != 0) return false;
+  // a lane's first weight is a 32-bit byte offset from the block's: the last output channel's last channels must be in reach
+  if (((int64_t)(std::min(p.BN, p.Og) - 1) * p.ws_o + (int64_t)(kSplitChannels - p.BN / 16) * p.ws_c) * 4 >= (1ll << 32)) return false;
   p.KC = kSplitChannels;
   p.cgrps = 4;
   p.n_chunks = (p.Cg + p.KC - 1) / p.KC;

@@ -154,3 +154,19 @@ def test_where_the_planner_takes_it():
     for p in (s.Plan(wl.conv2d(1, 16, 16, 16, 16)), s.Plan(wl.conv2d(32, 64, 64, 56, 56, 5, 5)),
               s.Plan(wl.conv2d(32, 64, 64, 28, 28, 3, 3, F32, F32, (1, 0, 2, 3))), s.Plan(wl.conv2d(32, 64, 64, 28, 28), mfma_variant=4, mfma_rows=7)):
         assert all("bf16-parts" not in p.describe(which) for which in (0, 1))
+
+
+def test_weights_out_of_reach_of_a_lane_offset():
+    """A workgroup's weights are addressed by 32-bit byte offsets from its first one: output channels (or, in the adjoint,
+    forward output channels) so far apart that the last of a tile lies 4 GiB on are not its work."""
+    import paper_2410_23745_amd as s
+    # 24 channels of a chunk apart: 24 * stride * 4 bytes reach 2^32 at 44739243 weights per channel
+    for d, which in ((wl.matmul(40, 16, 48234496), 2), (wl.conv2d(1, 50331648, 40, 5, 5, 1, 1), 1)):
+        assert "bf16-parts" not in s.Plan(d).describe(which)
+    for d in (wl.matmul(40, 16, 44739232), wl.conv2d(1, 44739232, 40, 5, 5, 1, 1)):
+        assert any("bf16-parts" in s.Plan(d).describe(which) for which in (1, 2))
+    # 127 output channels of a tile apart: 127 * stride + 24 weights reach 2^30 at 8454661 weights each
+    far, near = wl.conv2d(1, 8454664, 128, 3, 3, 1, 1), wl.conv2d(1, 8454656, 128, 3, 3, 1, 1)
+    assert "bf16-parts" not in s.Plan(far, mfma_variant=-5).describe(0) and "bf16-parts" in s.Plan(near, mfma_variant=-5).describe(0)
+    # (channels that the tile has no more of do not count)
+    assert "bf16-parts" in s.Plan(wl.conv2d(1, 8454664, 40, 3, 3, 1, 1), mfma_variant=-5).describe(0)
