@@ -266,13 +266,16 @@ bool gemm_configure(syno_plan* plan, int which, int64_t M, int64_t K, int64_t N)
   p.probe = static_cast<long long*>(o.clock_probe);
   double best = 1e30;
   const int steps = (p.K + kStepK - 1) / kStepK;
+  // the splits' sums, written and read: those of the weight gradient fit the scratch of the entry point without a workspace
+  // (32 MiB), the others stay below 64 MiB
+  const int64_t limit = 2ll * (which == SYNO_BWD_WEIGHT ? SYNO_STATIC_SCRATCH_BYTES : 64ll << 20);
   for (int c = 0; c < kConfigs; ++c) {
     const int n_m = (p.M + kTiles[c][0] - 1) / kTiles[c][0], n_n = (p.N + kTiles[c][1] - 1) / kTiles[c][1];
     for (int splits = 1; splits <= 16 && splits <= steps; ++splits) {      // (43 splits of 8192x128x128's dW: 19 us, 16: 14)
       const int per = (steps + splits - 1) / splits;
       if ((steps + per - 1) / per != splits) continue;
       const int64_t blocks = (int64_t)n_m * n_n * splits, bytes = (int64_t)splits * p.M * p.N * 8;
-      if (blocks >= (1 << 30) || (splits > 1 && bytes > (128ll << 20))) continue;
+      if (blocks >= (1 << 30) || (splits > 1 && bytes > limit)) continue;
       const double step = std::max(kTiles[c][0] * kTiles[c][1] / 32., (kTiles[c][0] + kTiles[c][1]) * 3.2);
       const double cost = (double)((blocks + 255) / 256) * (per * step + 4000.) + (splits > 1 ? 6000. + bytes / 1800. : 0.);
       if (cost < best) {

@@ -45,3 +45,11 @@ def test_which_products_are_taken():
     # fp32 operands, an axis that is no multiple of 8, a named number of splits
     for p in (s.Plan(wl.matmul(256, 256, 256)), s.Plan(wl.matmul(256, 256, 252, BF16, F32)), s.Plan(wl.matmul(256, 256, 256, BF16, F32), mfma_splits=2)):
         assert all(" as it is: " not in p.describe(which) for which in range(3))
+
+
+@pytest.mark.parametrize("M,N,K", ((11136, 8432, 200), (23992, 17816, 96), (16136, 13584, 216), (16384, 2048, 768), (10240, 1536, 2048)))
+def test_sums_of_the_weight_gradients_splits_fit_the_static_scratch(M, N, K):
+    """The entry point without a workspace has 32 MiB (it took the first three on the convolution kernels too)."""
+    import paper_2410_23745_amd as s
+    p = s.Plan(wl.matmul(M, N, K, BF16, F32))
+    assert " as it is: " in p.describe(2) and p.workspace_bytes(2) <= 32 << 20
