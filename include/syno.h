@@ -150,7 +150,9 @@ syno_status syno_backward_weight(const syno_plan* plan, const void* X, const voi
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the split partial sums live in a
  * buffer inside the library, SYNO_STATIC_SCRATCH_BYTES of static device memory per GPU, instead of a caller's
  * workspace.  Same result as syno_backward_weight, bit for bit.  Allocates nothing and never synchronises.
- * SYNO_ERR_SCRATCH when syno_plan_workspace_bytes(plan, SYNO_BWD_WEIGHT) exceeds the buffer.  All calls on one
+ * SYNO_ERR_SCRATCH when syno_plan_workspace_bytes(plan, SYNO_BWD_WEIGHT) exceeds the buffer; except that fp32
+ * operators with rows that only the bf16 matrix cores' kernel takes run on the index program then, which needs no
+ * scratch, is slower and sums in its own order (syno_plan_describe says so).  All calls on one
  * GPU share the one buffer: calls that may overlap on a GPU (different streams or threads) race. */
 #define SYNO_STATIC_SCRATCH_BYTES (32u << 20)
 syno_status syno_backward_weight_static(const syno_plan* plan, const void* X, const void* G, void* dW,

@@ -207,7 +207,8 @@ syno_status syno_backward_weight_static(const syno_plan* plan, const void* X, co
                                         hipStream_t stream) {
   if (!plan || !X || !G || !dW) return SYNO_ERR_NULL;
   const size_t need = plan->launch[SYNO_BWD_WEIGHT].workspace;
-  if (need > SYNO_STATIC_SCRATCH_BYTES) return SYNO_ERR_SCRATCH;
+  if (need > SYNO_STATIC_SCRATCH_BYTES)
+    return plan->launch[SYNO_BWD_WEIGHT].static_generic ? syno::launch_generic(plan, SYNO_BWD_WEIGHT, G, X, dW, stream) : SYNO_ERR_SCRATCH;
   void* ws = nullptr;
   if (need) {
     ws = static_scratch();
@@ -275,6 +276,8 @@ syno_status syno_plan_describe(const syno_plan* plan, int which, char* buf, size
     }
     default: break;
   }
+  if (which == SYNO_BWD_WEIGHT && plan->launch[which].static_generic && plan->launch[which].workspace > SYNO_STATIC_SCRATCH_BYTES)
+    d += " (without a workspace: index program)";
   snprintf(buf, size, "%s", d.c_str());
   return SYNO_OK;
 }

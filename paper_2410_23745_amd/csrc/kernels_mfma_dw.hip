@@ -1355,6 +1355,10 @@ void mfma_dw_configure(syno_plan* plan) {
   L.variant = 0;
   // one 64 x 32*ct x taps tile of fp32 sums per workgroup (whole tiles also where Og or Cg end inside one)
   L.workspace = dp.n_splits == 1 ? 0 : (size_t)dp.n_splits * dp.n_tiles * dp.slots * 1024;
+  // problems that only dw_split takes (the fp32 instructions' kernels stage whole rows, which are too wide here): whatever
+  // workspace it, or a plan around it, needs, the entry point without one has them on the index program
+  DwParams f32;
+  L.static_generic = dp.parts && !fill_dw_f32(plan, f32);
 }
 
 std::string mfma_dw_describe(const syno_plan* plan) {

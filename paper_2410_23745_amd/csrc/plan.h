@@ -123,6 +123,8 @@ struct Launch {
   // the family's kernel parameter record, filled when the plan is configured so that a launch only copies it
   alignas(8) unsigned char params[1536] = {};
   bool params_ready = false;
+  // backward-weight: the entry point without a workspace runs the index program where `workspace` exceeds its scratch
+  bool static_generic = false;
 };
 
 }  // namespace syno

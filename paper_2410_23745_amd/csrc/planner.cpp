@@ -1350,6 +1350,7 @@ syno_status build_plan(const syno_desc* desc, syno_plan* plan, std::string* why)
           L.kernel = KERNEL_MFMA_PHASES;
           L.workspace = round_up((size_t)plane_elems * esz) + round_up((size_t)c.Og * CP * window * window * 4) +
                         cw->launch[SYNO_BWD_WEIGHT].workspace;
+          L.static_generic = cw->launch[SYNO_BWD_WEIGHT].static_generic;
         } else {
           delete v; delete cw;
         }

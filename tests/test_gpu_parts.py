@@ -6,6 +6,7 @@ import torch
 
 from syno_inputs import F32, workloads as wl
 from test_gpu_parity import run_all, syno  # noqa: F401  (fixture)
+from util import assert_close, to_dev, to_host, tol_for
 
 # tile configurations: 0 = 64 output channels, 1 = 32 with the taps of a window dealt to two waves, 2 = to four,
 # 3 = 128 output channels of a 1x1 window
@@ -170,3 +171,32 @@ def test_weights_out_of_reach_of_a_lane_offset():
     assert "bf16-parts" not in s.Plan(far, mfma_variant=-5).describe(0) and "bf16-parts" in s.Plan(near, mfma_variant=-5).describe(0)
     # (channels that the tile has no more of do not count)
     assert "bf16-parts" in s.Plan(wl.conv2d(1, 8454664, 40, 3, 3, 1, 1), mfma_variant=-5).describe(0)
+
+
+# strided, rows wider than the fp32 instructions' kernel stages: the phase planes of X and the spread weights need 40 MB
+WIDE_STRIDED = dict(N=28, C=21, H=38, seed=51, Co=11, Wd=59, stride=2, with_grad=True)
+
+
+def test_which_calls_without_a_workspace_keep_the_index_program():
+    import paper_2410_23745_amd as s
+    f = WIDE_STRIDED
+    p = s.Plan(wl.conv2d(f["N"], f["C"], f["Co"], f["H"], f["Wd"], stride=2))
+    assert p.kernel(2) == "mfma_contraction_phases" and p.workspace_bytes(2) > 32 << 20
+    assert p.describe(2).endswith("(without a workspace: index program)")
+    # the scratch is enough; the fp32 instructions have the stride-1 problem too (never taken without a workspace)
+    for d in (wl.conv2d(2, 21, 11, 38, 59, stride=2), wl.conv2d(64, 64, 128, 56, 56, stride=2)):
+        assert s.Plan(d).kernel(2) == "mfma_contraction_phases" and "without a workspace" not in s.Plan(d).describe(2)
+
+
+@pytest.mark.gpu
+def test_weight_gradient_without_a_workspace_beyond_the_scratch(syno, oracle):  # noqa: F811
+    """The entry point without a workspace takes the call on the index program, whatever the other one does."""
+    w = wl.make_conv(**WIDE_STRIDED)
+    p = syno.Plan(w.desc)
+    X, G = to_dev(w.X, w.X_bits), to_dev(w.G, w.G_bits)
+    got = {"workspace": p.backward_weight(X, G), "static": torch.full(p.w_shape, float("nan"), device="cuda")}
+    p.backward_weight_static(X, G, got["static"])
+    _, dw = oracle.backward(w.desc, w.X, w.W, w.G, False, True)
+    _, mdw = oracle.backward(w.desc, np.abs(w.X), np.abs(w.W), np.abs(w.G), False, True)
+    for name, v in got.items():
+        assert_close(to_host(v), dw, mdw, p.free_size(2), False, "backward-weight " + name, tol_for(w.desc))
