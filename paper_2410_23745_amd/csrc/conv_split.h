@@ -452,11 +452,8 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     const int n = fdiv(rho, p.m_ho), px = (rho - n * p.Ho) * p.Wo + (m0 - i0 * p.Wo);
     const int64_t off = (int64_t)n * p.os_n + (int64_t)(g * p.Og + o) * p.os_o + px;
     v *= kResultScale;
-    // (two tests for four values first; a zero passes the precise one)
-    const float sum = fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]);
-    const float least = fminf(fminf(fabsf(v[0]), fabsf(v[1])), fminf(fabsf(v[2]), fabsf(v[3])));
-    if (!(sum <= 3.4028234663852886e38f && least >= kLeastResult))
-      odd |= !(trusted_result(v[0]) && trusted_result(v[1]) && trusted_result(v[2]) && trusted_result(v[3]));
+    // (one test for the four values; each is looked at again below)
+    odd |= !trusted_result(fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]));
     if (m0 + 3 < block_px && px + 3 < img_px && (off & 3) == 0) {
       *reinterpret_cast<float4*>(op + off) = make_float4(v[0], v[1], v[2], v[3]);
     } else {

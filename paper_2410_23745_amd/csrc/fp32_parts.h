@@ -23,12 +23,12 @@ __device__ __forceinline__ uint32_t round_pair(float lo, float hi) {      // v_c
 }
 
 // (x0, x1) -> the two values' parts, packed pairwise, times 2^24: the bf16 matrix instructions take subnormal operands for
-// zero, and this keeps the smallest part of every normal fp32 value normal (and the largest one of a subnormal).  The last
+// zero, and a multiple of 2^-149 becomes one of 2^-125, so that no part of any fp32 value, subnormal ones included, is a
+// subnormal; what the instructions drop of a sum is below 2^-126 / 2^48.  The last
 // remainder has at most 8 significant bits: its upper half is the value itself.  An infinity, a NaN or a value above 2^104
 // leaves a NaN in m or l, so every result that it takes part in is a NaN and is summed again when it is stored; so
-// are sums beyond 2^80, and results below 2^-80, which subnormal operands may have had a part in.
+// are sums beyond 2^80.
 constexpr float kPartScale = 16777216.f, kResultScale = 1.f / (16777216.f * 16777216.f);
-constexpr float kLeastResult = 8.271806125530277e-25f;      // 2^-80
 __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
   x0 *= kPartScale;
   x1 *= kPartScale;
@@ -39,10 +39,9 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& h, uint
   l = __builtin_amdgcn_perm(__float_as_uint(s1), __float_as_uint(s0), 0x07060302u);
 }
 
-// Whether a result can be what the parts' sum is (a zero may be a sum of zeros)
-__device__ __forceinline__ bool trusted_result(float v) {
-  return v == 0.f || (fabsf(v) >= kLeastResult && fabsf(v) <= 3.4028234663852886e38f);
-}
+// Whether a result is what the parts' sum is
+constexpr float kMostResult = 3.4028234663852886e38f;
+__device__ __forceinline__ bool trusted_result(float v) { return fabsf(v) <= kMostResult; }
 
 }  // namespace
 }  // namespace syno

@@ -173,6 +173,45 @@ def test_weights_out_of_reach_of_a_lane_offset():
     assert "bf16-parts" in s.Plan(wl.conv2d(1, 8454664, 40, 3, 3, 1, 1), mfma_variant=-5).describe(0)
 
 
+def least_time(call, n=5):
+    """us between events, the least of n calls"""
+    best = float("inf")
+    for _ in range(n + 1):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scale", (1e-25, 1e-30, 1e-37, 1e-40))
+def test_small_values_are_ordinary_ones(syno, scale):  # noqa: F811
+    """Values down to the subnormal ones have whole parts: every result is within 2^-22 of the size of its terms (nine parts
+    less the three smallest, sums of 32 or 64 terms rounded twice, at most 64 of them here), and of 2^-149 times the partial
+    sums that are stored as subnormals; and no call takes another way for them, which would be a hundred times slower."""
+    p = syno.Plan(wl.conv2d(8, 64, 64, 28, 28), mfma_variant=-2)
+    assert all("bf16-parts" in p.describe(which) for which in range(3))
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    X, G, W = (torch.randn(s, generator=gen, device="cuda") for s in (p.x_shape, p.out_shape, p.w_shape))
+    x, g = X * scale, G * scale
+    calls = (lambda x, g: p.forward(x, W), lambda x, g: p.backward_data(g, W), lambda x, g: p.backward_weight(X, g))
+    conv = torch.nn.functional.conv2d
+
+    def weight_sums(a, b):
+        return conv(a.transpose(0, 1).contiguous(), b.transpose(0, 1).contiguous(), padding=1).transpose(0, 1)
+
+    Wb = W.flip(2, 3).transpose(0, 1).contiguous()
+    for which, (a, b, sums) in enumerate(((x, W, lambda a, b: conv(a, b, padding=1)), (g, Wb, lambda a, b: conv(a, b, padding=1)), (X, g, weight_sums))):
+        a, b = a.double().cpu(), b.double().cpu()
+        got, whole, size = calls[which](x, g).double().cpu(), sums(a, b), sums(a.abs(), b.abs())
+        assert bool(((got - whole).abs() <= size * (2.0 ** -22 + 64 * 2.0 ** -24) + 300 * 2.0 ** -149).all()), which
+        slow, plain = least_time(lambda: calls[which](x, g)), least_time(lambda: calls[which](X, G))
+        assert slow <= 4 * plain + 50, (which, slow, plain)
+
+
 # strided, rows wider than the fp32 instructions' kernel stages: the phase planes of X and the spread weights need 40 MB
 WIDE_STRIDED = dict(N=28, C=21, H=38, seed=51, Co=11, Wd=59, stride=2, with_grad=True)
 
