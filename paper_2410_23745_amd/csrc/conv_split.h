@@ -36,26 +36,53 @@ __device__ __forceinline__ int split_slot(const SplitParams& p, int R0, int rows
   return -1;
 }
 
-// One result element summed plainly in fp64, for the (o, pixel) whose parts do not stand for their values
-__device__ __forceinline__ float split_exact(const SplitParams& p, const float* __restrict__ X, const float* __restrict__ W,
-                                                       int g, int o, int rho, int w, int c_begin, int c_end, bool adj) {
-  const int n = rho / p.Ho, h = rho - n * p.Ho;
-  double acc = 0.;
-  for (int kh = 0; kh < p.KH; ++kh) {
-    int r = h * p.sh + kh - p.ph;
-    if (p.h_wrap) r = (h + p.h_shift + p.h_shift_g * g) % p.Hi;
-    if (r < 0 || r >= p.Hi) continue;
-    for (int kw = 0; kw < p.KW; ++kw) {
-      const int x = w * p.sw + kw - p.pw;
-      if (x < 0 || x >= p.Wi) continue;
-      const int tap = kh * p.KW + kw;
-      const float* xs = X + (int64_t)n * p.xs_n + (int64_t)g * p.Cg * p.xs_c + (int64_t)r * p.Wi + x;
-      const float* ws = W + (int64_t)g * p.ws_g + (int64_t)o * p.ws_o + (adj ? p.KH * p.KW - 1 - tap : tap);
-      for (int c = c_begin; c < c_end; ++c) acc = fma((double)xs[(int64_t)c * p.xs_c], (double)ws[(int64_t)c * p.ws_c], acc);
-      if (acc != acc) break;      // (nothing makes a number of it again)
+// A 16 x 16 tile of results (pixels m0.. of the block, output channels o0.. of the group) with the fp32 matrix instructions,
+// on the operands where they lie: for tiles with results that the parts cannot give, by the wave that stores them.  A tap's
+// sum joins a result only where the tap lies inside the image.  Lane: pixels 4 * (lane / 16) + 0..3, channel lane % 16.
+// Bound by the loads' round trips: 32x64x64 56x56 takes 139 us with one infinity in X and 330 of NaNs alone, 62 without.
+template <int T, bool ADJ>
+__device__ __forceinline__ floatx4 split_plain_tile(const SplitParams& p, const float* __restrict__ X, const float* __restrict__ W,
+                                                    int g, int o0, int R0, int m0, int block_px, int lane) {
+  auto place = [&](int m, int& n, int& h, int& w) {
+    const int i = fdiv(m, p.m_wo);
+    w = m - i * p.Wo;
+    n = fdiv(R0 + i, p.m_ho);
+    h = R0 + i - n * p.Ho;
+  };
+  auto row_of = [&](int h, int kh) { return p.h_wrap ? (h + p.h_shift + p.h_shift_g * g) % p.Hi : h * p.sh + kh - p.ph; };
+  int n, h, w, at[T];
+  place(min(m0 + (lane & 15), block_px - 1), n, h, w);
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int kh = t / p.KW, r = row_of(h, kh), x = w * p.sw + t - kh * p.KW - p.pw;
+    at[t] = n * p.xs_n + min(max(r, 0), p.Hi - 1) * p.Wi + min(max(x, 0), p.Wi - 1);
+  }
+  const float* const xg = X + (int64_t)g * p.Cg * p.xs_c;
+  const float* const wo = W + (int64_t)g * p.ws_g + (int64_t)min(o0 + (lane & 15), p.Og - 1) * p.ws_o;
+  floatx4 sum[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) sum[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < p.Cg; c0 += 4) {
+    const int c = min(c0 + (lane >> 4), p.Cg - 1);
+    const bool live = c0 + (lane >> 4) < p.Cg;
+    const float *const xc = xg + (int64_t)c * p.xs_c, *const wc = wo + (int64_t)c * p.ws_c;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const float a = xc[at[t]], b = wc[ADJ ? T - 1 - t : t];
+      sum[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? a : 0.f, live ? b : 0.f, sum[t], 0, 0, 0);
     }
   }
-  return (float)acc;
+  floatx4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    place(min(m0 + 4 * (lane >> 4) + j, block_px - 1), n, h, w);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int kh = t / p.KW, r = row_of(h, kh), x = w * p.sw + t - kh * p.KW - p.pw;
+      if (r >= 0 && r < p.Hi && x >= 0 && x < p.Wi) v[j] += sum[t][j];
+    }
+  }
+  return v;
 }
 
 // A workgroup (8 waves, one per CU) owns TR whole result rows x BN output channels, like conv_mfma, and walks the reduction
@@ -438,7 +465,6 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   // ---- store: lane holds 4 consecutive pixels (rows of D) of one channel (column of D)
   const int img_px = p.Ho * p.Wo;
   float* const op = out + (int64_t)ksp * p.split_stride;
-  const int c_begin = ch_begin * kSplitChannels, c_end = min(p.Cg, ch_end * kSplitChannels);
   bool odd = false;                // some result of this lane is none that the parts can give
   auto element = [&](int m, int o) -> int64_t {       // pixel m of the block, output channel o -> element of the result
     const int i = fdiv(m, p.m_wo), r = R0 + i, n = fdiv(r, p.m_ho);
@@ -486,16 +512,23 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     }
   }
   // (see split_pair)
-  if (odd) {
+  if (__any(odd)) {
+#pragma unroll 1
     for (int i = first_tile; i < NTL * TN; i += tile_step) {
-      const int t = i / TN, o = nb * BN + (wn * TN + i % TN) * 16 + (lane & 15);
+      const int t = i / TN, o0 = nb * BN + (wn * TN + i % TN) * 16, o = o0 + (lane & 15);
+      const int m0 = (my_first + t) * 16, m = m0 + 4 * (lane >> 4);
+      if (t >= my_tiles || o0 >= p.Og) continue;
+      bool again[4], any = false;
+#pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int m = (my_first + t) * 16 + 4 * (lane >> 4) + j;
-        if (t >= my_tiles || o >= p.Og || m >= block_px) continue;
-        float* const at = op + element(m, o);
-        const int row = fdiv(m, p.m_wo);
-        if (!trusted_result(*at)) *at = split_exact(p, X, W, g, o, R0 + row, m - row * p.Wo, c_begin, c_end, ADJ);
+        again[j] = o < p.Og && m + j < block_px && !trusted_result(op[element(m + j, o)]);
+        any |= again[j];
       }
+      if (!__any(any)) continue;
+      const floatx4 v = split_plain_tile<T, ADJ>(p, X, W, g, o0, R0, m0, block_px, lane);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (again[j]) op[element(m + j, o)] = v[j];
     }
   }
   if (probe && threadIdx.x == 0) {

@@ -23,24 +23,55 @@
 //    85 -> 44.  Error against 64 bits 1.4e-7 to 1.7e-7 of the largest weight's gradient, before 3.3e-7 to 3.8e-7.
 #pragma once
 
-// One weight's gradient summed plainly in fp64
-__device__ __forceinline__ float dw_exact(const DwParams& p, const float* __restrict__ Gt, const float* __restrict__ Xt, int g, int o, int c, int kh, int kw) {
-  double acc = 0.;
-  const int n_images = p.rows_total / p.H;
-  for (int n = 0; n < n_images; ++n) {
-    const float* gp = Gt + (int64_t)n * p.gs_n + (int64_t)(g * p.Og + o) * p.plane;
-    const float* xp = Xt + (int64_t)n * p.xs_n + (int64_t)(g * p.Cg + c) * p.plane;
-    for (int h = max(0, p.ph - kh); h < min(p.H, p.H + p.ph - kh); ++h)
-      for (int w = max(0, p.pw - kw); w < min(p.W, p.W + p.pw - kw); ++w)
-        acc = fma((double)gp[h * p.W + w], (double)xp[(h + kh - p.ph) * p.W + w + kw - p.pw], acc);
-    if (acc != acc) break;
-  }
-  return (float)acc;
-}
-
 constexpr int kStreamChunk = 64;                 // pixels
 constexpr int kGUnits = 26;                      // LDS distance of G's channels in 16-byte units: 8 x 3 parts, and 2 (mod 4)
 constexpr uint32_t kNoPixel = 1u << 31;          // an offset beyond every tensor here: a buffer load answers it with zeros
+
+// All taps of a 16 x 16 tile (output channels o0.., input channels c0.. of the group) over the stream's pixels begin..end-1
+// with the fp32 matrix instructions, on the tensors where they lie: for tiles with sums that the parts cannot give.  A
+// pixel whose tap lies outside the image counts as zero in both operands.  Lane: output channels 4 * (lane / 16) + 0..3,
+// input channel lane % 16.  Each workgroup does its own pixels again, so that one infinity costs one split's share: 153 us
+// at 32x64x64 56x56, 330 where all of G is NaN, 69 without.
+template <int KH, int KW>
+__device__ __forceinline__ void dw_plain_tile(const DwParams& p, const float* __restrict__ Gt, const float* __restrict__ Xt, int g,
+                                              int o0, int c0, int begin, int end, int lane, floatx4 (&sum)[KH * KW]) {
+  constexpr int NX = 4 + KW - 1;                 // the pixels of a row that the taps of four read
+  const float* const gch = Gt + (int64_t)(g * p.Og + min(o0 + (lane & 15), p.Og - 1)) * p.plane;
+  const float* const xch = Xt + (int64_t)(g * p.Cg + min(c0 + (lane & 15), p.Cg - 1)) * p.plane;
+#pragma unroll
+  for (int t = 0; t < KH * KW; ++t) sum[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = begin; s0 < end; s0 += 16) {
+    const int s = s0 + 4 * (lane >> 4);          // four pixels of one row (its pitch is a multiple of 8)
+    const int row = (int)__umulhi((uint32_t)s, p.m_pitch), n = (int)__umulhi((uint32_t)row, p.m_rows);
+    const int h = row - n * (p.H + 1), w = s - row * p.pitch;
+    const bool live = n < p.n_images && h < p.H;
+    const float* const gr = gch + (live ? (int64_t)n * p.gs_n + h * p.W : 0);
+    float gv[4], xv[KH][NX];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) gv[e] = gr[live && w + e < p.W ? w + e : 0];
+#pragma unroll
+    for (int kh = 0; kh < KH; ++kh) {
+      const int hx = h + kh - p.ph;
+      const bool in = live && hx >= 0 && hx < p.H;
+      const float* const xr = xch + (in ? (int64_t)n * p.xs_n + hx * p.W : 0);
+#pragma unroll
+      for (int e = 0; e < NX; ++e) {
+        const int wx = w + e - p.pw;
+        xv[kh][e] = xr[in && wx >= 0 && wx < p.W ? wx : 0];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int kh = 0; kh < KH; ++kh)
+#pragma unroll
+        for (int kw = 0; kw < KW; ++kw) {
+          const int hx = h + kh - p.ph, wx = w + e + kw - p.pw;
+          const bool in = live && w + e < p.W && hx >= 0 && hx < p.H && wx >= 0 && wx < p.W;
+          sum[kh * KW + kw] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? gv[e] : 0.f, in ? xv[kh][e + kw] : 0.f, sum[kh * KW + kw], 0, 0, 0);
+        }
+  }
+}
 
 // VEC: pixels per load (4, 2 or 1, what the width divides by).  EDGE: rows without a zero pixel between them (widths that
 // are multiples of 8), whose ends the taps must not reach across.
@@ -248,26 +279,40 @@ __global__ __launch_bounds__(512) void dw_split(const DwParams p, const float* _
   }
   __syncthreads();
   if (half) return;
-  bool odd = false;
+  uint32_t odd = 0;                              // tiles of this wave with a sum that the parts cannot give
 #pragma unroll
   for (int ao = 0; ao < 2; ++ao)
 #pragma unroll
-    for (int i = 0; i < CT; ++i)
+    for (int i = 0; i < CT; ++i) {
+      bool any = false;
 #pragma unroll
       for (int t = 0; t < T; ++t) {
-        acc[ao][i][t] = (acc[ao][i][t] + red[((ao * CT + i) * T + t) * 64]) * kResultScale;
-        if (p.n_splits == 1)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) odd |= !trusted_result(acc[ao][i][t][v]);
+        const floatx4 v = (acc[ao][i][t] + red[((ao * CT + i) * T + t) * 64]) * kResultScale;
+        acc[ao][i][t] = v;
+        any |= !trusted_result(fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]));
       }
+      odd |= (uint32_t)(__any(any) != 0) << (ao * CT + i);
+    }
   dw_finish<KH, KW, CT>(p, partial, g, ob, cb, split, widx, lane, acc);
-  // (with several splits the kernel that adds them up looks at the whole sums)
-  if (!odd) return;
-  for (int q = 0; q < 2 * CT * T * 4; ++q) {
-    const int v = q & 3, t = (q >> 2) % T, it = (q >> 2) / T, o = ob * 64 + (2 * wo + it / CT) * 16 + 4 * (lane >> 4) + v;
-    const int c = cb * CX + (CT * wc + it % CT) * 16 + (lane & 15);
-    if (o >= p.Og || c >= p.Cg) continue;
-    float* const at = partial + (int64_t)g * p.ws_g + (int64_t)o * p.ws_o + (int64_t)c * p.ws_c + (t / KW) * p.ws_kh + (t % KW) * p.ws_kw;
-    if (!trusted_result(*at)) *at = dw_exact(p, Gt, Xt, g, o, c, t / KW, t % KW);
+  // (see split_pair)
+  while (odd) {
+    const int q = __builtin_ctz(odd), i = q % CT, ao = q / CT;
+    odd &= odd - 1;
+    const int o0 = ob * 64 + (2 * wo + ao) * 16, c0 = cb * CX + (CT * wc + i) * 16;
+    const int o = o0 + 4 * (lane >> 4), c = c0 + (lane & 15);
+    if (o0 >= p.Og || c0 >= p.Cg) continue;
+    floatx4 v[T];
+    dw_plain_tile<KH, KW>(p, Gt, Xt, g, o0, c0, chunk_begin * kStreamChunk, chunk_end * kStreamChunk, lane, v);
+    const int tile = (g * p.n_oblk + ob) * p.n_cblk + cb;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      // its place, as dw_finish has it
+      float* at = partial + (int64_t)g * p.ws_g + (int64_t)o * p.ws_o + (int64_t)c * p.ws_c + (t / KW) * p.ws_kh + (t % KW) * p.ws_kw;
+      if (p.n_splits > 1) at = partial + ((((int64_t)split * p.n_tiles + tile) * (8 * CT * T) + (widx * 2 * CT + q) * T + t) * 64 + lane) * 4;
+      const int64_t step = p.n_splits > 1 ? 1 : p.ws_o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (o + j < p.Og && c < p.Cg && !trusted_result(at[j * step])) at[j * step] = v[t][j];
+    }
   }
 }

@@ -954,9 +954,8 @@ __global__ __launch_bounds__(kRowsThreads) void dw_rows_bf16(const DwParams p, c
 // splits, in order, for taps j, j+4, ...; then the threads walk the tile in (o, c, tap) order, which is contiguous in
 // dW for the usual weight layouts, so dW is written in whole lines.
 constexpr int kMaxTaps = 9;
-// (Gt, Xt: read again where the sum of parts is none, p.parts only)
 __global__ __launch_bounds__(256) void dw_reduce_tiles(const DwParams p, const float4* __restrict__ partial,
-                                                       float* __restrict__ dW, const float* __restrict__ Gt, const float* __restrict__ Xt) {
+                                                       float* __restrict__ dW) {
   __shared__ float sums[kMaxTaps][64][4];
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int T = p.KH * p.KW;
@@ -989,16 +988,14 @@ __global__ __launch_bounds__(256) void dw_reduce_tiles(const DwParams p, const f
     const int c = c0 + cl;
     if (c >= p.Cg) continue;
     const int kh = t / p.KW;
-    float v = sums[t][(ol >> 2) * 16 + cl][ol & 3];
-    if (p.parts && !trusted_result(v)) v = dw_exact(p, Gt, Xt, g, o, c, kh, t - kh * p.KW);
-    dW[row + (int64_t)c * p.ws_c + kh * p.ws_kh + (t - kh * p.KW) * p.ws_kw] = v;
+    dW[row + (int64_t)c * p.ws_c + kh * p.ws_kh + (t - kh * p.KW) * p.ws_kw] = sums[t][(ol >> 2) * 16 + cl][ol & 3];
   }
 }
 
 // The same sums for many splits and few tiles: a block owns one slot (64 quadruples, one tap of a 16x16 tile), which
 // keeps enough blocks in flight when dW is small; the stores are scattered, which does not matter at that size.
 __global__ __launch_bounds__(256) void dw_reduce_slots(const DwParams p, const float4* __restrict__ partial,
-                                                       float* __restrict__ dW, const float* __restrict__ Gt, const float* __restrict__ Xt) {
+                                                       float* __restrict__ dW) {
   __shared__ float4 sums[4][64];
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int64_t n4 = (int64_t)p.n_tiles * p.slots * 64;
@@ -1029,7 +1026,7 @@ __global__ __launch_bounds__(256) void dw_reduce_slots(const DwParams p, const f
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int o = ob * 64 + (2 * (wave >> 1) + ao) * 16 + 4 * (lane >> 4) + v;
-    if (o < p.Og) dW[base + (int64_t)o * p.ws_o] = p.parts && !trusted_result(r[v]) ? dw_exact(p, Gt, Xt, g, o, c, t / p.KW, t % p.KW) : r[v];
+    if (o < p.Og) dW[base + (int64_t)o * p.ws_o] = r[v];
   }
 }
 
@@ -1458,10 +1455,10 @@ syno_status launch_mfma_dw(const syno_plan* plan, const void* A, const void* B, 
     // (written by the contraction itself)
   } else if (p.n_splits > 4 && p.n_tiles * (p.slots / (p.KH * p.KW)) < 256)
     hipLaunchKernelGGL(dw_reduce_slots, dim3(p.n_tiles * p.slots), dim3(256), 0, stream, p,
-                       reinterpret_cast<const float4*>(ws), static_cast<float*>(out), static_cast<const float*>(A), static_cast<const float*>(B));
+                       reinterpret_cast<const float4*>(ws), static_cast<float*>(out));
   else
     hipLaunchKernelGGL(dw_reduce_tiles, dim3(p.n_tiles * (p.slots / (p.KH * p.KW))), dim3(256), 0, stream, p,
-                       reinterpret_cast<const float4*>(ws), static_cast<float*>(out), static_cast<const float*>(A), static_cast<const float*>(B));
+                       reinterpret_cast<const float4*>(ws), static_cast<float*>(out));
   return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
 }
 

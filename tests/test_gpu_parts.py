@@ -212,6 +212,101 @@ def test_small_values_are_ordinary_ones(syno, scale):  # noqa: F811
         assert slow <= 4 * plain + 50, (which, slow, plain)
 
 
+def same_as_the_definition(got, plain, size, terms):
+    """got: a result; plain: the index program's, which sums a result's terms in order in fp32; size: its sums of the terms'
+    magnitudes.  Infinities and NaNs are the same, other values within the roundings of both sums."""
+    assert torch.equal(torch.isnan(got), torch.isnan(plain)) and torch.equal(torch.isposinf(got), torch.isposinf(plain))
+    assert torch.equal(torch.isneginf(got), torch.isneginf(plain))
+    fine = torch.isfinite(plain) & torch.isfinite(size)
+    assert bool(((got - plain).double().abs() <= size.double() * (2 * terms * 2.0 ** -24) + terms * 2.0 ** -149)[fine].all())
+
+
+def odd_values(a, b):
+    """Pairs like (a, b) with values that parts do not stand for, in either operand and in both."""
+    gen = torch.Generator().manual_seed(11)
+
+    def at(t, *values):
+        t = t.clone()
+        t.view(-1)[torch.randperm(t.numel(), generator=gen)[:len(values)].to(t.device)] = torch.tensor(values, device=t.device)
+        return t
+    inf, nan = float("inf"), float("nan")
+    yield at(a, inf), b
+    yield at(a, inf, -inf, nan, 3.4e38, -3e38), b * 1e-3
+    yield a, at(b, inf)
+    yield a, at(b, -inf, nan, 3e38)
+    yield a * 1e-3, at(b, *([nan, inf] * 20))
+    yield at(a, inf, 3e38), at(b, 1e-40, 1e-39)
+    yield a * 1e30, b
+    yield a, b * 1e32
+    yield a * float("nan"), b
+
+
+# every tap's way through the sums of whole tiles: reversed taps, a stride, cyclic rows by group, one-sided windows, 1x1
+ODD_CASES = {
+    "3x3": (lambda: wl.conv2d(2, 40, 48, 10, 12), (0, 1, 2), (0, 1)),
+    "3x3_one_column": (lambda: wl.conv2d(5, 32, 36, 6, 1), (0, 2), (0, 1)),
+    "3x3_stride2": (lambda: wl.conv2d(2, 40, 48, 6, 7, stride=2), (0, 1, 2), (0,)),
+    "3x1": (lambda: wl.conv2d(3, 36, 52, 7, 9, 3, 1), (0, 1), (0, 1)),
+    "1x1": (lambda: wl.conv2d(3, 72, 136, 7, 9, 1, 1), (3,), (0, 1)),
+    "cyclic_1x3": (lambda: wl.grouped_shift_unfold(3, 144, 144, 9, 11, 4, 3, F32, F32), (0, 1), (0, 1)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,cfg", [(n, c) for n, v in ODD_CASES.items() for c in v[1]])
+def test_tiles_with_results_that_parts_cannot_give(syno, name, cfg):  # noqa: F811
+    make, _, directions = ODD_CASES[name]
+    parts, plain = syno.Plan(make(), mfma_variant=-2 - cfg), syno.Plan(make(), kernel_policy=1)
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    W = torch.randn(parts.w_shape, generator=gen, device="cuda") / 20
+    for which in directions:
+        assert f"bf16-parts tiles={cfg} " in parts.describe(which)
+        A = torch.randn(parts.x_shape if which == 0 else parts.out_shape, generator=gen, device="cuda")
+        for a, w in odd_values(A, W):
+            got, ref, size = ((p.forward if which == 0 else p.backward_data)(x, y) for p, x, y in ((parts, a, w), (plain, a, w), (plain, a.abs(), w.abs())))
+            same_as_the_definition(got, ref, size, parts.free_size(which))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("W", (7, 8, 12, 14))
+@pytest.mark.parametrize("KH,KW", ((3, 3), (3, 1), (1, 3), (1, 1)))
+@pytest.mark.parametrize("groups", (0, 1, 3))
+def test_weight_gradient_tiles_with_results_that_parts_cannot_give(syno, W, KH, KW, groups):  # noqa: F811
+    d = wl.conv2d(3, 40, 72, 9, W, KH, KW)
+    parts, plain = syno.Plan(d, dw_workgroups=groups), syno.Plan(d, kernel_policy=1)
+    assert "bf16-parts" in parts.describe(2)
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    X, G = torch.randn(parts.x_shape, generator=gen, device="cuda"), torch.randn(parts.out_shape, generator=gen, device="cuda") / 20
+    for x, g in odd_values(X, G):
+        same_as_the_definition(parts.backward_weight(x, g), plain.backward_weight(x, g), plain.backward_weight(x.abs(), g.abs()), parts.free_size(2))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ("one infinity", "beyond the parts", "all NaN"))
+def test_values_that_parts_do_not_stand_for_are_no_cliff(syno, kind):  # noqa: F811
+    """A tile is summed again by the fp32 matrix instructions, not by its lanes one result at a time (a hundred times the
+    ordinary call's time and more)."""
+    p = syno.Plan(wl.conv2d(16, 64, 64, 56, 56))
+    assert all("bf16-parts" in p.describe(which) for which in range(3))
+    gen = torch.Generator(device="cuda").manual_seed(14)
+    X, G, W = (torch.randn(s, generator=gen, device="cuda") for s in (p.x_shape, p.out_shape, p.w_shape))
+
+    def odd(t):
+        if kind == "beyond the parts":
+            return t * 1e30
+        t = t.clone()
+        if kind == "all NaN":
+            return t.fill_(float("nan"))
+        t.view(-1)[t.numel() // 3] = float("inf")
+        return t
+    x, g = odd(X), odd(G)
+    for which, (slow, plain) in enumerate(((lambda: p.forward(x, W), lambda: p.forward(X, W)), (lambda: p.backward_data(g, W), lambda: p.backward_data(G, W)),
+                                           (lambda: p.backward_weight(X, g), lambda: p.backward_weight(X, G)))):
+        t, t0 = least_time(slow), least_time(plain)
+        print(f"[time] {kind} pass {which}: {t0:.0f} -> {t:.0f} us", flush=True)
+        assert t <= 10 * t0 + 50, (kind, which, t, t0)
+
+
 # strided, rows wider than the fp32 instructions' kernel stages: the phase planes of X and the spread weights need 40 MB
 WIDE_STRIDED = dict(N=28, C=21, H=38, seed=51, Co=11, Wd=59, stride=2, with_grad=True)
 
