@@ -84,8 +84,10 @@ typedef struct {
  *   mfma_variant    1 + index of the contraction kernel's tile variant (forward and backward-data), or -1 for the
  *                   row-streaming member of the family (bf16, at most 64 channels per group), or -2 - index of a tile
  *                   configuration of the fp32 contraction on the bf16 matrix cores;
- *                   mfma_rows = output rows per workgroup tile.  Ignored unless the pair fits the operator.
- *   mfma_taps       1: one window tap per inner step even where three would be taken
+ *                   mfma_rows = output rows per workgroup tile.  Ignored unless the pair fits the operator.  A tile
+ *                   variant (> 0) of an fp32 operator also keeps its weight gradient on the fp32 instructions
+ *   mfma_taps       1: one window tap per inner step even where three would be taken (fp32 operators then stay on the
+ *                   fp32 instructions, unless a tile configuration of the other kernel is named)
  *   mfma_splits     number of workgroups that share one output tile of the contraction kernel, each summing a
  *                   range of the reduced channels; their partial results go to the workspace and a second kernel
  *                   adds them in a fixed order (fp32 results only; by itself the planner splits only reductions

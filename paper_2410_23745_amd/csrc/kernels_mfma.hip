@@ -623,7 +623,8 @@ void mfma_configure(syno_plan* plan, int which) {
   if (!bf && plan->opt.mfma_variant <= 0 && !forced && plan->opt.mfma_rows >= 0) {
     const int named = plan->opt.mfma_variant <= -2 ? -2 - plan->opt.mfma_variant : -1;
     int best_cfg = -1, cfg_tr = 0;
-    double cfg_cost = named >= 0 ? 1e300 : best;
+    // (taps one by one are a choice within the other kernel)
+    double cfg_cost = named >= 0 ? 1e300 : plan->opt.mfma_taps == 1 && best_v >= 0 ? 0. : best;
     SplitParams sp;
     for (int cfg = 0; cfg < kNumSplitConfigs; ++cfg)
       for (int TR = 1; TR <= c.N * c.Ho && TR * c.Wo <= 16 * 28; ++TR) {

@@ -1321,6 +1321,8 @@ bool fill_dw_split(const syno_plan* plan, DwParams& p) {
 
 bool fill_any(const syno_plan* plan, DwParams& p) {
   if (plan->in_dtype == SYNO_BF16) return fill_dw(plan, p);
+  // (a named variant of the fp32 contraction kernel asks for the fp32 instructions)
+  if (plan->opt.mfma_variant > 0 && fill_dw_f32(plan, p)) return true;
   return fill_dw_split(plan, p) || fill_dw_f32(plan, p);
 }
 

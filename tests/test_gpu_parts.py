@@ -93,6 +93,14 @@ def test_weight_gradient_parity_at_the_edges(syno, oracle, name, groups):  # noq
     run_all(syno, oracle, w, 0, directions=(2,), dw_workgroups=groups)
 
 
+def weight_sums(x, g, KH, KW):
+    """The weight gradient of a convolution with zero padding, tap by tap."""
+    (C, H, W), O = x.shape[1:], g.shape[1]
+    x = torch.nn.functional.pad(x, (KW // 2, KW // 2, KH // 2, KH // 2))
+    return torch.stack([torch.stack([g.transpose(0, 1).reshape(O, -1) @ x[:, :, a:a + H, b:b + W].transpose(0, 1).reshape(C, -1).t().contiguous()
+                                     for b in range(KW)], -1) for a in range(KH)], -2)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("KH,KW", ((3, 1), (1, 3)))
 @pytest.mark.parametrize("N,C,O,H,W", ((2, 64, 64, 9, 30), (3, 72, 80, 12, 21), (4, 65, 63, 1, 24), (5, 100, 40, 5, 6)))
@@ -105,11 +113,7 @@ def test_weight_gradient_of_one_sided_windows(syno, N, C, O, H, W, KH, KW):  # n
     X, G = torch.randn(p.x_shape, generator=gen, device="cuda"), torch.randn(p.out_shape, generator=gen, device="cuda")
     got = p.backward_weight(X, G).double()
 
-    def sums(x, g):
-        x = torch.nn.functional.pad(x, (KW // 2, KW // 2, KH // 2, KH // 2))
-        return torch.stack([torch.stack([g.transpose(0, 1).reshape(O, -1) @ x[:, :, a:a + H, b:b + W].transpose(0, 1).reshape(C, -1).t().contiguous()
-                                         for b in range(KW)], -1) for a in range(KH)], -2)
-    whole, size = sums(X.double(), G.double()), sums(X.double().abs(), G.double().abs())
+    whole, size = weight_sums(X.double(), G.double(), KH, KW), weight_sums(X.double().abs(), G.double().abs(), KH, KW)
     assert bool(((got - whole).abs() <= size * (2.0 ** -22 + 64 * 2.0 ** -24)).all())
 
 
@@ -334,3 +338,38 @@ def test_weight_gradient_without_a_workspace_beyond_the_scratch(syno, oracle):  
     _, mdw = oracle.backward(w.desc, np.abs(w.X), np.abs(w.W), np.abs(w.G), False, True)
     for name, v in got.items():
         assert_close(to_host(v), dw, mdw, p.free_size(2), False, "backward-weight " + name, tol_for(w.desc))
+
+
+# (N, C, O, H, W): whole rows of 7 and of 14 pixels, pixels by four, by two and single; several chunks per workgroup
+FP32_DW_CASES = ((33, 40, 72, 7, 7), (9, 64, 65, 14, 14), (2, 32, 70, 30, 28), (4, 24, 40, 21, 10), (3, 33, 64, 23, 13))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("KH,KW", ((3, 3), (3, 1), (1, 3), (1, 1)))
+@pytest.mark.parametrize("groups", (1, 3))
+@pytest.mark.parametrize("N,C,O,H,W", FP32_DW_CASES)
+def test_weight_gradient_on_the_fp32_instructions(syno, N, C, O, H, W, KH, KW, groups):  # noqa: F811
+    """A named variant of the fp32 contraction kernel keeps the weight gradient on the fp32 instructions, which tensors of 2 GiB
+    and more have it on.  A sum rounds once per term and workgroup."""
+    p = syno.Plan(wl.conv2d(N, C, O, H, W, KH, KW), mfma_variant=1, mfma_rows=1, dw_workgroups=groups)
+    chunks, splits = (int(p.describe(2).split(k + "=")[1].split()[0]) for k in ("chunks", "splits"))
+    assert "bf16-parts" not in p.describe(2) and chunks > splits, p.describe(2)
+    gen = torch.Generator(device="cuda").manual_seed(16)
+    X, G = torch.randn(p.x_shape, generator=gen, device="cuda"), torch.randn(p.out_shape, generator=gen, device="cuda")
+    got = p.backward_weight(X, G).double()
+    whole, size = weight_sums(X.double(), G.double(), KH, KW), weight_sums(X.double().abs(), G.double().abs(), KH, KW)
+    assert bool(((got - whole).abs() <= size * ((N * H * W + 3) * 2.0 ** -24)).all())
+
+
+def test_named_choices_of_the_fp32_kernels():
+    import paper_2410_23745_amd as s
+    d = wl.conv2d(32, 64, 64, 28, 28)
+    assert all("bf16-parts" in s.Plan(d).describe(which) for which in range(3))
+    taps = s.Plan(d, mfma_taps=1)
+    assert all("taps/row-step=1 " in taps.describe(which) for which in (0, 1)), (taps.describe(0), taps.describe(1))
+    named = s.Plan(d, mfma_variant=4, mfma_rows=7)
+    assert "variant=3 " in named.describe(0) and "bf16-parts" not in named.describe(2)
+    assert "bf16-parts tiles=1 " in s.Plan(d, mfma_variant=-3, mfma_taps=1).describe(0)
+    # rows that the fp32 instructions' kernel does not stage
+    wide = wl.conv2d(1, 24, 40, 3, 199)
+    assert "bf16-parts" in s.Plan(wide, mfma_variant=1, mfma_rows=1).describe(2)
