@@ -50,10 +50,14 @@ typedef int intx4 __attribute__((ext_vector_type(4)));
 
 // 16 bytes per lane from `src` + offset + step to LDS address `lds` + 16 * lane.  Written out because the compiler waits for
 // its own direct loads before the next read of LDS, whichever buffer that reads; nothing but LDS is written, and the
-// caller waits (vmcnt) and meets the other waves before that buffer is read.
+// caller waits (vmcnt) and meets the other waves before that buffer is read.  m0, the address's register, is the compiler's
+// own and is said to be overwritten (it warns that it will not keep the value across, which is what is meant).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(intx4 src, uint32_t lds, uint32_t offset, uint32_t step) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(offset), "s"(src), "s"(step) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(offset), "s"(src), "s"(step) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // a raw buffer over everything below kOutside bytes from `base` on
 __device__ __forceinline__ intx4 buffer_at(const void* base) {
   const uint64_t a = reinterpret_cast<uint64_t>(base);
