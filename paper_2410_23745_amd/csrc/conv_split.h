@@ -141,8 +141,7 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     nb = bid % p.n_nblocks; bid /= p.n_nblocks;
     mb = bid % p.n_mblocks;
   }
-  int g = bid / p.n_mblocks, ksp = 0;
-  if (p.ksplit > 1) { ksp = g / p.G; g -= ksp * p.G; }
+  const int g = bid / p.n_mblocks;
   const int R0 = mb * p.TR;
   const int rows = min(p.TR, p.rows_total - R0);
 
@@ -171,9 +170,7 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   // memory round trip
   constexpr bool XN = MODE == 2 && NSUB == 1, WN2 = MODE == 2;
   float xr[XI][8], xn[XN ? XI : 1][8], wr[CW * T], wn2[WN2 ? CW * T : 1];
-  const int ch_begin = ksp * p.chunks_per_split;
-  const int ch_end = min(p.n_chunks, ch_begin + p.chunks_per_split);
-  const int last = ch_end - 1;
+  const int last = p.n_chunks - 1;
 
   // Loads are a wave-uniform base plus a 32-bit lane offset and stand in straight-line code (a load whose registers meet
   // other values at a branch's end is waited for right there): what has no source reads some valid element, and chunks past
@@ -201,7 +198,7 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
 #pragma unroll
     for (int j = 0; j < 4; ++j) split_pair(xr[k][2 * j], xr[k][2 * j + 1], h[j], m[j], l[j]);
     if (x_loff[k] >= 0) {
-      uint4* d = reinterpret_cast<uint4*>(smem + x_loff[k] + (MODE == 2 && ((ch - ch_begin) & 1) ? p.x_bytes : 0));
+      uint4* d = reinterpret_cast<uint4*>(smem + x_loff[k] + (MODE == 2 && (ch & 1) ? p.x_bytes : 0));
       d[0] = make_uint4(h[0], h[1], h[2], h[3]);
       d[1] = make_uint4(m[0], m[1], m[2], m[3]);
       d[2] = make_uint4(l[0], l[1], l[2], l[3]);
@@ -271,9 +268,9 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   auto first_w = [&](int ch, int buf) { static_for<0, TS>([&](auto i) { stage_w(ch, i, buf); }); };     // first group of taps
   auto rest_w = [&](int ch, int buf) { static_for<TS, T>([&](auto i) { stage_w(ch, i, buf); }); };
 
-  fetch_w(ch_begin, all, wr);
-  load_x(ch_begin, xr);
-  if constexpr (WN2 && NSUB == 2) fetch_w(ch_begin + 1, all, wn2);
+  fetch_w(0, all, wr);
+  load_x(0, xr);
+  if constexpr (WN2 && NSUB == 2) fetch_w(1, all, wn2);
   // while the first loads travel: what the window's padding reads is zeroed once and never written (slot edges, rows outside
   // the image)
   for (int s = tid; s < p.n_slots; s += NT) slot_src[s] = split_slot(p, R0, rows, n0, h0, g, s);
@@ -315,7 +312,7 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     constexpr int sub = decltype(sub_c)::value, n = sub ? T - TS : TS, P = decltype(pieces_c)::value;
     static_assert(n >= WK, "every wave has a k-step in every stage");
     const int q0 = wk * n / WK, q1 = (wk + 1) * n / WK;
-    const int xoff = MODE == 2 && ((ch - ch_begin) & 1) ? p.x_bytes : 0;
+    const int xoff = MODE == 2 && (ch & 1) ? p.x_bytes : 0;
     const int woff = b_base + (wbuf ? p.w_bytes : 0);
     auto a_off = [&](int q) {
       const int tap = sub * TS + q, kh = p.KW == 3 ? tap / 3 : tap, kw = p.KW == 3 ? tap - 3 * kh : 0;
@@ -395,22 +392,22 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   // ---- the stages
   constexpr std::integral_constant<int, 0> s0{};
   constexpr std::integral_constant<int, 1> s1{};
-  if constexpr (XN) load_x(ch_begin + 1, xn);
-  if constexpr (MODE == 2) whole_x(ch_begin);
-  if constexpr (MODE >= 1) first_w(ch_begin, 0);
-  if constexpr (MODE == 2) { if constexpr (XN) load_x(ch_begin + 2, xn); else load_x(ch_begin + 1, xr); }
+  if constexpr (XN) load_x(1, xn);
+  if constexpr (MODE == 2) whole_x(0);
+  if constexpr (MODE >= 1) first_w(0, 0);
+  if constexpr (MODE == 2) { if constexpr (XN) load_x(2, xn); else load_x(1, xr); }
   if constexpr (MODE >= 1 && NSUB == 1) {
-    fetch_w(ch_begin + 1, all, wr);
-    if constexpr (WN2) fetch_w(ch_begin + 2, all, wn2);
+    fetch_w(1, all, wr);
+    if constexpr (WN2) fetch_w(2, all, wn2);
   }
-  for (int ch = ch_begin; ch < ch_end; ++ch) {
+  for (int ch = 0; ch < p.n_chunks; ++ch) {
     __syncthreads();
     if constexpr (MODE < 2) {                   // what has one buffer is written between two barriers
       whole_x(ch);
       if constexpr (MODE == 0) first_w(ch, 0);
       __syncthreads();
     }
-    const int buf = MODE >= 1 && NSUB == 1 ? (ch - ch_begin) & 1 : 0;
+    const int buf = MODE >= 1 && NSUB == 1 ? ch & 1 : 0;
     constexpr int FXP = MODE < 2 ? XI : 0;      // X of the next chunk is requested in the first stage, or staged in the last
     if constexpr (NSUB == 2 && MODE >= 1) {
       constexpr int P = FXP + (T - TS) + FW;
@@ -464,7 +461,6 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
 
   // ---- store: lane holds 4 consecutive pixels (rows of D) of one channel (column of D)
   const int img_px = p.Ho * p.Wo;
-  float* const op = out + (int64_t)ksp * p.split_stride;
   bool odd = false;                // some result of this lane is none that the parts can give
   auto element = [&](int m, int o) -> int64_t {       // pixel m of the block, output channel o -> element of the result
     const int i = fdiv(m, p.m_wo), r = R0 + i, n = fdiv(r, p.m_ho);
@@ -481,11 +477,11 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     // (one test for the four values; each is looked at again below)
     odd |= !trusted_result(fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]));
     if (m0 + 3 < block_px && px + 3 < img_px && (off & 3) == 0) {
-      *reinterpret_cast<float4*>(op + off) = make_float4(v[0], v[1], v[2], v[3]);
+      *reinterpret_cast<float4*>(out + off) = make_float4(v[0], v[1], v[2], v[3]);
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        if (m0 + j < block_px) op[element(m0 + j, o)] = v[j];
+        if (m0 + j < block_px) out[element(m0 + j, o)] = v[j];
     }
   };
   int first_tile = 0, tile_step = 1;        // the tiles of this wave's area that it stores
@@ -521,14 +517,14 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
       bool again[4], any = false;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        again[j] = o < p.Og && m + j < block_px && !trusted_result(op[element(m + j, o)]);
+        again[j] = o < p.Og && m + j < block_px && !trusted_result(out[element(m + j, o)]);
         any |= again[j];
       }
       if (!__any(any)) continue;
       const floatx4 v = split_plain_tile<T, ADJ>(p, X, W, g, o0, R0, m0, block_px, lane);
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        if (again[j]) op[element(m + j, o)] = v[j];
+        if (again[j]) out[element(m + j, o)] = v[j];
     }
   }
   if (probe && threadIdx.x == 0) {
@@ -543,7 +539,7 @@ void launch_split_one(const SplitParams& p, const float* X, const float* W, floa
   static const hipError_t lds_opt_in =
       hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
   (void)lds_opt_in;
-  hipLaunchKernelGGL(kernel, dim3(p.n_mblocks * p.n_nblocks * p.G * p.ksplit), dim3(512), p.lds_bytes, s, p, X, W, out);
+  hipLaunchKernelGGL(kernel, dim3(p.n_mblocks * p.n_nblocks * p.G), dim3(512), p.lds_bytes, s, p, X, W, out);
 }
 
 // The instantiation with `tiles` = N, N-1, .. 1 pixel tiles per wave

@@ -2,8 +2,11 @@
 //
 // An fp32 value is the exact sum of three bf16 values (8 significant bits each): x = h + m + l with h = bf16(x),
 // m = bf16(x - h), l = x - h - m.  A product of two fp32 values is then nine bf16 products, each exact in fp32, of which
-// the three smallest (m*l, l*m, l*l: below 2^-24 of the product) are left out; the six others are accumulated in fp32 by
+// the three smallest (m*l, l*m, l*l) are left out; the six others are accumulated in fp32 by
 // v_mfma_f32_16x16x32_bf16.  Six of them take 96 cycles for 32 terms where v_mfma_f32_16x16x4_f32 takes 256.
+// What is left out is together below 0.996 * 2^-24 of the product (every pair of mantissas' largest m and l; 0.09 * 2^-24
+// in the mean square), about one more rounding of it: a result with a single term that is not zero can be 2 * 2^-24 off where
+// the fp32 instructions give 2^-24, and sums are closer than theirs, because the large sum is rounded less often.
 #pragma once
 #include <hip/hip_runtime.h>
 

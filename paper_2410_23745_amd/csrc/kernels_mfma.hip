@@ -478,7 +478,7 @@ bool fill_split(const syno_plan* plan, int which, int cfg, int TR, SplitParams& 
   auto magic = [](int64_t d) { return (uint32_t)(((1ull << 32) + d - 1) / std::max<int64_t>(d, 1)); };
   if (2048 * per_cg >= (1ll << 32) || (int64_t)p.rows_total * c.Ho >= (1ll << 32)) return false;
   p.m_wo = magic(c.Wo); p.m_ho = magic(c.Ho); p.m_vpr = magic(c.Wi); p.m_pcg = magic(per_cg);
-  p.ksplit = 1; p.chunks_per_split = p.n_chunks; p.split_stride = 0;
+  p.ksplit = 1;
   deal_to_xcds(c, false, p);
   // (tiles that are all resident at once come back to neither operand: those that start together share the larger one)
   if (p.xcd_m > 0 && (p.n_mblocks / p.xcd_m) * (p.n_nblocks / p.xcd_n) <= 32)
@@ -542,8 +542,8 @@ double split_cost(const SplitParams& p, int cfg, const ConvLike& c) {
   }
   chunk += v.mode == 1 ? 1500.0 : 0.0;
   chunk = std::max(chunk, 3900.0);      // (a memory round trip over the two chunks that are on their way)
-  const double wgs = (double)p.n_mblocks * p.n_nblocks * c.G * p.ksplit;
-  return std::ceil(wgs / kNumCU) * (p.chunks_per_split * chunk + 22000.0);
+  const double wgs = (double)p.n_mblocks * p.n_nblocks * c.G;
+  return std::ceil(wgs / kNumCU) * (p.n_chunks * chunk + 22000.0);
 }
 
 size_t packed_weight_bytes(const MfmaParams& p) {
@@ -664,7 +664,7 @@ std::string mfma_describe(const syno_plan* plan, int which) {
     const SplitConfig& v = kSplitConfigs[-2 - plan->launch[which].variant];
     char b[256];
     snprintf(b, sizeof b, "bf16-parts tiles=%d rows/block=%d BN=%d KC=%d weights=%s waves=%dx%dx%d grid=%d lds=%dB slots=%d", -2 - plan->launch[which].variant, p.TR,
-             p.BN, p.KC, p.adjoint ? "turned-while-staged" : "direct", v.WM, v.WN, v.WK, p.n_mblocks * p.n_nblocks * p.G * p.ksplit, p.lds_bytes, p.n_slots);
+             p.BN, p.KC, p.adjoint ? "turned-while-staged" : "direct", v.WM, v.WN, v.WK, p.n_mblocks * p.n_nblocks * p.G, p.lds_bytes, p.n_slots);
     std::string d = b;
     if (p.xcd_m > 0)
       d += " tiles-per-xcd=" + std::to_string(p.n_mblocks / p.xcd_m) + "x" + std::to_string(p.n_nblocks / p.xcd_n) +
