@@ -268,27 +268,43 @@ bool gemm_configure(syno_plan* plan, int which, int64_t M, int64_t K, int64_t N)
   p.lda = (int)(which == SYNO_BWD_DATA ? N : K);
   p.ldb = (int)N;
   p.probe = static_cast<long long*>(o.clock_probe);
-  double best = 1e30;
   const int steps = (p.K + kStepK - 1) / kStepK;
-  // the splits' sums, written and read: those of the weight gradient fit the scratch of the entry point without a workspace
-  // (32 MiB), the others stay below 64 MiB
-  const int64_t limit = 2ll * (which == SYNO_BWD_WEIGHT ? SYNO_STATIC_SCRATCH_BYTES : 64ll << 20);
-  for (int c = 0; c < kConfigs; ++c) {
-    const int n_m = (p.M + kTiles[c][0] - 1) / kTiles[c][0], n_n = (p.N + kTiles[c][1] - 1) / kTiles[c][1];
-    for (int splits = 1; splits <= 16 && splits <= steps; ++splits) {      // (43 splits of 8192x128x128's dW: 19 us, 16: 14)
-      const int per = (steps + splits - 1) / splits;
-      if ((steps + per - 1) / per != splits) continue;
-      const int64_t blocks = (int64_t)n_m * n_n * splits, bytes = (int64_t)splits * p.M * p.N * 8;
-      if (blocks >= (1 << 30) || (splits > 1 && bytes > limit)) continue;
-      const double step = std::max(kTiles[c][0] * kTiles[c][1] / 32., (kTiles[c][0] + kTiles[c][1]) * 3.2);
-      const double cost = (double)((blocks + 255) / 256) * (per * step + 4000.) + (splits > 1 ? 6000. + bytes / 1800. : 0.);
-      if (cost < best) {
-        best = cost;
-        p.config = c; p.n_m = n_m; p.n_n = n_n; p.splits = splits; p.steps_per_split = per;
+  auto take = [&](int c, int splits) {
+    p.config = c;
+    p.n_m = (p.M + kTiles[c][0] - 1) / kTiles[c][0];
+    p.n_n = (p.N + kTiles[c][1] - 1) / kTiles[c][1];
+    p.steps_per_split = (steps + splits - 1) / splits;
+    p.splits = (steps + p.steps_per_split - 1) / p.steps_per_split;
+  };
+  const int64_t sums = (int64_t)p.M * p.N * 4;     // bytes of one split's
+  auto cheapest = [&](int64_t limit) {
+    double best = 1e30;
+    int best_c = -1, best_splits = 0;
+    for (int c = 0; c < kConfigs; ++c)
+      for (int splits = 1; splits <= 16 && splits <= steps; ++splits) {      // (43 splits of 8192x128x128's dW: 19 us, 16: 14)
+        take(c, splits);
+        if (p.splits != splits) continue;
+        const int64_t blocks = (int64_t)p.n_m * p.n_n * splits;
+        if (blocks >= (1 << 30) || (splits > 1 && splits * sums > limit)) continue;
+        const double step = std::max(kTiles[c][0] * kTiles[c][1] / 32., (kTiles[c][0] + kTiles[c][1]) * 3.2);
+        const double cost = (double)((blocks + 255) / 256) * (p.steps_per_split * step + 4000.) + (splits > 1 ? 6000. + splits * sums * 2 / 1800. : 0.);
+        if (cost < best) { best = cost; best_c = c; best_splits = splits; }
       }
-    }
+    if (best_c >= 0) take(best_c, best_splits);
+    return best_c >= 0;
+  };
+  if (!cheapest(64ll << 20)) return false;
+  // The weight gradient's sums have to fit the scratch of the entry point without a workspace.  Where that refuses the cheapest
+  // choice: the small tiles, two workgroups of which a compute unit holds, in as many splits as one such round and the scratch
+  // have room for (us, the refused choice -> this, and in brackets the cheapest one by the estimate that fits: 11136x8432x200
+  // 68 -> 73 (77), 23992x17816x96 217 -> 196 (234), 16384x2048x768 72 -> 70 (82), 16136x13584x216 146 -> 188 (240)).
+  constexpr int64_t scratch = SYNO_STATIC_SCRATCH_BYTES;
+  if (which == SYNO_BWD_WEIGHT && p.splits > 1 && p.splits * sums > scratch) {
+    take(2, 1);
+    const int64_t splits = std::min<int64_t>({2 * 256 / ((int64_t)p.n_m * p.n_n), scratch / sums, steps});
+    if (splits >= 2) take(2, (int)splits);
+    else if (!cheapest(scratch)) return false;
   }
-  if (best >= 1e30) return false;
   Launch& L = plan->launch[which];
   static_assert(sizeof(GemmParams) <= sizeof(L.params), "parameter record does not fit");
   memcpy(L.params, &p, sizeof p);
