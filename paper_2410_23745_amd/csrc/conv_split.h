@@ -88,8 +88,8 @@ __device__ __forceinline__ floatx4 split_plain_tile(const SplitParams& p, const 
 // A workgroup (8 waves, one per CU) owns TR whole result rows x BN output channels, like conv_mfma, and walks the reduction
 // in chunks of 32 channels, the weights of a 3x3 window in two groups of taps per chunk ("stages").
 //  - X lies in LDS as [channel octet][row slot][pixel][part] 16-byte pieces: with the 48-byte pixel pitch and octets a
-//    multiple of 256 bytes apart the 64 lanes of a fragment read meet no bank twice (measured: 4.4 cycles per read, 8.1 with
-//    any other distance), and taps and parts are constant offsets.
+//    multiple of 256 bytes apart the 64 lanes of a fragment read meet no bank twice (a kernel of such reads alone: 4.4 cycles
+//    each, 8.1 with any other distance; the writes of the staging do conflict), and taps and parts are constant offsets.
 //  - W lies as [tap][part][channel octet][output channel].
 //  - Staging is dealt evenly over the 512 threads, because a wave that stages more than its neighbours is waited for at the
 //    next barrier: X items are single pixels x 8 channels (adjacent lanes adjacent pixels, XI items per thread), W items

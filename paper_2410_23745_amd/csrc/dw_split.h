@@ -9,7 +9,7 @@
 //  - A workgroup (8 waves) owns 64 output x 32*CT input channels and a range of 64-pixel chunks.  G's chunks go through two
 //    LDS buffers, X's through a ring that holds the window's rows around the chunk and the chunk staged next:
 //    [channel][8 pixels][part] 16-byte units, channels 2 (mod 4) units apart, which keeps the fragment reads free of bank
-//    conflicts (measured: 4.4 cycles per 1 KB read, 8.1 otherwise), and the parts at constant offsets.
+//    conflicts (a kernel of such reads alone: 4.4 cycles per 1 KB, 8.1 otherwise), and the parts at constant offsets.
 //  - One barrier per chunk.  A chunk is two k-steps of 32 pixels, one per half of the waves; the next chunk is written, and
 //    the one after it requested, between the taps.  The halves' sums meet in LDS at the end.
 //  - Bound: 96 cycles of matrix work per 16x16 tile, tap and k-step, against some 200 vector instructions per wave and
@@ -17,7 +17,8 @@
 //    do not exist are buffer loads past the end, which give zeros.  Filling (a
 //    pitch above the width, the zero rows) costs 2 % at 56x56, 18 % at 28, 22 % at 14, 31 % at 7.  Issuing the requests
 //    earlier, a second set of registers for them, and interleaving the vector work with the matrix instructions by hand
-//    each left the times as they are: 850 TFLOP/s of bf16 products, filling included, where a large library product has 1190.
+//    each left the times as they are: 890 to 990 TFLOP/s of bf16 products in the kernel by itself, filling included, where a
+//    large library product has 1190 (matrix units occupied 0.36 to 0.40 of the time at the nominal clock, by the counters).
 //  - Measured, with the kernel that adds the splits up, against the fp32 instructions (batch 32): 64 channels at 56x56 86 ->
 //    59 us, 128 at 28 89 -> 64, 256 at 14 94 -> 69, 512 at 7 89 -> 71; 1x1 64 -> 256 at 56 93 -> 49; 3x1 96 -> 64 at 56
 //    85 -> 44.  Error against 64 bits 1.4e-7 to 1.7e-7 of the largest weight's gradient, before 3.3e-7 to 3.8e-7.
