@@ -307,9 +307,10 @@ __global__ __launch_bounds__(kThreads) void view_stream(const ViewParams p, cons
 // the target element; the host has checked, by enumerating the tables, that every combination of their indices picks
 // a different one (elements that none picks are zeroed first).  The remaining iterators are summed:
 //   - long sums: a workgroup takes one combination and one slice of the remaining iterators flattened row-major;
-//     threads keep private fp32 sums over runs along the innermost one, the workgroup adds them in a fixed tree, and
-//     a second kernel adds the slices in order;
-//   - short sums: a thread per combination walks the remaining iterators itself.
+//     threads keep private fp64 sums over runs along the innermost one, the workgroup adds them in a fixed tree, and
+//     a second kernel adds the slices in order (a single slice is stored at once);
+//   - short sums: a thread per combination walks the remaining iterators itself, or, where the combinations are too few
+//     to cover that walk's memory latency, the 64 lanes of a wave share it.
 // No atomics either way, so the result does not depend on scheduling.
 constexpr int kMaxIter = 2 * kMaxAxes;
 struct ViewGradParams {
@@ -354,10 +355,11 @@ __device__ __forceinline__ void store_target(void* base, int64_t off, float v) {
   else static_cast<float*>(base)[off] = v;
 }
 
-template <bool IBF, bool TO_X>
+// `target` is written where there is one slice, else `partial` and `t_index`.
+template <bool IBF, bool OBF, bool TO_X>
 __global__ __launch_bounds__(kThreads) void view_grad_long(const ViewGradParams p, const void* __restrict__ G,
                                                            const void* __restrict__ other, double* __restrict__ partial,
-                                                           int* __restrict__ t_index) {
+                                                           int* __restrict__ t_index, void* __restrict__ target) {
   extern __shared__ __align__(16) int tab[];
   __shared__ double wave_sum[kThreads / 64];
   const ViewStream& vs = p.vs;
@@ -409,8 +411,12 @@ __global__ __launch_bounds__(kThreads) void view_grad_long(const ViewGradParams 
   if (threadIdx.x == 0) {
     double t = wave_sum[0];
     for (int w = 1; w < kThreads / 64; ++w) t += wave_sum[w];
-    partial[blockIdx.x] = t;
-    if (slice == 0) t_index[combo] = b0.t;
+    if (p.n_splits == 1) {
+      store_target<OBF>(target, b0.t, (float)t);
+    } else {
+      partial[blockIdx.x] = t;
+      if (slice == 0) t_index[combo] = b0.t;
+    }
   }
 }
 
@@ -424,30 +430,49 @@ __global__ __launch_bounds__(kThreads) void view_grad_sum(const double* __restri
   store_target<OBF>(target, t_index[combo], (float)t);
 }
 
-template <bool IBF, bool OBF, bool TO_X>
+// LANES per combination: 1, or 64 where the combinations alone would leave the chip to wait for memory.  A lane's points
+// go four at a time, so that their loads are under way together: a chain of dependent offsets and loads per point is what
+// bounds the walk.  fp32, one lane -> 64 lanes (us): 57 combinations of 1014 points 527 -> 14, 120 of 684 385 -> 13, 29 of
+// 578 314 -> 13.
+template <bool IBF, bool OBF, bool TO_X, int LANES>
 __global__ __launch_bounds__(kThreads) void view_grad_short(const ViewGradParams p, const void* __restrict__ G,
                                                             const void* __restrict__ other, void* __restrict__ target) {
   extern __shared__ __align__(16) int tab[];
   const ViewStream& vs = p.vs;
   build_tables(vs, p.tab_off, p.free_off, p.n_free, p.tab_total, tab);
   const int* tabO = TO_X ? tab + p.tab_total : tab;
-  const int64_t combo = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t combo = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / LANES;
   if (combo >= p.n_combo) return;
   const GradBase b0 = grad_base<TO_X>(p, tab, (int)combo);
   double acc = 0.0;
-  for (uint32_t idx = 0; idx < (uint32_t)p.total_rest; ++idx) {
-    uint32_t rest = idx;
-    int go = b0.g, oo = b0.o;
-    for (int j = p.n_rest - 1; j >= 0; --j) {
-      const int axis = p.rest_axis[j];
-      const uint32_t sz = (uint32_t)vs.size[axis];
-      const uint32_t q = div_magic(rest, sz, p.rest_magic[j]);
-      const int d = (int)(rest - q * sz);
-      rest = q;
-      go += d * p.ostride[axis];
-      oo += tabO[p.tab_off[axis] + d];
+  const uint32_t n = (uint32_t)p.total_rest;
+  for (uint32_t first = threadIdx.x % LANES; first < n; first += 4 * LANES) {
+    float g[4], x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t idx = first + k * LANES;
+      uint32_t rest = min(idx, n - 1);
+      int go = b0.g, oo = b0.o;
+      for (int j = p.n_rest - 1; j >= 0; --j) {
+        const int axis = p.rest_axis[j];
+        const uint32_t sz = (uint32_t)vs.size[axis];
+        const uint32_t q = div_magic(rest, sz, p.rest_magic[j]);
+        const int d = (int)(rest - q * sz);
+        rest = q;
+        go += d * p.ostride[axis];
+        oo += tabO[p.tab_off[axis] + d];
+      }
+      g[k] = load_one<IBF>(G, go);
+      x[k] = load_one<IBF>(other, oo);
     }
-    acc = fma((double)load_one<IBF>(G, go), (double)load_one<IBF>(other, oo), acc);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (first + k * LANES < n) acc = fma((double)g[k], (double)x[k], acc);
+  }
+  if constexpr (LANES > 1) {
+#pragma unroll
+    for (int d = LANES / 2; d >= 1; d >>= 1) acc += __shfl_down(acc, d, LANES);
+    if (threadIdx.x % LANES != 0) return;
   }
   store_target<OBF>(target, b0.t, (float)acc);
 }
@@ -459,7 +484,12 @@ __global__ __launch_bounds__(kThreads) void view_grad_zero(uint32_t* __restrict_
   if ((bytes & 2) && blockIdx.x == 0 && threadIdx.x == 0) reinterpret_cast<uint16_t*>(dst)[bytes / 2 - 1] = 0;
 }
 
-constexpr int64_t kLongSum = 1024;       // remaining points from which a workgroup, not a thread, takes a combination
+constexpr int64_t kLongSum = 1024;       // remaining points from which a workgroup, not a thread or a wave, takes a combination
+// A wave, not a thread, takes a combination of at least a few points as long as there are fewer combinations than the chip
+// holds waves at a quarter of its occupancy (a thread's four points are one memory round trip; beyond that number of
+// combinations adjacent threads, which usually read adjacent elements, are the better use of it).
+constexpr int64_t kSharedPoints = 9, kSharedCombos = 65536;
+bool shared_walk(const ViewGradParams& p) { return p.total_rest >= kSharedPoints && p.n_combo <= kSharedCombos; }
 
 bool fill_grad(const syno_plan* plan, bool to_x, ViewGradParams& p) {
   p = ViewGradParams{};
@@ -606,8 +636,8 @@ void view_configure(syno_plan* plan, int which) {
     static_assert(sizeof(ViewGradParams) <= sizeof(L.params), "parameter record does not fit");
     L.params_ready = fill_grad(plan, which == SYNO_BWD_DATA, d);
     memcpy(L.params, &d, sizeof d);
-    // long sums: slice sums, then the target index of every combination
-    L.workspace = d.n_splits > 0 ? grad_partial_bytes(d) + (size_t)d.n_combo * 4 : 0;
+    // several slices: their sums, then the target index of every combination
+    L.workspace = d.n_splits > 1 ? grad_partial_bytes(d) + (size_t)d.n_combo * 4 : 0;
     return;
   }
   ViewParams p;
@@ -624,7 +654,7 @@ std::string view_describe(const syno_plan* plan, int which) {
   ViewGradParams d;
   memcpy(&d, plan->launch[which].params, sizeof d);
   std::string r = "gather targets=" + std::to_string(d.n_combo) + " products/target=" + std::to_string(d.total_rest * d.run);
-  r += d.n_splits > 0 ? " slices=" + std::to_string(d.n_splits) : std::string(" thread-per-target");
+  r += d.n_splits > 0 ? " slices=" + std::to_string(d.n_splits) : std::string(shared_walk(d) ? " wave-per-target" : " thread-per-target");
   if (d.zero_first) r += " zero-filled-first";
   return r;
 }
@@ -644,29 +674,30 @@ syno_status launch_view(const syno_plan* plan, int which, const void* A, const v
       hipLaunchKernelGGL(view_grad_zero, dim3((unsigned)std::min<int64_t>((words + kThreads - 1) / kThreads, 2048)), dim3(kThreads),
                          0, stream, static_cast<uint32_t*>(out), bytes);
     }
-    auto pick = [&](auto long_f32x, auto long_bfx, auto long_f32w, auto long_bfw) {
-      return to_x ? (ibf ? long_bfx : long_f32x) : (ibf ? long_bfw : long_f32w);
-    };
-    if (d.n_splits > 0) {
-      if (!ws) return SYNO_ERR_WORKSPACE;
-      double* partial = static_cast<double*>(ws);
-      int* t_index = reinterpret_cast<int*>(static_cast<char*>(ws) + grad_partial_bytes(d));
-      const dim3 grid((unsigned)(d.n_combo * d.n_splits));
-      auto k = pick(view_grad_long<false, true>, view_grad_long<true, true>, view_grad_long<false, false>, view_grad_long<true, false>);
-      hipLaunchKernelGGL(k, grid, dim3(kThreads), lds, stream, d, A, B, partial, t_index);
-      const dim3 sgrid((unsigned)((d.n_combo + kThreads - 1) / kThreads));
-      if (obf) hipLaunchKernelGGL(view_grad_sum<true>, sgrid, dim3(kThreads), 0, stream, partial, t_index, out, d.n_combo, d.n_splits);
-      else hipLaunchKernelGGL(view_grad_sum<false>, sgrid, dim3(kThreads), 0, stream, partial, t_index, out, d.n_combo, d.n_splits);
-    } else {
-      const dim3 grid((unsigned)((d.n_combo + kThreads - 1) / kThreads));
-      if (obf) {
-        hipLaunchKernelGGL((view_grad_short<true, true, true>), grid, dim3(kThreads), lds, stream, d, A, B, out);
+    auto launch = [&](auto ibf_c, auto obf_c, auto x_c) {
+      constexpr bool IBF = decltype(ibf_c)::value, OBF = decltype(obf_c)::value, TO_X = decltype(x_c)::value;
+      if (d.n_splits > 0) {
+        double* partial = static_cast<double*>(ws);
+        int* t_index = reinterpret_cast<int*>(static_cast<char*>(ws) + (d.n_splits > 1 ? grad_partial_bytes(d) : 0));
+        hipLaunchKernelGGL((view_grad_long<IBF, OBF, TO_X>), dim3((unsigned)(d.n_combo * d.n_splits)), dim3(kThreads), lds, stream, d, A, B,
+                           partial, t_index, out);
+        if (d.n_splits > 1)
+          hipLaunchKernelGGL(view_grad_sum<OBF>, dim3((unsigned)((d.n_combo + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, partial,
+                             t_index, out, d.n_combo, d.n_splits);
+      } else if (shared_walk(d)) {
+        const unsigned per = kThreads / 64;
+        hipLaunchKernelGGL((view_grad_short<IBF, OBF, TO_X, 64>), dim3((d.n_combo + per - 1) / per), dim3(kThreads), lds, stream, d, A, B, out);
       } else {
-        auto k = pick(view_grad_short<false, false, true>, view_grad_short<true, false, true>, view_grad_short<false, false, false>,
-                      view_grad_short<true, false, false>);
-        hipLaunchKernelGGL(k, grid, dim3(kThreads), lds, stream, d, A, B, out);
+        hipLaunchKernelGGL((view_grad_short<IBF, OBF, TO_X, 1>), dim3((unsigned)((d.n_combo + kThreads - 1) / kThreads)), dim3(kThreads), lds,
+                           stream, d, A, B, out);
       }
-    }
+    };
+    if (d.n_splits > 1 && !ws) return SYNO_ERR_WORKSPACE;
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    if (!to_x) ibf ? launch(yes, no, no) : launch(no, no, no);
+    else if (obf) launch(yes, yes, yes);
+    else ibf ? launch(yes, no, yes) : launch(no, no, yes);
     return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
   }
   ViewParams p;

@@ -852,6 +852,29 @@ def test_pure_views_small(syno, oracle, name, dt):
         assert torch.equal(dX, dX2)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("points", [8, 9, 63, 64, 65, 255, 257, 1023, 1024, 4097, 8192])
+def test_view_gradients_by_sum_length(syno, oracle, points, dt):
+    """A thread (up to 8 points), a wave (up to 1023), one workgroup and several per target; the copies of an Expand
+    make dX a sum of the same length."""
+    t = F32 if dt == "f32" else BF16
+    s = {4097: 17, 8192: 64}.get(points, 1)
+    b = Builder([("a", 5), ("r", points // s), ("s", s), ("c", 3)])
+    cx, cw = b.share(3)
+    b.expand(1)
+    b.expand(2)
+    expand = b.finish([0, cx], [cw], t, t)
+    for d in (wl.shifted_scale(points // s, 7, s, 1, t, t), expand):
+        xs, ws, _ = oracle.describe(d)
+        os_ = oracle.out_shape(d)
+        st = wl.Stream(63)
+        w = wl._finish(d, xs, ws, os_, st.normal(xs), st.uniform_pm(2.0, ws), st.normal(os_), 1)
+        assert run_all(syno, oracle, w, 0, directions=(1, 2)) == ["bandwidth_view"] * 3
+    plan = syno.Plan(d)
+    want = "thread-per-target" if points < 9 else "wave-per-target" if points < 1024 else "slices"
+    assert want in plan.describe(1), plan.describe(1)
+
+
 def test_pure_view_full_size(syno, oracle):
     """The shapes the benchmark's detail times (102.8 MB in and out), all three passes, in full against the checker
     (the weight gradients are one sum of 200704 products per channel, and one of 25.7 million)."""
