@@ -636,8 +636,8 @@ void view_configure(syno_plan* plan, int which) {
     static_assert(sizeof(ViewGradParams) <= sizeof(L.params), "parameter record does not fit");
     L.params_ready = fill_grad(plan, which == SYNO_BWD_DATA, d);
     memcpy(L.params, &d, sizeof d);
-    // several slices: their sums, then the target index of every combination
-    L.workspace = d.n_splits > 1 ? grad_partial_bytes(d) + (size_t)d.n_combo * 4 : 0;
+    // long sums: slice sums, then the target index of every combination (unused by a single slice)
+    L.workspace = d.n_splits > 0 ? grad_partial_bytes(d) + (size_t)d.n_combo * 4 : 0;
     return;
   }
   ViewParams p;
@@ -678,7 +678,7 @@ syno_status launch_view(const syno_plan* plan, int which, const void* A, const v
       constexpr bool IBF = decltype(ibf_c)::value, OBF = decltype(obf_c)::value, TO_X = decltype(x_c)::value;
       if (d.n_splits > 0) {
         double* partial = static_cast<double*>(ws);
-        int* t_index = reinterpret_cast<int*>(static_cast<char*>(ws) + (d.n_splits > 1 ? grad_partial_bytes(d) : 0));
+        int* t_index = reinterpret_cast<int*>(static_cast<char*>(ws) + grad_partial_bytes(d));
         hipLaunchKernelGGL((view_grad_long<IBF, OBF, TO_X>), dim3((unsigned)(d.n_combo * d.n_splits)), dim3(kThreads), lds, stream, d, A, B,
                            partial, t_index, out);
         if (d.n_splits > 1)
@@ -692,7 +692,7 @@ syno_status launch_view(const syno_plan* plan, int which, const void* A, const v
                            stream, d, A, B, out);
       }
     };
-    if (d.n_splits > 1 && !ws) return SYNO_ERR_WORKSPACE;
+    if (d.n_splits > 0 && !ws) return SYNO_ERR_WORKSPACE;
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
     if (!to_x) ibf ? launch(yes, no, no) : launch(no, no, no);

@@ -852,6 +852,33 @@ def test_pure_views_small(syno, oracle, name, dt):
         assert torch.equal(dX, dX2)
 
 
+@pytest.mark.parametrize("kh,kw", [(1, 1), (1, 3), (3, 1), (3, 3), (5, 1)])
+@pytest.mark.parametrize("N,C,Co,H,W", [
+    (1, 1, 8, 2, 4),          # one item per row, fewer pixels than a chunk
+    (3, 17, 33, 5, 7),        # one past a tile of channels; a row ends inside an item, and so does the tensor
+    (2, 32, 64, 9, 16),       # whole items, rows without filling between them
+    (7, 40, 24, 11, 30),      # ragged channels, several chunks
+    (1, 3, 70, 37, 13),       # an odd width: rows at every alignment
+    (2, 20, 36, 6, 64),       # the widest rows of a 5-row window
+])
+def test_bf16_weight_gradient_stream(syno, oracle, kh, kw, N, C, Co, H, W):
+    """Windows, tile edges, row ends and the number of splits of the bf16 weight gradient's pixel stream."""
+    d = wl.conv2d(N, C, Co, H, W, kh, kw, BF16, F32)
+    xs, ws, _ = oracle.describe(d)
+    os_ = oracle.out_shape(d)
+    st = wl.Stream(64)
+    w = wl._finish(d, xs, ws, os_, st.normal(xs), st.uniform_pm(2.0, ws), st.normal(os_), 1)
+    seen = set()
+    for workgroups in (0, 1, 1000):
+        plan = syno.Plan(d, dw_workgroups=workgroups)
+        text = plan.describe(2)
+        assert " stream pixels/chunk=" in text, text
+        seen.add(text.split("splits=")[1].split()[0])
+        run_all(syno, oracle, w, 0, directions=(2,), dw_workgroups=workgroups)
+    chunks = int(text.split("chunks=")[1].split()[0])
+    assert len(seen) > 1 or chunks == 1, (seen, text)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("points", [8, 9, 63, 64, 65, 255, 257, 1023, 1024, 4097, 8192])
 def test_view_gradients_by_sum_length(syno, oracle, points, dt):
