@@ -105,6 +105,11 @@ def load_library():
 _TORCH_DTYPE = {0: torch.float32, 1: torch.bfloat16}
 
 
+def _stream(device: torch.device) -> int:
+    """The handle of the stream that is current on `device` (without the object that torch.cuda.current_stream wraps it in: 1 us)."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
 def _marshal(desc, options=None):
     """OpDesc-like object (+ a dict of syno_plan_options fields) -> (syno_desc, objects that must stay alive
     while it is used)."""
@@ -159,6 +164,9 @@ class Plan:
         self.x_shape = tuple(xs[:xr.value])
         self.w_shape = tuple(ws[:wr.value])
         self.out_shape = tuple(os_[:orr.value])
+        # what a call needs of the plan, asked for once (the plan does not change)
+        self._elems = {s: self._numel(s) for s in (self.x_shape, self.w_shape, self.out_shape)}
+        self._need = [self.workspace_bytes(which) for which in range(3)]
         self._ws = {}
 
     def __del__(self):
@@ -200,15 +208,16 @@ class Plan:
             n *= int(s)
         return n
 
-    def _arg(self, t: torch.Tensor, shape, dtype, what: str) -> int:
-        if not (t.is_cuda and t.is_contiguous() and t.dtype == dtype and t.numel() == self._numel(shape)):
-            raise ValueError(f"{what}: need a contiguous {dtype} device tensor with {self._numel(shape)} elements")
-        if t.data_ptr() % 16:
-            raise ValueError(f"{what}: pointer must be 16-byte aligned")
-        return t.data_ptr()
+    def _arg(self, t: torch.Tensor, shape, dtype, *what: str) -> int:
+        if not (t.is_cuda and t.dtype is dtype and t.numel() == self._elems[shape] and t.is_contiguous()):
+            raise ValueError(f"{' '.join(what)}: need a contiguous {dtype} device tensor with {self._elems[shape]} elements")
+        p = t.data_ptr()
+        if p & 15:
+            raise ValueError(f"{' '.join(what)}: pointer must be 16-byte aligned")
+        return p
 
     def _workspace(self, which: int, device, workspace: Optional[torch.Tensor]) -> int:
-        need = self.workspace_bytes(which)
+        need = self._need[which]
         if need == 0:
             return 0
         if workspace is None:
@@ -220,14 +229,13 @@ class Plan:
         return workspace.data_ptr()
 
     def _call(self, fn, which, a, a_shape, b, b_shape, out, out_shape, out_dtype, workspace, what):
-        pa = self._arg(a, a_shape, self.in_dtype, what + " first input")
-        pb = self._arg(b, b_shape, self.in_dtype, what + " second input")
+        pa = self._arg(a, a_shape, self.in_dtype, what, "first input")
+        pb = self._arg(b, b_shape, self.in_dtype, what, "second input")
+        device = a.device
         if out is None:
-            out = torch.empty(out_shape if out_shape else (1,), dtype=out_dtype, device=a.device)
-        po = self._arg(out, out_shape, out_dtype, what + " output")
-        ws = self._workspace(which, a.device, workspace)
-        stream = torch.cuda.current_stream(a.device).cuda_stream
-        st = fn(self._h, pa, pb, po, ws, stream)
+            out = torch.empty(out_shape if out_shape else (1,), dtype=out_dtype, device=device)
+        po = self._arg(out, out_shape, out_dtype, what, "output")
+        st = fn(self._h, pa, pb, po, self._workspace(which, device, workspace), _stream(device))
         if st:
             raise SynoError(st, what)
         return out
@@ -240,11 +248,11 @@ class Plan:
                   (self.out_shape, self.w_shape, self.x_shape, self.out_dtype),
                   (self.x_shape, self.out_shape, self.w_shape, torch.float32))[which]
         name = ("syno_forward", "syno_backward_data", "syno_backward_weight")[which]
-        pa = self._arg(a, shapes[0], self.in_dtype, name + " first input")
-        pb = self._arg(b, shapes[1], self.in_dtype, name + " second input")
-        po = self._arg(out, shapes[2], shapes[3], name + " output")
+        pa = self._arg(a, shapes[0], self.in_dtype, name, "first input")
+        pb = self._arg(b, shapes[1], self.in_dtype, name, "second input")
+        po = self._arg(out, shapes[2], shapes[3], name, "output")
         ws = self._workspace(which, a.device, workspace)
-        stream = torch.cuda.current_stream(a.device).cuda_stream
+        stream = _stream(a.device)
         fn, h = getattr(load_library(), name), self._h
 
         def launch():
@@ -254,15 +262,15 @@ class Plan:
         return launch
 
     def forward(self, X, W, out=None, workspace=None):
-        return self._call(load_library().syno_forward, FWD, X, self.x_shape, W, self.w_shape, out, self.out_shape,
+        return self._call(_lib.syno_forward, FWD, X, self.x_shape, W, self.w_shape, out, self.out_shape,
                           self.out_dtype, workspace, "syno_forward")
 
     def backward_data(self, G, W, dX=None, workspace=None):
-        return self._call(load_library().syno_backward_data, BWD_DATA, G, self.out_shape, W, self.w_shape, dX,
+        return self._call(_lib.syno_backward_data, BWD_DATA, G, self.out_shape, W, self.w_shape, dX,
                           self.x_shape, self.out_dtype, workspace, "syno_backward_data")
 
     def backward_weight(self, X, G, dW=None, workspace=None):
-        return self._call(load_library().syno_backward_weight, BWD_WEIGHT, X, self.x_shape, G, self.out_shape, dW,
+        return self._call(_lib.syno_backward_weight, BWD_WEIGHT, X, self.x_shape, G, self.out_shape, dW,
                           self.w_shape, torch.float32, workspace, "syno_backward_weight")
 
     def backward_weight_static(self, X, G, dW):
@@ -270,7 +278,7 @@ class Plan:
         px = self._arg(X, self.x_shape, self.in_dtype, "syno_backward_weight_static X")
         pg = self._arg(G, self.out_shape, self.in_dtype, "syno_backward_weight_static G")
         po = self._arg(dW, self.w_shape, torch.float32, "syno_backward_weight_static dW")
-        st = load_library().syno_backward_weight_static(self._h, px, pg, po, torch.cuda.current_stream(X.device).cuda_stream)
+        st = load_library().syno_backward_weight_static(self._h, px, pg, po, _stream(X.device))
         if st:
             raise SynoError(st, "syno_backward_weight_static")
         return dW
@@ -362,6 +370,7 @@ class Chain:
         self.stages = [Plan(descs[i], _borrowed=lib.syno_chain_plan(self._h, i), _owner=self) for i in range(n)]
         # dX has the first stage's output type; for a materialised graph, the graph's
         self.dx_dtype = _TORCH_DTYPE[int(_materialize.out_dtype)] if _materialize is not None else self.stages[0].out_dtype
+        self._need = [self.workspace_bytes(which) for which in range(2)]
         self._ws = {}
 
     @classmethod
@@ -385,7 +394,7 @@ class Chain:
         return n.value
 
     def _workspace(self, which, device, workspace):
-        need = self.workspace_bytes(which)
+        need = self._need[which]
         if need == 0:
             return 0
         if workspace is None:
@@ -422,7 +431,7 @@ class Chain:
             out = torch.empty(last.out_shape, dtype=last.out_dtype, device=X.device)
         po = last._arg(out, last.out_shape, last.out_dtype, "syno_chain_forward out")
         ws = self._workspace(0, X.device, workspace)
-        stream = torch.cuda.current_stream(X.device).cuda_stream
+        stream = _stream(X.device)
         st = load_library().syno_chain_forward(self._h, px, self._ptrs(pw), self._ptrs(pa), po, ws, stream)
         if st:
             raise SynoError(st, "syno_chain_forward")
@@ -452,7 +461,7 @@ class Chain:
                 dX = torch.empty(first.x_shape, dtype=self.dx_dtype, device=X.device)
             pdx = first._arg(dX, first.x_shape, self.dx_dtype, "syno_chain_backward dX")
         ws = self._workspace(1, X.device, workspace)
-        stream = torch.cuda.current_stream(X.device).cuda_stream
+        stream = _stream(X.device)
         st = load_library().syno_chain_backward(self._h, px, self._ptrs(pw), self._ptrs(pa), pg, pdx,
                                                 self._ptrs(pdw), ws, stream)
         if st:
