@@ -124,7 +124,7 @@ syno_status run(const syno_plan* plan, int which, const void* A, const void* B, 
       // gradients of a strided convolution on the stride's phase planes (see the planner)
       if (!ws) return SYNO_ERR_WORKSPACE;
       const syno::ConvLike& c = plan->conv;
-      const int window = plan->phase_window;
+      const int window = which == SYNO_BWD_WEIGHT ? plan->phase_window_dw : plan->phase_window_dx;
       const size_t esz = plan->in_dtype == SYNO_BF16 ? 2 : 4, osz = plan->out_dtype == SYNO_BF16 ? 2 : 4;
       const int ps = plan->phase_s;
       const size_t CP = (size_t)c.Cg * ps * ps;
@@ -134,9 +134,14 @@ syno_status run(const syno_plan* plan, int which, const void* A, const void* B, 
         void* Xp = w0;
         float* dWp = reinterpret_cast<float*>(w0 + round_up((size_t)plan->phase_view_x->out_elems * esz));
         void* rest = reinterpret_cast<char*>(dWp) + round_up((size_t)c.Og * CP * window * window * 4);
-        const void* one = unit_weight(plan->in_dtype);
-        if (!one) return SYNO_ERR_HIP;
-        syno_status st = run(plan->phase_view_x, SYNO_FWD, B, one, Xp, nullptr, stream);
+        syno_status st;
+        if (ps == 2) {
+          st = syno::launch_phase_planes(c, true, (int)esz, B, Xp, stream);
+        } else {
+          const void* one = unit_weight(plan->in_dtype);
+          if (!one) return SYNO_ERR_HIP;
+          st = run(plan->phase_view_x, SYNO_FWD, B, one, Xp, nullptr, stream);
+        }
         if (st != SYNO_OK) return st;
         st = run(plan->phase_conv_dw, SYNO_BWD_WEIGHT, A, Xp, dWp, rest, stream);
         if (st != SYNO_OK) return st;
@@ -146,13 +151,15 @@ syno_status run(const syno_plan* plan, int which, const void* A, const void* B, 
       void* Wpp = w0;
       void* dXp = w0 + round_up(CP * c.Og * window * window * esz);
       void* rest = static_cast<char*>(dXp) + round_up((size_t)plan->phase_view_dx->out_elems * osz);
-      const void* one = unit_weight(plan->out_dtype);
-      if (!one) return SYNO_ERR_HIP;
       syno_status st = syno::launch_phase_weight_build(c, ps, window, (int)esz, B, Wpp, stream);
       if (st != SYNO_OK) return st;
-      st = run(plan->phase_conv_dx, SYNO_FWD, A, Wpp, dXp, rest, stream);
+      const int pass = window == 2 ? SYNO_BWD_DATA : SYNO_FWD;
+      st = run(plan->phase_conv_dx, pass, A, Wpp, dXp, rest, stream);
       if (st != SYNO_OK) return st;
-      void* view_ws = static_cast<char*>(rest) + plan->phase_conv_dx->launch[SYNO_FWD].workspace;
+      if (ps == 2) return syno::launch_phase_planes(c, false, (int)osz, dXp, out, stream);
+      const void* one = unit_weight(plan->out_dtype);
+      if (!one) return SYNO_ERR_HIP;
+      void* view_ws = static_cast<char*>(rest) + plan->phase_conv_dx->launch[pass].workspace;
       return run(plan->phase_view_dx, SYNO_BWD_DATA, dXp, one, out, view_ws, stream);
     }
     default: return SYNO_ERR_UNSUPPORTED;
@@ -256,9 +263,10 @@ syno_status syno_plan_describe(const syno_plan* plan, int which, char* buf, size
     case syno::KERNEL_MFMA_PHASES: {
       char inner[400];
       const syno_plan* conv = which == SYNO_BWD_WEIGHT ? plan->phase_conv_dw : plan->phase_conv_dx;
-      if (syno_plan_describe(conv, which == SYNO_BWD_WEIGHT ? SYNO_BWD_WEIGHT : SYNO_FWD, inner, sizeof(inner)) == SYNO_OK)
+      const int pass = which == SYNO_BWD_WEIGHT ? SYNO_BWD_WEIGHT : plan->phase_window_dx == 2 ? SYNO_BWD_DATA : SYNO_FWD;
+      if (syno_plan_describe(conv, pass, inner, sizeof(inner)) == SYNO_OK)
         d += std::string(which == SYNO_BWD_WEIGHT ? " space-to-depth of X, then the weight gradient of a stride-1 convolution over the phase planes: "
-                                                  : " forward contraction onto the phase planes of dX, then depth-to-space: ") + inner;
+                                                  : " contraction onto the phase planes of dX, then depth-to-space: ") + inner;
       break;
     }
     case syno::KERNEL_MFMA_TRANSPOSED: {

@@ -315,7 +315,7 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     const int xoff = MODE == 2 && (ch & 1) ? p.x_bytes : 0;
     const int woff = b_base + (wbuf ? p.w_bytes : 0);
     auto a_off = [&](int q) {
-      const int tap = sub * TS + q, kh = p.KW == 3 ? tap / 3 : tap, kw = p.KW == 3 ? tap - 3 * kh : 0;
+      const int tap = sub * TS + q, kh = T == 4 ? tap / 2 : p.KW == 3 ? tap / 3 : tap, kw = T == 4 ? tap & 1 : p.KW == 3 ? tap - 3 * kh : 0;
       return xoff + (kh * p.Wp + kw) * 48;
     };
     uint4 a[2][kPlanes], b[TN][kPlanes];
@@ -546,17 +546,15 @@ void launch_split_one(const SplitParams& p, const float* X, const float* W, floa
 template <int WM, int WN, int WK, int TN, int T, int MODE, int N>
 void launch_split_tiles(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s) {
   if (tiles == N) {
-    // X items per thread: 1, 2 or 4
-    if (p.x_items > 2) {
-      if (p.adjoint) launch_split_one<WM, WN, WK, N, TN, T, MODE, 4, true>(p, X, W, out, s);
-      else launch_split_one<WM, WN, WK, N, TN, T, MODE, 4, false>(p, X, W, out, s);
-    } else if (p.x_items > 1) {
-      if (p.adjoint) launch_split_one<WM, WN, WK, N, TN, T, MODE, 2, true>(p, X, W, out, s);
-      else launch_split_one<WM, WN, WK, N, TN, T, MODE, 2, false>(p, X, W, out, s);
-    } else {
-      if (p.adjoint) launch_split_one<WM, WN, WK, N, TN, T, MODE, 1, true>(p, X, W, out, s);
-      else launch_split_one<WM, WN, WK, N, TN, T, MODE, 1, false>(p, X, W, out, s);
-    }
+    // X items per thread: 1, 2 or 4.  2x2 windows: backward-data only
+    auto go = [&](auto xi_c) {
+      constexpr int XI = decltype(xi_c)::value;
+      if (T == 4 || p.adjoint) launch_split_one<WM, WN, WK, N, TN, T, MODE, XI, true>(p, X, W, out, s);
+      else if constexpr (T != 4) launch_split_one<WM, WN, WK, N, TN, T, MODE, XI, false>(p, X, W, out, s);
+    };
+    if (p.x_items > 2) go(std::integral_constant<int, 4>{});
+    else if (p.x_items > 1) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 1>{});
   } else if constexpr (N > 1) {
     launch_split_tiles<WM, WN, WK, TN, T, MODE, N - 1>(tiles, p, X, W, out, s);
   }
@@ -568,6 +566,9 @@ void launch_split_tiles(int tiles, const SplitParams& p, const float* X, const f
 void launch_split_0_9(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s);
 void launch_split_1_9(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s);
 void launch_split_2_9(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s);
+void launch_split_0_4(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s);
+void launch_split_1_4(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s);
+void launch_split_2_4(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s);
 void launch_split_0_3(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s);
 void launch_split_1_3(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s);
 void launch_split_3_1(int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s);

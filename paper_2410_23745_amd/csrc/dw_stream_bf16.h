@@ -215,7 +215,7 @@ __global__ __launch_bounds__(512) void dw_stream_bf16(const DwParams p, const ui
           const uint32_t prev = col[ks] == 0 ? 0u : v.prev, next = col[ks] == p.pitch - 8 ? 0u : v.next;
           a[0][i] = make_uint4(alignbit16(c.y, c.x), alignbit16(c.z, c.y), alignbit16(c.w, c.z), alignbit16(next, c.w));
           a[1][i] = c;
-          a[2][i] = make_uint4(alignbit16(c.x, prev), alignbit16(c.y, c.x), alignbit16(c.z, c.y), alignbit16(c.w, c.z));
+          if constexpr (KW == 3) a[KW - 1][i] = make_uint4(alignbit16(c.x, prev), alignbit16(c.y, c.x), alignbit16(c.z, c.y), alignbit16(c.w, c.z));
         }
       }
     };

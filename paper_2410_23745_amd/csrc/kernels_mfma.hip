@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void phase_weight_gather(const PhaseParams q, 
   const int o = r / q.C;
   const int dh = floor_div(kh - q.p, q.s), a = kh - q.p - q.s * dh;
   const int dw = floor_div(kw - q.p, q.s), b = kw - q.p - q.s * dw;
-  const int th = q.window == 3 ? dh + 1 : 0, tw = q.window == 3 ? dw + 1 : 0;
+  const int th = q.window >= 2 ? dh + 1 : 0, tw = q.window >= 2 ? dw + 1 : 0;
   const int cp = (c * q.s + a) * q.s + b;
   dW[(int64_t)o * q.ws_o + (int64_t)c * q.ws_c + kh * q.ws_kh + kw * q.ws_kw] =
       dWp[(((int64_t)o * q.C * q.s * q.s + cp) * q.window + th) * q.window + tw];
@@ -204,15 +204,44 @@ __global__ __launch_bounds__(256) void phase_weight_build(const PhaseParams q, c
   int r = i;
   const int tw = r % q.window; r /= q.window;
   const int th = r % q.window; r /= q.window;
-  const int o = r % q.O;
-  const int cp = r / q.O;
+  const int o = q.window == 2 ? r / CP : r % q.O;
+  const int cp = q.window == 2 ? r - o * CP : r / q.O;
   const int b = cp % q.s, a = (cp / q.s) % q.s, c = cp / (q.s * q.s);
-  const int dh = q.window == 3 ? th - 1 : 0, dw = q.window == 3 ? tw - 1 : 0;
+  // (window 2: the convolution's own taps, of rows -1 and 0; else its adjoint's)
+  const int dh = q.window == 3 ? th - 1 : q.window == 2 ? 1 - th : 0, dw = q.window == 3 ? tw - 1 : q.window == 2 ? 1 - tw : 0;
   const int kh = a + q.p - q.s * dh, kw = b + q.p - q.s * dw;
   T v = 0;
   if (kh >= 0 && kh < q.K && kw >= 0 && kw < q.K)
     v = W[(int64_t)o * q.ws_o + (int64_t)c * q.ws_c + kh * q.ws_kh + kw * q.ws_kw];
   Wpp[i] = v;
+}
+
+// Image rows into the planes of their even and odd pixels (TO) or back: a thread moves V pixels of each of two planes, 2V adjacent
+// pixels of the image.  Bound by memory: 32x64x56x56 fp32 10.8 us (the general view kernel 21.4).
+template <class T, int V, bool TO>
+__global__ __launch_bounds__(256) void phase_planes(const T* __restrict__ src, T* __restrict__ dst, uint32_t Ho, uint32_t Wo, uint32_t items) {
+  typedef T run __attribute__((ext_vector_type(V)));
+  typedef T pair __attribute__((ext_vector_type(2 * V), aligned(sizeof(T) * 2 * V > 16 ? 16 : sizeof(T) * 2 * V)));
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  if (i >= items) return;
+  const uint32_t per = (uint32_t)(Wo / V), line = i / per;       // image row: (plane pair, h', a)
+  const uint32_t w = (i - line * per) * V, nc = line / (2u * Ho), row = line - nc * 2u * Ho, a = row & 1, h = row >> 1;
+  // (elements of a tensor: below 2^31)
+  const uint32_t image = line * 2u * Wo + 2 * w, plane = (((nc * 2 + a) * 2) * Ho + h) * Wo + w, next = (uint32_t)Ho * Wo;
+  if constexpr (TO) {
+    const pair v = *reinterpret_cast<const pair*>(src + image);
+    run e, o;
+#pragma unroll
+    for (int k = 0; k < V; ++k) { e[k] = v[2 * k]; o[k] = v[2 * k + 1]; }
+    *reinterpret_cast<run*>(dst + plane) = e;
+    *reinterpret_cast<run*>(dst + plane + next) = o;
+  } else {
+    const run e = *reinterpret_cast<const run*>(src + plane), o = *reinterpret_cast<const run*>(src + plane + next);
+    pair v;
+#pragma unroll
+    for (int k = 0; k < V; ++k) { v[2 * k] = e[k]; v[2 * k + 1] = o[k]; }
+    *reinterpret_cast<pair*>(dst + image) = v;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -427,7 +456,8 @@ constexpr int kNumSplitConfigs = 4;
 constexpr SplitConfig kSplitConfigs[kNumSplitConfigs] = {{4, 2, 1, 2, 0, 7}, {4, 1, 2, 2, 1, 7}, {2, 1, 4, 2, 2, 7}, {4, 2, 1, 4, 2, 4}};
 
 void launch_split(int cfg, int T, int tiles, const SplitParams& p, const float* X, const float* W, float* out, hipStream_t s) {
-  if (cfg == 0) (T == 9 ? launch_split_0_9 : launch_split_0_3)(tiles, p, X, W, out, s);
+  if (T == 4) (cfg == 0 ? launch_split_0_4 : cfg == 1 ? launch_split_1_4 : launch_split_2_4)(tiles, p, X, W, out, s);
+  else if (cfg == 0) (T == 9 ? launch_split_0_9 : launch_split_0_3)(tiles, p, X, W, out, s);
   else if (cfg == 1) (T == 9 ? launch_split_1_9 : launch_split_1_3)(tiles, p, X, W, out, s);
   else if (cfg == 2) launch_split_2_9(tiles, p, X, W, out, s);
   else launch_split_3_1(tiles, p, X, W, out, s);
@@ -439,8 +469,9 @@ bool fill_split(const syno_plan* plan, int which, int cfg, int TR, SplitParams& 
   if ((which == SYNO_FWD ? plan->x_elems : plan->out_elems) * 4 >= (1ll << 32)) return false;
   const SplitConfig& v = kSplitConfigs[cfg];
   const int T = c.KH * c.KW;
-  if ((c.KH != 1 && c.KH != 3) || (c.KW != 1 && c.KW != 3)) return false;
-  if ((cfg == 3) != (T == 1) || (v.WK == 4 && T < 9)) return false;      // (every wave needs a tap in every stage)
+  // windows of 1 or 3 along either axis; backward-data also of 2x2 (the gradients of strided convolutions)
+  if (T == 4 ? c.KH != 2 || c.KW != 2 || which == SYNO_FWD : (c.KH != 1 && c.KH != 3) || (c.KW != 1 && c.KW != 3)) return false;
+  if ((cfg == 3) != (T == 1) || (v.WK == 4 && T < 4)) return false;      // (every wave needs a tap in every stage)
   // weights in the forward layout, whole weight items
   if ((c.KW > 1 && c.ws_kw != 1) || (c.KH > 1 && c.ws_kh != c.KW) || c.ws_c != T) return false;
   p = SplitParams{};
@@ -783,6 +814,31 @@ syno_status launch_phase_weight_build(const ConvLike& c, int s, int window, int 
     hipLaunchKernelGGL(phase_weight_build<uint32_t>, grid, dim3(256), 0, stream, q, static_cast<const uint32_t*>(W), static_cast<uint32_t*>(Wpp));
   else
     hipLaunchKernelGGL(phase_weight_build<uint16_t>, grid, dim3(256), 0, stream, q, static_cast<const uint16_t*>(W), static_cast<uint16_t*>(Wpp));
+  return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
+}
+
+syno_status launch_phase_planes(const ConvLike& c, bool to_planes, int elem_bytes, const void* src, void* dst, hipStream_t stream) {
+  // four pixels of a plane per thread where every run is as long and aligned as that: the width a multiple of 4 (planes of
+  // h' x w' pixels then begin at multiples of 4, too), else one
+  const int V = c.Wo % 4 == 0 ? 4 : 1;
+  const int64_t items = (int64_t)c.N * c.Cg * 2 * c.Ho * (c.Wo / V);
+  if (items * 2 * V >= (1ll << 31)) return SYNO_ERR_SHAPE;
+  const dim3 grid((unsigned)((items + 255) / 256));
+  auto go = [&](auto t, auto v_c, auto to_c) {
+    using T = decltype(t);
+    hipLaunchKernelGGL((phase_planes<T, decltype(v_c)::value, decltype(to_c)::value>), grid, dim3(256), 0, stream, static_cast<const T*>(src),
+                       static_cast<T*>(dst), (uint32_t)c.Ho, (uint32_t)c.Wo, (uint32_t)items);
+  };
+  auto by_width = [&](auto t, auto to_c) {
+    if (V == 4) go(t, std::integral_constant<int, 4>{}, to_c);
+    else go(t, std::integral_constant<int, 1>{}, to_c);
+  };
+  auto by_way = [&](auto t) {
+    if (to_planes) by_width(t, std::true_type{});
+    else by_width(t, std::false_type{});
+  };
+  if (elem_bytes == 4) by_way(uint32_t{});
+  else by_way(uint16_t{});
   return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
 }
 

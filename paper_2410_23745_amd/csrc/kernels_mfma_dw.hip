@@ -626,7 +626,7 @@ uint32_t magic_of(int d) { return (uint32_t)(((1ull << 32) + d - 1) / d); }
 // bf16: the stream kernel's tile of sums per window - output-channel and input-channel tiles of 16 per wave, waves side by side
 // along the input channels (the other waves share the k-steps)
 struct StreamTile { int no, nc, wc; };
-constexpr StreamTile stream_tile(int T) { return T == 1 ? StreamTile{4, 4, 1} : T == 3 ? StreamTile{2, 2, 1} : StreamTile{2, 1, 2}; }
+constexpr StreamTile stream_tile(int T) { return T == 1 ? StreamTile{4, 4, 1} : T <= 4 ? StreamTile{2, 2, 1} : StreamTile{2, 1, 2}; }
 
 bool fill_dw_stream(const syno_plan* plan, DwParams& p) {
   const ConvLike& c = plan->conv;
@@ -781,17 +781,19 @@ bool fill_dw_f32_as(const syno_plan* plan, DwParams& p, bool direct) {
 // Windows with a row extent take the kernel with the alternating wave halves when their rows fit its item lists,
 // else (and all other windows) the kernel that looks its rows up in a table.
 bool fill_dw_f32(const syno_plan* plan, DwParams& p) {
+  if (plan->conv.KH == 2) return false;          // (not instantiated)
   if (plan->conv.KH == 3 && fill_dw_f32_as(plan, p, true)) return true;
   return fill_dw_f32_as(plan, p, false);
 }
 
-// fp32 on the bf16 matrix cores: windows of 1 or 3 along either axis, rows not cyclic.  Images of up to 4 columns, of whose
+// fp32 on the bf16 matrix cores: windows of 1 or 3 along either axis, or 2x2, rows not cyclic.  Images of up to 4 columns, of whose
 // rows at least half would be filling, and a single chunk of pixels, where there is nothing to overlap the splitting with,
 // stay with the fp32 instructions: 64x256x256 64x1 3x1 86 us against 52, 1x1024x1024 7x7 50.5 against 45; from 7 columns
 // and two chunks on this one is ahead (2x512x512 7x7 26.5 against 26.4, 4x512x512 29.9 against 31.1, 32x64x64 56x56 59 against 86).
 bool fill_dw_split(const syno_plan* plan, DwParams& p) {
   const ConvLike& c = plan->conv;
-  if (c.h_wrap || (c.KH != 1 && c.KH != 3) || (c.KW != 1 && c.KW != 3) || c.Wo <= 4) return false;
+  if (c.h_wrap || c.Wo <= 4) return false;
+  if (c.KH == 2 ? c.KW != 2 : (c.KH != 1 && c.KH != 3) || (c.KW != 1 && c.KW != 3)) return false;
   if (std::max(plan->x_elems, plan->out_elems) * 4 >= kNoPixel) return false;        // byte offsets
   p = DwParams{};
   p.G = c.G; p.Og = c.Og; p.Cg = c.Cg; p.H = c.Ho; p.W = c.Wo; p.KH = c.KH; p.KW = c.KW; p.ph = c.ph; p.pw = c.pw;
@@ -846,11 +848,12 @@ bool mfma_dw_supports(const syno_plan* p) {
   if (p->in_dtype != SYNO_BF16 && p->in_dtype != SYNO_F32) return false;
   const ConvLike& c = p->conv;
   if (c.sh != 1 || c.sw != 1 || c.w_wrap) return false;
-  // windows: 1, 3 or 5 along an axis, at most 9 taps (each tap is a set of accumulators); a 5-wide window along the
+  // windows: 1, 3 or 5 along an axis or 2x2, at most 9 taps (each tap is a set of accumulators); a 5-wide window along the
   // row only with fp32 inputs (the bf16 kernels cut their shifted fragments for 3-wide windows)
-  if (c.KH != 1 && ((c.KH != 3 && c.KH != 5) || c.h_wrap || c.ph != c.KH / 2 || c.ws_kh < 0)) return false;
+  if ((c.KH == 2) != (c.KW == 2)) return false;
+  if (c.KH != 1 && ((c.KH != 2 && c.KH != 3 && c.KH != 5) || c.h_wrap || c.ph != c.KH / 2 || c.ws_kh < 0)) return false;
   if (c.Wi != c.Wo || c.Hi != c.Ho) return false;
-  if (c.KW != 1 && c.KW != 3 && !(c.KW == 5 && p->in_dtype == SYNO_F32)) return false;
+  if (c.KW > 3 && !(c.KW == 5 && p->in_dtype == SYNO_F32)) return false;
   if (c.KH * c.KW > 9) return false;
   if (c.pw != c.KW / 2) return false;
   if (c.ws_kw < 0 || (c.Og == 1 && c.Cg == 1)) return false;
@@ -915,7 +918,8 @@ syno_status launch_mfma_dw(const syno_plan* plan, const void* A, const void* B, 
   float* const dst = p.n_splits == 1 ? static_cast<float*>(out) : static_cast<float*>(ws);
   using std::integral_constant;
   auto by_window = [&](auto go) {
-    if (p.KH == 3 && p.KW == 3) go(integral_constant<int, 3>{}, integral_constant<int, 3>{}, integral_constant<int, 1>{});
+    if (p.KH == 2) go(integral_constant<int, 2>{}, integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    else if (p.KH == 3 && p.KW == 3) go(integral_constant<int, 3>{}, integral_constant<int, 3>{}, integral_constant<int, 1>{});
     else if (p.KH == 5) go(integral_constant<int, 5>{}, integral_constant<int, 1>{}, integral_constant<int, 1>{});
     else if (p.KW == 5) go(integral_constant<int, 1>{}, integral_constant<int, 5>{}, integral_constant<int, 1>{});
     else if (p.KH == 3) go(integral_constant<int, 3>{}, integral_constant<int, 1>{}, integral_constant<int, 2>{});
@@ -934,6 +938,7 @@ syno_status launch_mfma_dw(const syno_plan* plan, const void* A, const void* B, 
           else if (p.W % 2 == 0) launch_dw_kernel(dw_split<kh, kw, ct, 2, false>, grid, p, Gf, Xf, dst, stream, 512);
           else launch_dw_kernel(dw_split<kh, kw, ct, 1, false>, grid, p, Gf, Xf, dst, stream, 512);
         }
+      } else if constexpr (kh == 2) {            // (no kernel on the fp32 instructions)
       } else if (kh == 3 && p.direct) {
         if constexpr (kh == 3) {
         if (p.mode == 4) launch_dw_kernel(dw_rows_f32<kw, ct, 4>, grid, p, Gf, Xf, dst, stream, kRowsThreads);

@@ -153,7 +153,9 @@ struct syno_plan {
   // and in the result element type; phase_conv_dw / phase_conv_dx: the stride-1 convolutions whose backward-weight and
   // forward contractions do the work (owned)
   syno_plan *phase_view_x = nullptr, *phase_view_dx = nullptr, *phase_conv_dw = nullptr, *phase_conv_dx = nullptr;
-  int32_t phase_window = 0;      // window of those convolutions: 3 (pad 1) or 1
+  // windows of those convolutions, per gradient: 3 (pad 1), 2 (rows and columns -1 and 0) or 1.  With window 2 dX is that
+  // convolution's backward-data, else the forward contraction of its adjoint
+  int32_t phase_window_dw = 0, phase_window_dx = 0;
   int32_t phase_s = 0;           // phases per image axis that take part: s, or 1 for a 1x1 window, which only reads phase
                                  // (0, 0) - the view is then the sub-sampling X[.., s*h', s*w'] itself
   ~syno_plan() { delete inner; delete inner_dx; delete phase_view_x; delete phase_view_dx; delete phase_conv_dw; delete phase_conv_dx; }
@@ -229,9 +231,12 @@ std::string gemm_describe(const syno_plan* p, int which);
 syno_status launch_gemm(const syno_plan* p, int which, const void* A, const void* B, void* out, void* ws, hipStream_t stream);
 // kernels_mfma.hip, gradients of a strided convolution through the phase planes:
 // (s = the phases per axis that take part: the stride, or 1 when only phase (0,0) is read)
-// dW[o,c,kh,kw] (any strides) = dWp[o][(c*s+a)*s+b][th][tw] with s*dh+a = kh-p, th = dh+1 (window 3) or 0 (window 1)
+// dW[o,c,kh,kw] (any strides) = dWp[o][(c*s+a)*s+b][th][tw] with s*dh+a = kh-p, th = dh+1 (window 2 or 3) or 0 (window 1)
 syno_status launch_phase_weight_gather(const ConvLike& c, int s, int window, const float* dWp, float* dW, hipStream_t stream);
-// Wpp[(c*s+a)*s+b][o][th][tw] (contiguous, 2- or 4-byte elements) = W[o,c,kh,kw] with kh = a+p-s*dh, or 0 where there is none
+// Wpp[(c*s+a)*s+b][o][th][tw] (contiguous, 2- or 4-byte elements) = W[o,c,kh,kw] with kh = a+p-s*dh, or 0 where there is none;
+// window 2: Wpp[o][(c*s+a)*s+b][th][tw] with kh = a+p+s*(th-1)
+// planes[n][(c,a,b)][h'][w'] = image[n][c][2h'+a][2w'+b] (s = 2, 2- or 4-byte elements, c.Wo columns of planes), or the way back
+syno_status launch_phase_planes(const ConvLike& c, bool to_planes, int elem_bytes, const void* src, void* dst, hipStream_t stream);
 syno_status launch_phase_weight_build(const ConvLike& c, int s, int window, int elem_bytes, const void* W, void* Wpp, hipStream_t stream);
 // kernels_mfma_dw.hip: the backward-weight member of the MFMA family
 bool mfma_dw_supports(const syno_plan* p);

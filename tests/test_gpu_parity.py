@@ -852,6 +852,27 @@ def test_pure_views_small(syno, oracle, name, dt):
         assert torch.equal(dX, dX2)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("N,C,Co,H,W", [
+    (1, 32, 32, 3, 5),         # one chunk of pixels and of channels; odd planes
+    (3, 40, 72, 9, 7),         # ragged channels; a row of 7 pixels
+    (2, 64, 96, 6, 12),        # whole runs of four pixels
+    (2, 34, 36, 5, 4),         # rows that the parts leave to the 3-wide window
+    (1, 24, 130, 28, 30),
+])
+def test_strided_gradients_on_a_2x2_window(syno, oracle, N, C, Co, H, W, bf16):
+    """3x3 with stride 2: gradients of the stride-1 convolution of the phase planes with the taps of rows and columns -1 and 0;
+    the same window as a convolution of its own."""
+    t = BF16 if bf16 else F32
+    for d, kernels in ((wl.conv2d(N, C, Co, H, W, 3, 3, t, F32, stride=2), {"mfma_contraction_phases"}),
+                       (wl.conv2d(N, C, Co, H, W, 2, 2, t, F32), {"mfma_contraction_bf16", "mfma_contraction_f32", "generic_index_program"})):
+        xs, ws, _ = oracle.describe(d)
+        os_ = oracle.out_shape(d)
+        st = wl.Stream(65)
+        w = wl._finish(d, xs, ws, os_, st.normal(xs), st.uniform_pm(1.0, ws), st.normal(os_), 1)
+        assert set(run_all(syno, oracle, w, 0, directions=(1, 2))[1:]) <= kernels
+
+
 @pytest.mark.parametrize("kh,kw", [(1, 1), (1, 3), (3, 1), (3, 3), (5, 1)])
 @pytest.mark.parametrize("N,C,Co,H,W", [
     (1, 1, 8, 2, 4),          # one item per row, fewer pixels than a chunk
