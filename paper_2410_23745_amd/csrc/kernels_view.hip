@@ -433,7 +433,7 @@ __global__ __launch_bounds__(kThreads) void view_grad_sum(const double* __restri
 // LANES per combination: 1, or 64 where the combinations alone would leave the chip to wait for memory.  A lane's points
 // go four at a time, so that their loads are under way together: a chain of dependent offsets and loads per point is what
 // bounds the walk.  fp32, one lane -> 64 lanes (us): 57 combinations of 1014 points 527 -> 14, 120 of 684 385 -> 13, 29 of
-// 578 314 -> 13.
+// 578 314 -> 13.  (Weight gradients of views on whole rows do not come here: view_rows.h.)
 template <bool IBF, bool OBF, bool TO_X, int LANES>
 __global__ __launch_bounds__(kThreads) void view_grad_short(const ViewGradParams p, const void* __restrict__ G,
                                                             const void* __restrict__ other, void* __restrict__ target) {
@@ -586,6 +586,39 @@ void launch_dtype(const syno_plan* plan, const ViewParams& p, int V, size_t lds,
   else launch_typed<false, false, SCATTER>(p, V, lds, A, B, out, s);
 }
 
+#include "view_rows.h"
+
+// The record of a weight gradient on whole rows, from the general one: long sums over a view of rows, and shorter ones as long as
+// a workgroup for each is no more than a few rounds of the chip (57 combinations of 1014 points: 14.4 us by waves that first
+// build tables, 4.9 so).
+bool fill_rows_grad(const syno_plan* plan, const ViewGradParams& d, ViewRowsGrad& q) {
+  q = ViewRowsGrad{};
+  ViewRows all;
+  if (d.zero_first || (d.n_splits == 0 && (!shared_walk(d) || d.n_combo > 8192)) || !fill_view_rows(plan, all)) return false;
+  const int splits = std::max(1, d.n_splits);
+  const int last = plan->view.n_axes - 1;
+  q.v = all;
+  q.v.n_outer = 0;
+  int64_t rows = 1;
+  for (int i = 0; i < last; ++i) {
+    bool carry = false;
+    for (int j = 0; j < d.n_carry; ++j) carry |= d.carry_axis[j] == i;
+    if (carry) {
+      const int j = q.n_carry++;
+      q.c_size[j] = all.size[i]; q.c_sg[j] = d.ostride[i]; q.c_sx[j] = all.sx[i]; q.c_sw[j] = all.sw[i];
+    } else {
+      const int j = q.v.n_outer++;
+      q.v.size[j] = all.size[i]; q.v.magic[j] = all.magic[i]; q.v.sx[j] = all.sx[i]; q.sg[j] = d.ostride[i];
+      rows *= all.size[i];
+    }
+  }
+  q.v.rows = (int32_t)rows;
+  q.n_combo = d.n_combo;
+  q.chunk = (int32_t)((rows + splits - 1) / splits);
+  q.n_splits = (int32_t)((rows + q.chunk - 1) / q.chunk);
+  return true;
+}
+
 int run_width(const syno_plan* plan) {
   return plan->view.size[plan->view.n_axes - 1] % 4 == 0 ? 4 : 1;
 }
@@ -618,6 +651,8 @@ bool fill(const syno_plan* plan, ViewParams& p) {
 }  // namespace
 
 // Forward of every separable gather; backward-data where the view is one-to-one (a scatter of the same tables).
+constexpr int kOnRows = 1;      // Launch::variant: the record is that of view_rows.h
+
 bool view_supports(const syno_plan* plan, int which) {
   if (!plan->pure_view) return false;
   if (plan->in_dtype == SYNO_F32 && plan->out_dtype != SYNO_F32) return false;
@@ -636,6 +671,14 @@ void view_configure(syno_plan* plan, int which) {
     static_assert(sizeof(ViewGradParams) <= sizeof(L.params), "parameter record does not fit");
     L.params_ready = fill_grad(plan, which == SYNO_BWD_DATA, d);
     memcpy(L.params, &d, sizeof d);
+    // whole rows where the view has them (the same slices at most, and the same workspace)
+    ViewRowsGrad r;
+    static_assert(sizeof(ViewRowsGrad) <= sizeof(L.params), "parameter record does not fit");
+    L.variant = 0;
+    if (which == SYNO_BWD_WEIGHT && L.params_ready && fill_rows_grad(plan, d, r)) {
+      L.variant = kOnRows;
+      memcpy(L.params, &r, sizeof r);
+    }
     // long sums: slice sums, then the target index of every combination (unused by a single slice)
     L.workspace = d.n_splits > 0 ? grad_partial_bytes(d) + (size_t)d.n_combo * 4 : 0;
     return;
@@ -645,12 +688,25 @@ void view_configure(syno_plan* plan, int which) {
   L.params_ready = fill(plan, p);
   memcpy(L.params, &p, sizeof p);
   L.workspace = 0;
+  ViewRows r;
+  static_assert(sizeof(ViewRows) <= sizeof(L.params), "parameter record does not fit");
+  L.variant = 0;
+  if (L.params_ready && fill_view_rows(plan, r)) {
+    L.variant = kOnRows;
+    memcpy(L.params, &r, sizeof r);
+  }
 }
 
 std::string view_describe(const syno_plan* plan, int which) {
   if (!plan->launch[which].params_ready) return "unconfigured";
-  if (which == SYNO_FWD) return "stream";
-  if (which == SYNO_BWD_DATA && plan->view.one_to_one) return "scatter";
+  const bool on_rows = plan->launch[which].variant == kOnRows;
+  if (which == SYNO_FWD) return on_rows ? "rows stream" : "stream";
+  if (which == SYNO_BWD_DATA && plan->view.one_to_one) return on_rows ? "rows scatter" : "scatter";
+  if (on_rows) {
+    ViewRowsGrad r;
+    memcpy(&r, plan->launch[which].params, sizeof r);
+    return "rows gather targets=" + std::to_string(r.n_combo) + " rows/target=" + std::to_string(r.v.rows) + " slices=" + std::to_string(r.n_splits);
+  }
   ViewGradParams d;
   memcpy(&d, plan->launch[which].params, sizeof d);
   std::string r = "gather targets=" + std::to_string(d.n_combo) + " products/target=" + std::to_string(d.total_rest * d.run);
@@ -663,6 +719,52 @@ std::string view_describe(const syno_plan* plan, int which) {
 syno_status launch_view(const syno_plan* plan, int which, const void* A, const void* B, void* out, void* ws,
                         hipStream_t stream) {
   if (!plan->launch[which].params_ready) return SYNO_ERR_UNSUPPORTED;
+  const bool on_rows = plan->launch[which].variant == kOnRows, ibf_in = plan->in_dtype == SYNO_BF16;
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  if (on_rows && which == SYNO_BWD_WEIGHT) {
+    ViewRowsGrad r;
+    memcpy(&r, plan->launch[which].params, sizeof r);
+    if (!ws && r.n_splits > 1) return SYNO_ERR_WORKSPACE;
+    double* partial = static_cast<double*>(ws);        // (unused by a single slice)
+    int* t_index = ws ? reinterpret_cast<int*>(static_cast<char*>(ws) + (((size_t)r.n_combo * r.n_splits * 8 + 255) & ~(size_t)255)) : nullptr;
+    const dim3 grid((unsigned)(r.n_combo * r.n_splits));
+    auto go = [&](auto bf, auto v_c) {
+      hipLaunchKernelGGL((view_rows_grad<decltype(bf)::value, decltype(v_c)::value>), grid, dim3(kThreads), 0, stream, r, A, B, partial, t_index,
+                         static_cast<float*>(out));
+    };
+    auto by_width = [&](auto bf) {
+      if (view_rows_width(r.v) == 4) go(bf, std::integral_constant<int, 4>{});
+      else go(bf, std::integral_constant<int, 1>{});
+    };
+    if (ibf_in) by_width(yes);
+    else by_width(no);
+    if (r.n_splits > 1)
+      hipLaunchKernelGGL(view_grad_sum<false>, dim3((unsigned)((r.n_combo + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, partial, t_index,
+                         out, r.n_combo, r.n_splits);
+    return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
+  }
+  if (on_rows) {
+    ViewRows r;
+    memcpy(&r, plan->launch[which].params, sizeof r);
+    const int passes = (r.rows + r.R - 1) / r.R, most = plan->opt.view_workgroups > 0 ? plan->opt.view_workgroups : 256 * 8;
+    auto go = [&](auto ibf, auto obf, auto back, auto v_c) {
+      hipLaunchKernelGGL((view_rows<decltype(ibf)::value, decltype(obf)::value, decltype(back)::value, decltype(v_c)::value>),
+                         dim3((unsigned)std::min(passes, most)), dim3(kThreads), 0, stream, r, A, B, out);
+    };
+    auto by_width = [&](auto ibf, auto obf, auto back) {
+      if (view_rows_width(r) == 4) go(ibf, obf, back, std::integral_constant<int, 4>{});
+      else go(ibf, obf, back, std::integral_constant<int, 1>{});
+    };
+    auto by_type = [&](auto back) {
+      if (ibf_in && plan->out_dtype == SYNO_BF16) by_width(yes, yes, back);
+      else if (ibf_in) by_width(yes, no, back);
+      else by_width(no, no, back);
+    };
+    if (which == SYNO_FWD) by_type(no);
+    else by_type(yes);
+    return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
+  }
   if (which == SYNO_BWD_WEIGHT || (which == SYNO_BWD_DATA && !plan->view.one_to_one)) {
     ViewGradParams d;
     memcpy(&d, plan->launch[which].params, sizeof d);
@@ -693,8 +795,6 @@ syno_status launch_view(const syno_plan* plan, int which, const void* A, const v
       }
     };
     if (d.n_splits > 0 && !ws) return SYNO_ERR_WORKSPACE;
-    constexpr std::true_type yes{};
-    constexpr std::false_type no{};
     if (!to_x) ibf ? launch(yes, no, no) : launch(no, no, no);
     else if (obf) launch(yes, yes, yes);
     else ibf ? launch(yes, no, yes) : launch(no, no, yes);

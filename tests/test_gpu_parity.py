@@ -923,6 +923,30 @@ def test_view_gradients_by_sum_length(syno, oracle, points, dt):
     assert want in plan.describe(1), plan.describe(1)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16", "bf16_f32out"])
+@pytest.mark.parametrize("N,C,H,W", [(1, 1, 1, 4), (3, 5, 7, 8), (2, 9, 11, 13), (1, 300, 2, 260), (2, 3, 2, 1100), (40, 6, 33, 5)])
+def test_views_of_whole_rows(syno, oracle, N, C, H, W, dt):
+    """Rows shorter and longer than a pass, pieces of four and of one, the piece that the wrap cuts at each of its places, an
+    outer axis that is transposed and one that is repeated."""
+    i, o = (F32 if dt == "f32" else BF16), (BF16 if dt == "bf16" else F32)
+    descs = [wl.shifted_scale(N, C, H, W, i, o)]
+    for by in (0, 2, W - 3):
+        b = Builder([("h", H), ("n", N), ("c", C), ("w", W)])
+        cx, cw = b.share(2)
+        descs.append(b.finish([1, cx, 0, b.shift(3, by % W)], [cw], i, o))
+    b = Builder([("n", N), ("r", 3), ("c", C), ("w", W)])
+    cx, cw = b.share(2)
+    b.expand(1)
+    descs.append(b.finish([0, cx, b.shift(3, 1)], [cw], i, o))
+    for d in descs:
+        xs, ws, _ = oracle.describe(d)
+        os_ = oracle.out_shape(d)
+        st = wl.Stream(66)
+        w = wl._finish(d, xs, ws, os_, st.normal(xs), st.uniform_pm(2.0, ws), st.normal(os_), 1)
+        assert run_all(syno, oracle, w, 0) == ["bandwidth_view"] * 3
+        assert syno.Plan(d).describe(0).endswith("rows stream")
+
+
 def test_pure_view_full_size(syno, oracle):
     """The shapes the benchmark's detail times (102.8 MB in and out), all three passes, in full against the checker
     (the weight gradients are one sum of 200704 products per channel, and one of 25.7 million)."""
