@@ -106,6 +106,22 @@ syno_status run(const syno_plan* plan, int which, const void* A, const void* B, 
       return syno::launch_mfma(plan, which, A, B, out, ws, stream);
     case syno::KERNEL_MFMA_TRANSPOSED:
       if (L.params_ready) return syno::launch_gemm(plan, which, A, B, out, ws, stream);
+      if (const syno_plan* s = plan->sliced[which]) {
+        // as below, in slices of the reduction: their results go to the workspace's end (rounded up to 256 bytes) and are summed
+        char* sums = static_cast<char*>(ws);
+        const void *image = which == SYNO_FWD ? B : A, *filter = which == SYNO_FWD ? A : B;
+        if (which == SYNO_BWD_DATA) {
+          const syno_status st = syno::launch_transpose_2d(B, ws, plan->w_shape[0], plan->w_shape[1], 4, stream);
+          if (st != SYNO_OK) return st;
+          image = ws;
+          filter = A;
+          sums += ((size_t)plan->w_elems * 4 + 255) & ~(size_t)255;
+        }
+        const syno_status st = syno::launch_mfma(s, which == SYNO_BWD_WEIGHT ? SYNO_BWD_DATA : SYNO_FWD, image, filter, sums, nullptr, stream);
+        if (st != SYNO_OK) return st;
+        const int64_t n = which == SYNO_FWD ? plan->out_elems : which == SYNO_BWD_DATA ? plan->x_elems : plan->w_elems;
+        return syno::launch_sum_results(reinterpret_cast<const float*>(sums), static_cast<float*>(out), n, s->conv.G, stream);
+      }
       // forward: the weight is the image and the input the filter; the gradients keep their operand order
       // (upstream gradient first) and only name the other contraction of the inner plan
       if (which == SYNO_FWD) return run(plan->inner, SYNO_FWD, B, A, out, ws, stream);
@@ -273,6 +289,12 @@ syno_status syno_plan_describe(const syno_plan* plan, int which, char* buf, size
       char inner[400];
       if (plan->launch[which].params_ready) {
         d += " " + syno::gemm_describe(plan, which);
+        break;
+      }
+      if (const syno_plan* s = plan->sliced[which]) {
+        d += std::string(which == SYNO_BWD_DATA ? " as the product G * W^T (transposed copy of W)," : " as") + " 1x1 convolution in " +
+             std::to_string(s->conv.G) + " slices of the reduction, then their sum: mfma_contraction_f32 " +
+             syno::mfma_describe(s, which == SYNO_BWD_WEIGHT ? SYNO_BWD_DATA : SYNO_FWD);
         break;
       }
       if (plan->launch[which].variant == syno::kViaTransposedCopy) {

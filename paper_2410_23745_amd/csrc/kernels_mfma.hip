@@ -673,6 +673,7 @@ void mfma_configure(syno_plan* plan, int which) {
       plan->launch[which].params_ready = true;
       plan->launch[which].variant = -2 - best_cfg;
       plan->launch[which].workspace = 0;
+      plan->launch[which].cycles = cfg_cost;
       return;
     }
   }
@@ -684,6 +685,7 @@ void mfma_configure(syno_plan* plan, int which) {
   memcpy(plan->launch[which].params, &mp, sizeof mp);
   plan->launch[which].params_ready = true;
   plan->launch[which].variant = best_v * 4096 + best_tr;
+  plan->launch[which].cycles = best;
   plan->launch[which].workspace = weight_workspace_bytes(mp, bf) + (mp.ksplit > 1 ? (size_t)mp.ksplit * mp.split_stride * 4 : 0);
 }
 
@@ -717,6 +719,13 @@ std::string mfma_describe(const syno_plan* plan, int which) {
   if (p.ksplit > 1) d += " reduction-splits=" + std::to_string(p.ksplit);
   return d;
 }
+
+namespace {
+void sum_results(const float* parts, float* out, int64_t n, int count, int64_t stride, hipStream_t stream) {
+  const int64_t blocks = std::min<int64_t>(((n + 3) / 4 + 255) / 256, 8 * kNumCU);
+  hipLaunchKernelGGL(sum_split_results, dim3((unsigned)blocks), dim3(256), 0, stream, parts, out, n, count, stride);
+}
+}  // namespace
 
 syno_status launch_mfma(const syno_plan* plan, int which, const void* A, const void* B, void* out, void* ws,
                         hipStream_t stream) {
@@ -781,10 +790,13 @@ syno_status launch_mfma(const syno_plan* plan, int which, const void* A, const v
   }
   if (p.ksplit > 1) {
     const int64_t n = which == SYNO_FWD ? plan->out_elems : plan->x_elems;
-    const int64_t blocks = std::min<int64_t>(((n + 3) / 4 + 255) / 256, 8 * kNumCU);
-    hipLaunchKernelGGL(sum_split_results, dim3((unsigned)blocks), dim3(256), 0, stream, static_cast<const float*>(out),
-                       static_cast<float*>(result), n, p.ksplit, (int64_t)p.split_stride);
+    sum_results(static_cast<const float*>(out), static_cast<float*>(result), n, p.ksplit, p.split_stride, stream);
   }
+  return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
+}
+
+syno_status launch_sum_results(const float* parts, float* out, int64_t n, int count, hipStream_t stream) {
+  sum_results(parts, out, n, count, n, stream);
   return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
 }
 

@@ -120,6 +120,7 @@ struct Launch {
   int32_t coop = 0;           // generic kernel: one workgroup per target (1) or one lane per target (0)
   int32_t variant = 0;        // tile configuration index within the family
   size_t workspace = 0;
+  double cycles = 0;          // estimated duration (convolutions on the matrix cores, forward and backward-data)
   // the family's kernel parameter record, filled when the plan is configured so that a launch only copies it
   alignas(8) unsigned char params[1536] = {};
   bool params_ready = false;
@@ -148,6 +149,9 @@ struct syno_plan {
   // matrix products: dX = G * W^T is a matrix product too; the plan of ITS 1x1 convolution (owned), whose forward
   // contraction runs on a transposed copy of W in the workspace (Launch::variant = kViaTransposedCopy)
   syno_plan* inner_dx = nullptr;
+  // fp32 matrix products whose tiles leave compute units idle: per call, the contraction in conv.G slices of its reduction
+  // (a grouped 1x1 convolution on the same operands, owned), whose results are summed afterwards
+  syno_plan* sliced[3] = {nullptr, nullptr, nullptr};
   // strided convolutions (stride s below the window): the gradients run at stride 1 on the s*s phase planes
   // X[.., s*h'+a, s*w'+b] taken as s*s*C channels.  phase_view_x / phase_view_dx: the space-to-depth view in the input
   // and in the result element type; phase_conv_dw / phase_conv_dx: the stride-1 convolutions whose backward-weight and
@@ -158,7 +162,7 @@ struct syno_plan {
   int32_t phase_window_dw = 0, phase_window_dx = 0;
   int32_t phase_s = 0;           // phases per image axis that take part: s, or 1 for a 1x1 window, which only reads phase
                                  // (0, 0) - the view is then the sub-sampling X[.., s*h', s*w'] itself
-  ~syno_plan() { delete inner; delete inner_dx; delete phase_view_x; delete phase_view_dx; delete phase_conv_dw; delete phase_conv_dx; }
+  ~syno_plan() { for (syno_plan* s : sliced) delete s; delete inner; delete inner_dx; delete phase_view_x; delete phase_view_dx; delete phase_conv_dw; delete phase_conv_dx; }
   bool pure_view = false;
   syno::ViewStream view{};
 };
@@ -223,6 +227,8 @@ std::string rows_describe(const syno_plan* p, int which);
 syno_status launch_rows(const syno_plan* p, int which, const void* A, const void* B, void* out, void* ws, hipStream_t stream);
 // kernels_mfma.hip: dst[c][r] = src[r][c] for a row-major rows x cols matrix of 2- or 4-byte elements
 constexpr int kViaTransposedCopy = 100;
+// kernels_mfma.hip: out[i] = the sum over k < count of parts[k * n + i]
+syno_status launch_sum_results(const float* parts, float* out, int64_t n, int count, hipStream_t stream);
 syno_status launch_transpose_2d(const void* src, void* dst, int64_t rows, int64_t cols, int elem_bytes, hipStream_t stream);
 // kernels_gemm_bf16.hip: contraction `which` of the bf16 product [M x K] * [K x N] on its operands as they lie;
 // gemm_configure fills launch[which].params and sets .workspace

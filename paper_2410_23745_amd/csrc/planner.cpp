@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -864,6 +865,54 @@ int64_t fold_width(int64_t N) {
   return best;
 }
 
+// Contraction `which` of the fp32 product [M x K] * [K x N] in slices of its reduction, where the 1x1 convolution's tiles leave
+// compute units idle: the slices are the groups of a grouped 1x1 convolution on the same operands, on the bf16-parts kernel,
+// and its results are summed afterwards.  Bound by that kernel's chunks (one workgroup to a compute unit): the fewest rounds of
+// 256 workgroups times chunks, against the sums' way to memory and back; both by the estimates that choose the tiles.  Slices
+// are equal and of a multiple of 8 channels, what that kernel takes; more than 32 were not tried.  The sums fit the scratch of the
+// weight gradient's entry point without a workspace.  Whole -> in slices (us, M x K x N): forward 500x2048x1024 78 -> 28,
+// 1000x1536x1536 80 -> 45, 776x3072x3072 175 -> 115; dX 96x768x2304 53 -> 25, 1312x1344x1600 99 -> 75; dW 8192x768x2304 421 ->
+// 194, 8192x256x256 57 -> 27, 624x256x704 32 -> 15.  Of 25 products none got slower; errors against 64 bits are 0.3 to 0.8 of
+// what they were, and those left whole are as they were.
+void slice_product(syno_plan* plan, int which, int64_t M, int64_t K, int64_t N) {
+  Launch& L = plan->launch[which];
+  const syno_plan_options& o = plan->opt;
+  if (L.kernel != KERNEL_MFMA_TRANSPOSED || L.params_ready || plan->in_dtype != SYNO_F32 || plan->out_dtype != SYNO_F32) return;
+  if (o.mfma_splits || o.mfma_rows || o.mfma_variant || o.mfma_taps || (which == SYNO_BWD_DATA && L.variant != kViaTransposedCopy)) return;
+  const bool weight = which == SYNO_BWD_WEIGHT;
+  const syno_plan* whole = which == SYNO_BWD_DATA ? plan->inner_dx : plan->inner;
+  const int contraction = weight ? SYNO_BWD_DATA : SYNO_FWD;
+  const int64_t red = weight ? M : which == SYNO_FWD ? K : N, result = weight ? K * N : which == SYNO_FWD ? M * N : M * K;
+  double best = whole->launch[contraction].cycles;
+  // (the fp32 kernel's weight gradient first writes a transposed copy of X: a launch and its bytes at about 3 TB/s)
+  if (weight && whole->launch[contraction].variant >= 0) best += 10000.0 + 2.0 * M * K * 4.0 / 3.0e12 * 2.4e9;
+  for (int slices = 2; slices <= 32; ++slices) {
+    if (red % (8 * slices) || red / slices < 32 || slices * result * 4 > (int64_t)SYNO_STATIC_SCRATCH_BYTES) continue;
+    const int64_t ws_g = red / slices * (weight ? whole->conv.ws_o : whole->conv.ws_c);
+    if (ws_g >= (1ll << 31)) continue;
+    std::unique_ptr<syno_plan> s(new syno_plan());
+    s->in_dtype = s->out_dtype = SYNO_F32;
+    s->opt = plan->opt;
+    s->conv_like = true;
+    s->conv = whole->conv;
+    s->conv.G = slices;
+    (weight ? s->conv.Og : s->conv.Cg) = (int32_t)(red / slices);
+    s->conv.ws_g = (int32_t)ws_g;
+    s->x_elems = weight ? slices * result : whole->x_elems;
+    s->out_elems = weight ? whole->out_elems : slices * result;
+    if (!mfma_supports(s.get(), contraction)) continue;
+    mfma_configure(s.get(), contraction);
+    if (s->launch[contraction].variant > -2) continue;     // (not on the bf16-parts kernel)
+    // the second launch, and the results written and read back at about 3 TB/s
+    const double cycles = s->launch[contraction].cycles + 10000.0 + (2.0 * slices + 1.0) * result * 4.0 / 3.0e12 * 2.4e9;
+    if (cycles >= best) continue;
+    best = cycles;
+    delete plan->sliced[which];
+    plan->sliced[which] = s.release();
+    L.workspace = (which == SYNO_BWD_DATA ? ((size_t)K * N * 4 + 255) & ~(size_t)255 : 0) + (size_t)slices * result * 4;
+  }
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------
@@ -1456,6 +1505,7 @@ syno_status build_plan(const syno_desc* desc, syno_plan* plan, std::string* why)
     }
     for (int which = 0; which < 3; ++which)
       if (plan->launch[which].kernel == KERNEL_MFMA_TRANSPOSED) plan->launch[which].params_ready = gemm_configure(plan, which, M, K, N);
+    for (int which = 0; which < 3; ++which) slice_product(plan, which, M, K, N);
   }
   return SYNO_OK;
 }
