@@ -691,7 +691,10 @@ void view_configure(syno_plan* plan, int which) {
   ViewRows r;
   static_assert(sizeof(ViewRows) <= sizeof(L.params), "parameter record does not fit");
   L.variant = 0;
-  if (L.params_ready && fill_view_rows(plan, r)) {
+  // (rows of one piece leave three of a thread's four loads to a pass unused: from about 1.5 million of them on, further rounds of the
+  // chip, the general kernel is the faster one.  64x128xHx4 fp32, general and on rows (us): H 128 16.2, 13.1; 196 19.0, 18.5;
+  // 392 29.0, 32.3 to 35.0)
+  if (L.params_ready && fill_view_rows(plan, r) && !(r.L == 4 && r.rows > (3 << 19))) {
     L.variant = kOnRows;
     memcpy(L.params, &r, sizeof r);
   }

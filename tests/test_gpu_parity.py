@@ -947,6 +947,16 @@ def test_views_of_whole_rows(syno, oracle, N, C, H, W, dt):
         assert syno.Plan(d).describe(0).endswith("rows stream")
 
 
+def test_many_views_rows_of_one_piece(syno):
+    """On either side of the line between the two kernels: the same products, rounded once."""
+    for h, kernel in ((96, "rows"), (97, "stream")):
+        p = syno.Plan(wl.shifted_scale(128, 128, h, 4))
+        assert ("rows" in p.describe(0)) == ("rows" in p.describe(1)) == (kernel == "rows")
+        X, W = torch.randn(p.x_shape, device="cuda"), torch.randn(128, device="cuda")
+        assert torch.equal(p.forward(X, W), W.reshape(1, -1, 1, 1) * torch.roll(X, -1, dims=3))
+        assert torch.equal(p.backward_data(X, W), torch.roll(W.reshape(1, -1, 1, 1) * X, 1, dims=3))
+
+
 def test_pure_view_full_size(syno, oracle):
     """The shapes the benchmark's detail times (102.8 MB in and out), all three passes, in full against the checker
     (the weight gradients are one sum of 200704 products per channel, and one of 25.7 million)."""
