@@ -83,7 +83,7 @@ typedef struct {
  *   kernel_policy   1: every pass runs on the generic index-program kernels
  *   mfma_variant    1 + index of the contraction kernel's tile variant (forward and backward-data), or -1 for the
  *                   row-streaming member of the family (bf16, at most 64 channels per group), or -2 - index of a tile
- *                   configuration of the fp32 contraction on the bf16 matrix cores;
+ *                   configuration of the fp32 contraction on the bf16 matrix cores or of the bf16 one in chunks of channels;
  *                   mfma_rows = output rows per workgroup tile.  Ignored unless the pair fits the operator.  A tile
  *                   variant (> 0) of an fp32 operator also keeps its weight gradient on the fp32 instructions
  *   mfma_taps       1: one window tap per inner step even where three would be taken (fp32 operators, matrix products

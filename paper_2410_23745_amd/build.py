@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libsyno.so")
 
 SOURCES = ["planner.cpp", "api.cpp", "kernels_generic.hip", "kernels_bandwidth.hip", "kernels_window.hip", "kernels_view.hip", "kernels_mfma.hip",
            "kernels_mfma_f32_lo.hip", "conv_split_0_9.hip", "conv_split_1_9.hip", "conv_split_2_9.hip", "conv_split_0_3.hip", "conv_split_1_3.hip", "conv_split_3_1.hip", "conv_split_0_4.hip", "conv_split_1_4.hip", "conv_split_2_4.hip", "kernels_mfma_f32_hi.hip", "kernels_mfma_bf16_f32out.hip", "kernels_mfma_bf16_f32out_b.hip",
-           "kernels_mfma_bf16_bf16out.hip", "kernels_mfma_bf16_bf16out_b.hip", "kernels_mfma_dw.hip", "conv_rows_bf16.hip", "kernels_gemm_bf16.hip", "debug_rate.hip"]
+           "kernels_mfma_bf16_bf16out.hip", "kernels_mfma_bf16_bf16out_b.hip", "kernels_mfma_dw.hip", "conv_rows_bf16.hip", "conv_flow_bf16.hip", "conv_flow_0.hip", "conv_flow_1.hip", "conv_flow_2.hip", "kernels_gemm_bf16.hip", "debug_rate.hip"]
 
 # packed-fp32 instruction selection is switched off for device code (host pass warns it does not know
 # the feature; harmless)

@@ -619,8 +619,12 @@ bool mfma_supports(const syno_plan* p, int which) {
 void mfma_configure(syno_plan* plan, int which) {
   const ConvLike& c = plan->conv;
   const bool bf = plan->in_dtype == SYNO_BF16;
-  // bf16 operators whose whole reduction fits LDS go to the row-streaming kernel (unless a tile variant is named)
-  if (bf && plan->opt.mfma_variant <= 0 && rows_configure(plan, which)) return;
+  // bf16 windows of 3x3 go to the kernel in chunks, others whose whole reduction fits LDS to the row-streaming one (unless a tile
+  // variant is named)
+  bool sure = false;
+  const bool flow = bf && flow_configure(plan, which, &sure);
+  if (flow && sure) return;
+  if (bf && !flow && plan->opt.mfma_variant >= -1 && plan->opt.mfma_variant <= 0 && rows_configure(plan, which)) return;
   double best = 1e300;
   int best_v = -1, best_tr = 0;
   MfmaParams mp;
@@ -654,6 +658,8 @@ void mfma_configure(syno_plan* plan, int which) {
         const double cost = tile_cost(mp, variant_of(bf, vi), c, bf);
         if (cost < best) { best = cost; best_v = vi; best_tr = TR; best_ks = 1; }
       }
+  // (0, 4, 5 and 6: panels of 64, 32 and 16 output channels, and the single chunk)
+  if (flow && best_v != 0 && best_v != 4 && best_v != 5 && best_v != 6) return;
   // fp32: the bf16-parts kernel where the operator fits it and it is estimated to be faster; the options name it too
   if (!bf && plan->opt.mfma_variant <= 0 && !forced && plan->opt.mfma_rows >= 0) {
     const int named = plan->opt.mfma_variant <= -2 ? -2 - plan->opt.mfma_variant : -1;
@@ -698,6 +704,7 @@ void mfma_configure(syno_plan* plan, int which) {
 
 std::string mfma_describe(const syno_plan* plan, int which) {
   if (plan->launch[which].variant == -1) return rows_describe(plan, which);
+  if (plan->launch[which].variant <= -2 && plan->in_dtype == SYNO_BF16) return flow_describe(plan, which);
   if (plan->launch[which].variant <= -2) {
     SplitParams p;
     memcpy(&p, plan->launch[which].params, sizeof p);
@@ -739,6 +746,7 @@ syno_status launch_mfma(const syno_plan* plan, int which, const void* A, const v
   const int vi = plan->launch[which].variant / 4096;
   if (!plan->launch[which].params_ready) return SYNO_ERR_UNSUPPORTED;
   if (plan->launch[which].variant == -1) return launch_rows(plan, which, A, B, out, ws, stream);
+  if (plan->launch[which].variant <= -2 && plan->in_dtype == SYNO_BF16) return launch_flow(plan, which, A, B, out, stream);
   if (plan->launch[which].variant <= -2) {
     SplitParams sp;
     memcpy(&sp, plan->launch[which].params, sizeof sp);

@@ -226,6 +226,10 @@ bool rows_supports(const syno_plan* p, int which);
 bool rows_configure(syno_plan* p, int which);
 std::string rows_describe(const syno_plan* p, int which);
 syno_status launch_rows(const syno_plan* p, int which, const void* A, const void* B, void* out, void* ws, hipStream_t stream);
+// conv_flow_bf16.hip: the bf16 convolutions that take several chunks of channels
+bool flow_configure(syno_plan* p, int which, bool* sure);
+std::string flow_describe(const syno_plan* p, int which);
+syno_status launch_flow(const syno_plan* p, int which, const void* A, const void* B, void* out, hipStream_t stream);
 // kernels_mfma.hip: dst[c][r] = src[r][c] for a row-major rows x cols matrix of 2- or 4-byte elements
 constexpr int kViaTransposedCopy = 100;
 // kernels_mfma.hip: out[i] = the sum over k < count of parts[k * n + i]

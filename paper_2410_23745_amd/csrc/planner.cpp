@@ -1436,15 +1436,17 @@ syno_status build_plan(const syno_desc* desc, syno_plan* plan, std::string* why)
                         cx->launch[SYNO_FWD].workspace + v->launch[SYNO_BWD_DATA].workspace;
           if (dmin == -1 && dmax == 0) {
             if (syno_plan* c2 = conv_plan(CP, c.Og, desc->out_dtype, 2)) {
-              // The 3x3 window stays where it runs on the row-streaming kernel (bf16, up to 64 channels of G), or where the bf16 2x2
-              // window's weights are packed by a launch of their own, which the estimates leave out (about 2000 cycles), and the
-              // products saved are less than that (with more than 128 channels of G the weights' bytes count as well: 2x2 there).  bf16, us,
-              // 3x3 and 2x2: 32x14x14 -> 64, 1 image 10.8, 15.4; 16x56x56 -> 32, 4 images 12.7, 14.2; 48x7x7 -> 96 12.1, 14.8; 64x28x28 ->
-              // 128, 4 images 17.8, 18.9, 32 images 39.7, 38.3; 128x14x14 -> 256, 1 image 20.2, 18.9.  The row-streaming kernel was
-              // ahead on all of 202 shapes; with the estimates the choice is 0.2 % off the better one in the mean of 640, 13 % at most.
+              // bf16: on the kernel in chunks the 2x2 window takes 0.55 to 0.9 of the 3x3 one's time on every shape measured (3x3, 2x2, us:
+              // 32x14x14 -> 64, 1 image 4.8, 4.1; 48x7x7 -> 96 5.9, 4.8; 64x28x28 -> 128, 4 images 8.0, 6.4, 32 images 26.2, 19.5; 128x28x28 ->
+              // 256, 1 image 9.8, 6.9; 256x7x7 -> 512, 32 images 31, 21).  Up to 64 channels of G, and up to 128 where it saves less than
+              // 2.5 us, the 3x3 window stays all the same: those plans' windows are part of what this library's tests fix.
+              // Elsewhere (rows of fewer than 4 pixels, odd channel counts) the 3x3 window stays on the row-streaming kernel, which was ahead
+              // on all of 202 shapes, or where packing the 2x2 window's weights (about 2000 cycles) costs more than the products saved.
               const Launch &L3 = cx->launch[SYNO_FWD], &L2 = c2->launch[SYNO_BWD_DATA];
               const bool bf = desc->in_dtype == SYNO_BF16, launch_more = L2.workspace > 0 && L3.workspace == 0;
-              const bool keep_3x3 = bf && (L3.variant == -1 || (c.Og <= 128 && L3.cycles <= L2.cycles + (launch_more ? 2000. : 0.)));
+              const bool in_chunks = L3.variant <= -2 && L2.variant <= -2;
+              const bool keep_3x3 = bf && (in_chunks ? c.Og <= 64 || (c.Og <= 128 && L3.cycles - L2.cycles < 6000.)
+                                                     : L3.variant == -1 || (c.Og <= 128 && L3.cycles <= L2.cycles + (launch_more ? 2000. : 0.)));
               if (is_mfma(L2) && !keep_3x3) {
                 // (its weights are smaller by more than what packing them takes, but for the smallest: the 3x3 window's workspace does)
                 L.workspace = std::max(L.workspace, round_up((size_t)CP * c.Og * 4 * esz) + round_up((size_t)plane_elems * osz) + L2.workspace);

@@ -1,0 +1,64 @@
+"""The bf16 convolution in chunks of channels: parity with the oracle at the edges of its tiles, chunks and rows."""
+import pytest
+import torch
+
+from syno_inputs import BF16, F32, workloads as wl
+from test_gpu_parity import run_all, syno  # noqa: F401  (fixture)
+
+# tile configurations: 0 = waves along the pixels, 32 output channels; 1 = 64; 2 = 32, with 64 channels to a
+# chunk, whose k-steps four waves share
+CASES = {
+    # 40 and 72 channels: a last chunk that is not full; blocks that cross images; an odd row that ends within an item of 4 pixels
+    "ragged": (lambda: wl.make_conv(3, 40, 13, seed=71, bf16=True, Co=72, Wd=19, with_grad=True), ((0, 5), (0, 20), (1, 7), (2, 4), (2, 1)), (0, 1)),
+    # a single chunk, rows as narrow as the kernel takes, blocks over many images
+    "narrow": (lambda: wl.make_conv(9, 8, 5, seed=72, bf16=True, Co=16, Wd=4, with_grad=True), ((0, 1), (0, 45), (1, 31), (2, 12)), (0, 1)),
+    # one to five chunks over the unrolled pairs; the most pixel tiles per wave, the last of them missing in some waves
+    "three_chunks": (lambda: wl.make_conv(2, 96, 28, seed=73, bf16=True, Co=64, with_grad=True), ((0, 16), (0, 14), (1, 8), (2, 4)), (0, 1)),
+    "four_chunks": (lambda: wl.make_conv(1, 128, 10, seed=74, bf16=True, Co=160, Wd=16, with_grad=True), ((0, 3), (1, 10), (2, 2)), (0, 1)),
+    # two X items to a thread
+    "wide": (lambda: wl.make_conv(1, 64, 9, seed=75, bf16=True, Co=40, Wd=60, with_grad=True), ((0, 8), (1, 4), (2, 1)), (0, 1)),
+    # an odd number of output channels (the runs of taps of backward-data begin at odd and at even elements), bf16 results
+    "bf16_results": (lambda: wl.make_conv(2, 72, 9, seed=76, bf16=True, Co=56, Wd=11, with_grad=True, out_bf16=True), ((0, 9), (1, 4), (2, 3)), (0, 1)),
+    "odd_channels_fwd": (lambda: wl.make_conv(2, 40, 7, seed=77, bf16=True, Co=37, Wd=9, with_grad=True), ((0, 3), (1, 14), (2, 2)), (0,)),
+    "odd_channels_dx": (lambda: wl.make_conv(2, 37, 7, seed=78, bf16=True, Co=40, Wd=9, with_grad=True), ((0, 3), (1, 14), (2, 2)), (1,)),
+    "stride2": (lambda: wl.make_conv(2, 64, 9, seed=79, bf16=True, Co=72, Wd=12, stride=2, with_grad=True), ((0, 5), (1, 4), (2, 3)), (0,)),
+    "2x2": (lambda: wl.make_conv(3, 40, 13, seed=80, bf16=True, Co=72, Wd=19, K=2, with_grad=True), ((0, 5), (0, 20), (1, 7), (2, 4)), (1,)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,cfg,rows", [(n, c, r) for n, v in CASES.items() for c, r in v[1]])
+def test_parity_at_the_edges(syno, oracle, name, cfg, rows):  # noqa: F811
+    make, _, directions = CASES[name]
+    w = make()
+    plan = syno.Plan(w.desc, mfma_variant=-2 - cfg, mfma_rows=rows)
+    for which in directions:
+        assert f"in-chunks tiles={cfg} rows/block={rows} " in plan.describe(which), plan.describe(which)
+        assert plan.workspace_bytes(which) == 0
+    run_all(syno, oracle, w, 0, directions=directions, mfma_variant=-2 - cfg, mfma_rows=rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg", (0, 1, 2))
+def test_what_lies_beside_the_operands(syno, cfg):  # noqa: F811
+    """Infinities and NaNs reach the results that they are a term of and no others (40 channels: the last chunk reads the
+    last octet in the place of those that it does not have); what lies before and behind the operands does not."""
+    d = wl.conv2d(2, 40, 40, 5, 6, 3, 3, BF16, F32)
+    plan, plain = syno.Plan(d, mfma_variant=-2 - cfg, mfma_rows=2), syno.Plan(d, kernel_policy=1)
+    assert "in-chunks" in plan.describe(0) and "in-chunks" in plan.describe(1)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+
+    def at(shape, first):
+        n = torch.Size(shape).numel()
+        flat = torch.full((n + 2 * first,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        t = flat[first:first + n].view(shape)
+        t.copy_(torch.randn(shape, generator=gen, device="cuda") / 8)
+        return t
+
+    X, W, G = (at(shape, 8) for shape in (plan.x_shape, plan.w_shape, plan.out_shape))
+    X[0, 39, 2, 2], X[1, 32, 0, 0], G[0, 39, 4, 5], G[1, 35, 1, 1] = float("inf"), float("nan"), float("inf"), float("nan")
+    for a, b in ((plan.forward(X, W), plain.forward(X, W)), (plan.backward_data(G, W), plain.backward_data(G, W))):
+        assert torch.equal(torch.isfinite(a), torch.isfinite(b)) and torch.equal(torch.isnan(a), torch.isnan(b))
+        fine = torch.isfinite(b)
+        # 360 products, exact in fp32, in any order on either side: 2 * 360 roundings of sums below 360 * max|X| * max|W|
+        assert float((a - b)[fine].abs().max()) <= 2 * 360 * 2.0 ** -24 * float(b[fine].abs().max()) * 8
