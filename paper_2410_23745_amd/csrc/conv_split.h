@@ -8,10 +8,12 @@ namespace syno {
 
 struct SplitParams : MfmaParams {
   int32_t x_bytes, w_bytes;          // one LDS buffer of the source rows and of the weights
-  uint32_t m_wp;                     // ceil(2^32 / Wp)
   int32_t x_items;                   // X items (one pixel x 8 channels) per thread
   int32_t octet;                     // pixels between channel octets in LDS: a multiple of 16
   int32_t adjoint;                   // weights of backward-data: taps reversed (selects the instantiation)
+  // for the block's place and its rows: images, row slots of a whole image, tiles of a group, those of an XCD; ceil(2^32 / d), 0 for d = 1
+  int32_t n_images, img_slots, xcd_sm, xcd_sn;
+  uint32_t m_tiles, m_nblocks, m_xcdn, m_sm, m_sn, m_img, m_slots;
 };
 
 namespace {
@@ -21,20 +23,8 @@ constexpr int kSplitChannels = 32;   // channels per chunk = one MFMA k-step per
 constexpr int split_taps(int T) { return T == 9 ? 5 : T; }
 constexpr int split_subs(int T) { return T == 9 ? 2 : 1; }
 
-// slot_source without divisions: first row n0*Ho + h0 of the block given, the images walked one after the other
-__device__ __forceinline__ int split_slot(const SplitParams& p, int R0, int rows, int n, int h, int g, int s) {
-  if (p.h_wrap) return slot_source(p, R0, rows, g, s);
-  for (int left = rows; left > 0; ++n, h = 0) {
-    const int seg = min(p.Ho - h, left), slots = (seg - 1) * p.sh + p.KH;
-    if (s < slots) {
-      const int r = h * p.sh + s - p.ph;
-      return r >= 0 && r < p.Hi ? n * p.xs_n + r * p.Wi : -1;
-    }
-    s -= slots;
-    left -= seg;
-  }
-  return -1;
-}
+// n / d through m = ceil(2^32 / d), 0 for d = 1 (no branch)
+__device__ __forceinline__ int div_by(int n, uint32_t m) { return (int)__umulhi((uint32_t)n, m) + (n & (m ? 0 : -1)); }
 
 // A 16 x 16 tile of results (pixels m0.. of the block, output channels o0.. of the group) with the fp32 matrix instructions,
 // on the operands where they lie: for tiles with results that the parts cannot give, by the wave that stores them.  A tap's
@@ -108,7 +98,6 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   constexpr int CW = BN / 16;                      // channels of a weight item: BN * 32 / CW = 512 items
   constexpr int TS = split_taps(T), NSUB = split_subs(T);
   extern __shared__ __align__(16) unsigned char smem[];
-  int* slot_src = reinterpret_cast<int*>(smem + p.lds_tab_off);
 
   long long* const probe = reinterpret_cast<long long*>(((unsigned long long)p.probe_hi << 32) | p.probe_lo);
   if (probe && threadIdx.x == 0) {
@@ -127,25 +116,25 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     wm = widx >> 2;
     wk = (widx + wm) & 3;
   }
-  int bid = blockIdx.x, nb, mb;
+  // (precomputed reciprocals: until the first load is out a call does nothing else; 5000 cycles with divisions and a walk over the images)
+  const int g = div_by(blockIdx.x, p.m_tiles), local = blockIdx.x - g * (p.n_mblocks * p.n_nblocks);
+  int nb, mb;
   if (p.xcd_m > 0) {
-    const int tiles = p.n_mblocks * p.n_nblocks;
-    const int plane = bid / tiles, local = bid - plane * tiles;
     const int xcd = local & 7, idx = local >> 3;
-    const int sm = p.n_mblocks / p.xcd_m, sn = p.n_nblocks / p.xcd_n;
-    const int xm = xcd / p.xcd_n, xn = xcd - xm * p.xcd_n;
-    const int im = p.xcd_rows_first ? idx % sm : idx / sn;
-    mb = xm * sm + im; nb = xn * sn + (p.xcd_rows_first ? idx / sm : idx - im * sn);
-    bid = plane * p.n_mblocks;
+    const int xm = div_by(xcd, p.m_xcdn), xn = xcd - xm * p.xcd_n;
+    int im, in;
+    if (p.xcd_rows_first) { in = div_by(idx, p.m_sm); im = idx - in * p.xcd_sm; }
+    else { im = div_by(idx, p.m_sn); in = idx - im * p.xcd_sn; }
+    mb = xm * p.xcd_sm + im;
+    nb = xn * p.xcd_sn + in;
   } else {
-    nb = bid % p.n_nblocks; bid /= p.n_nblocks;
-    mb = bid % p.n_mblocks;
+    mb = div_by(local, p.m_nblocks);
+    nb = local - mb * p.n_nblocks;
   }
-  const int g = bid / p.n_mblocks;
   const int R0 = mb * p.TR;
   const int rows = min(p.TR, p.rows_total - R0);
 
-  const int n0 = fdiv(R0, p.m_ho), h0 = R0 - n0 * p.Ho;
+  const int n0 = div_by(R0, p.m_ho), h0 = R0 - n0 * p.Ho;
   // ---- what this thread stages: one weight item, XI X items
   const float* Wg = W + (int64_t)g * p.ws_g + (int64_t)nb * BN * p.ws_o;
   const char* wbase = reinterpret_cast<const char*>(Wg);
@@ -153,17 +142,33 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   const uint32_t w_off = nb * BN + w_o < p.Og ? (uint32_t)(w_o * p.ws_o + w_c * p.ws_c) * 4u : 0u;
   const int w_loff = p.lds_w_off + ((w_c >> 3) * BN + w_o) * 16 + (w_c & 7) * 2;
   const char* xbase = reinterpret_cast<const char*>(X + (int64_t)g * p.Cg * p.xs_c);
+  // slot s of the first image is its row h0 * sh + s - ph; the images after it begin with their first row.  Cyclic rows (a window of
+  // one row): slot s is row R0 + s, moved on
+  const int first_slots = (min(rows, p.Ho - h0) - 1) * p.sh + p.KH;
+  const int shift = p.h_wrap ? (p.h_shift + p.h_shift_g * g) % p.Hi : 0;
   uint32_t x_off[XI];
-  int x_loff[XI], x_cg[XI];
+  int x_loff[XI], x_cg[XI], x_zero[XI];
 #pragma unroll
   for (int k = 0; k < XI; ++k) {
     const int per_cg = p.n_slots * p.Wi, idx = tid + k * NT;
-    const int cg = fdiv(idx, p.m_pcg), rem = idx - cg * per_cg;
-    const int s = fdiv(rem, p.m_vpr), x = rem - s * p.Wi;
-    const int src = idx < 4 * per_cg ? split_slot(p, R0, rows, n0, h0, g, s) : -1;
+    const int cg = div_by(idx, p.m_pcg), rem = idx - cg * per_cg;
+    const int s = div_by(rem, p.m_vpr), x = rem - s * p.Wi;
+    int n, r;
+    if (p.h_wrap) {
+      n = div_by(R0 + s, p.m_ho);
+      r = R0 + s - n * p.Ho + shift;
+      r = r >= p.Hi ? r - p.Hi : r;
+    } else {
+      const int past = s - first_slots, j = div_by(max(past, 0), p.m_img);
+      n = past < 0 ? n0 : n0 + 1 + j;
+      r = past < 0 ? h0 * p.sh + s - p.ph : past - j * p.img_slots - p.ph;
+    }
+    const bool live = cg < 4 && (unsigned)r < (unsigned)p.Hi && n < p.n_images;
+    const int at = (cg * p.octet + s * p.Wp + x + p.pw) * 48;
     x_cg[k] = cg * 8;
-    x_off[k] = src >= 0 ? (uint32_t)(src + x + x_cg[k] * p.xs_c) * 4u : 0u;
-    x_loff[k] = src >= 0 ? (cg * p.octet + s * p.Wp + x + p.pw) * 48 : -1;
+    x_off[k] = live ? (uint32_t)(n * p.xs_n + r * p.Wi + x + x_cg[k] * p.xs_c) * 4u : 0u;
+    x_loff[k] = live ? at : -1;
+    x_zero[k] = cg < 4 && !live ? at : -1;       // a row outside the image: zeroed once and never written
   }
 
   // values on their way from memory: those staged next, and (xn, wn) those after them where a stage is shorter than a
@@ -271,19 +276,28 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   fetch_w(0, all, wr);
   load_x(0, xr);
   if constexpr (WN2 && NSUB == 2) fetch_w(1, all, wn2);
-  // while the first loads travel: what the window's padding reads is zeroed once and never written (slot edges, rows outside
-  // the image)
-  for (int s = tid; s < p.n_slots; s += NT) slot_src[s] = split_slot(p, R0, rows, n0, h0, g, s);
-  __syncthreads();
-  for (int i = tid; i < 4 * p.n_slots * p.Wp; i += NT) {
-    const int r = fdiv(i, p.m_wp), x = i - r * p.Wp, cg = r / p.n_slots, s = r - cg * p.n_slots;
-    if (slot_src[s] >= 0 && x >= p.pw && x < p.pw + p.Wi) continue;
-    unsigned char* d = smem + (cg * p.octet + s * p.Wp + x) * 48;
+  // while the first loads travel: what the window's padding reads is zeroed once and never written (rows outside the image, the
+  // columns on either side of the rows)
+  constexpr int XB = MODE == 2 ? 2 : 1;
 #pragma unroll
-    for (int b = 0; b < (MODE == 2 ? 2 : 1); ++b)
+  for (int k = 0; k < XI; ++k)
+    if (x_zero[k] >= 0) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) reinterpret_cast<uint4*>(d + b * p.x_bytes)[k] = make_uint4(0, 0, 0, 0);
-  }
+      for (int b = 0; b < XB; ++b)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) reinterpret_cast<uint4*>(smem + x_zero[k] + b * p.x_bytes)[j] = make_uint4(0, 0, 0, 0);
+    }
+  if (p.KW > 1)
+    for (int i = tid; i < 4 * p.n_slots; i += NT) {
+      const int cg = div_by(i, p.m_slots), s = i - cg * p.n_slots;
+      for (int e = 0; e < p.KW - 1; ++e) {
+        unsigned char* d = smem + (cg * p.octet + s * p.Wp + (e < p.pw ? e : p.Wi + e)) * 48;
+#pragma unroll
+        for (int b = 0; b < XB; ++b)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) reinterpret_cast<uint4*>(d + b * p.x_bytes)[j] = make_uint4(0, 0, 0, 0);
+      }
+    }
   // ---- per-lane operand bases
   const int block_px = rows * p.Wo;
   const int MT = (block_px + 15) >> 4;
@@ -295,8 +309,10 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   for (int t = 0; t < NTL; ++t) {
     int m = (my_first + t) * 16 + (lane & 15);
     if (t >= my_tiles || m >= block_px) m = 0;
-    const int i = fdiv(m, p.m_wo), w = m - i * p.Wo;
-    a_base[t] = (slot_of_row(p, R0, i) * p.Wp + w * p.sw + (lane >> 4) * p.octet) * 48;
+    const int i = div_by(m, p.m_wo), w = m - i * p.Wo;
+    // (every image before the row's adds KH - sh slots)
+    const int slot = p.h_wrap ? i : i * p.sh + (p.KH - p.sh) * div_by(h0 + i, p.m_ho);
+    a_base[t] = (slot * p.Wp + w * p.sw + (lane >> 4) * p.octet) * 48;
   }
   const int b_base = p.lds_w_off + ((lane >> 4) * BN + wn * TN * 16 + (lane & 15)) * 16;
 

@@ -501,20 +501,26 @@ bool fill_split(const syno_plan* plan, int which, int cfg, int TR, SplitParams& 
   const int64_t per_cg = (int64_t)p.n_slots * c.Wi;
   if (4 * per_cg > 4 * 512) return false;
   p.x_items = (int)((4 * per_cg + 511) / 512);
-  p.m_wp = (uint32_t)(((1ull << 32) + p.Wp - 1) / p.Wp);
   p.octet = (p.n_slots * p.Wp + 15) & ~15;
   p.x_bytes = 4 * p.octet * 48;
   p.w_bytes = split_taps(T) * kPlanes * 4 * p.BN * 16;
   p.lds_w_off = (v.mode == 2 ? 2 : 1) * p.x_bytes;
-  p.lds_tab_off = p.lds_w_off + (v.mode >= 1 ? 2 : 1) * p.w_bytes;
-  p.lds_bytes = p.lds_tab_off + ((p.n_slots * 4 + 15) & ~15);
+  p.lds_bytes = p.lds_w_off + (v.mode >= 1 ? 2 : 1) * p.w_bytes;
   if (v.WK > 1) p.lds_bytes = std::max<int>(p.lds_bytes, 8 * (int)((MT + v.WM - 1) / v.WM) * v.TN * 1024);
   if (p.lds_bytes > kMaxLdsBytes) return false;
-  auto magic = [](int64_t d) { return (uint32_t)(((1ull << 32) + d - 1) / std::max<int64_t>(d, 1)); };
-  if (2048 * per_cg >= (1ll << 32) || (int64_t)p.rows_total * c.Ho >= (1ll << 32)) return false;
+  auto magic = [](int64_t d) { return d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); };
+  const int64_t tiles = (int64_t)p.n_mblocks * p.n_nblocks;
+  if (2048 * per_cg >= (1ll << 32) || (int64_t)p.rows_total * c.Ho >= (1ll << 32) || c.G * tiles * tiles >= (1ll << 32)) return false;
   p.m_wo = magic(c.Wo); p.m_ho = magic(c.Ho); p.m_vpr = magic(c.Wi); p.m_pcg = magic(per_cg);
+  p.n_images = c.N;
+  p.img_slots = (c.Ho - 1) * p.sh + c.KH;
+  p.m_tiles = magic(tiles); p.m_nblocks = magic(p.n_nblocks); p.m_img = magic(p.img_slots); p.m_slots = magic(p.n_slots);
   p.ksplit = 1;
   deal_to_xcds(c, false, p);
+  if (p.xcd_m > 0) {
+    p.xcd_sm = p.n_mblocks / p.xcd_m; p.xcd_sn = p.n_nblocks / p.xcd_n;
+    p.m_xcdn = magic(p.xcd_n); p.m_sm = magic(p.xcd_sm); p.m_sn = magic(p.xcd_sn);
+  }
   // (tiles that are all resident at once come back to neither operand: those that start together share the larger one)
   if (p.xcd_m > 0 && (p.n_mblocks / p.xcd_m) * (p.n_nblocks / p.xcd_n) <= 32)
     p.xcd_rows_first = (double)p.Og * p.Cg * T > (double)c.N * p.Cg * c.Hi * c.Wi;
