@@ -167,17 +167,28 @@ __global__ __launch_bounds__(512) void dw_split(const DwParams p, const float* _
   const int ring = p.stream_ring;
   auto wrap = [&](int pos) { return pos >= ring ? pos - ring : pos; };
 
-  // ---- the first chunk's G and its whole window of X
+  // ---- the first chunk's G and its whole window of X: all of a round's requests before anything is waited for (one by one
+  // they cost a memory round trip each, 4 at 56x56)
   int base = 0;                        // ring position of the current chunk's first pixel
   {
+    constexpr int IN = 3;              // items of X on their way at a time (a wave's 64 exist or do not: their number is a multiple of 64)
+    const int groups = (kStreamChunk + 2 * B) / XE, all = CX * groups;
     request(gbase, g_at, gr);
-    lay(g_put, gr);
-    const int groups = (kStreamChunk + 2 * B) / XE;
-    for (int i = tid; i < CX * groups; i += NT) {
-      const int ch = i / groups, q = i - ch * groups, pos = q * XE - B;
-      float v[XE];
-      request(xbase, place(chunk_begin * kStreamChunk + pos, (uint32_t)min(ch, c_last) * (uint32_t)p.plane * 4u, p.xs_n), v);
-      lay(xl + ch * x_row + bytes_of(pos < 0 ? pos + ring : pos), v);
+    for (int i0 = tid; i0 < all; i0 += IN * NT) {
+      float v[IN][XE];
+      int put[IN];
+#pragma unroll
+      for (int e = 0; e < IN; ++e) {
+        const int i = i0 + e * NT;
+        if (i >= all) break;
+        const int ch = (int)__umulhi((uint32_t)i, p.m_groups), q = i - ch * groups, pos = q * XE - B;
+        put[e] = ch * x_row + bytes_of(pos < 0 ? pos + ring : pos);
+        request(xbase, place(chunk_begin * kStreamChunk + pos, (uint32_t)min(ch, c_last) * (uint32_t)p.plane * 4u, p.xs_n), v[e]);
+      }
+      if (i0 == tid) lay(g_put, gr);
+#pragma unroll
+      for (int e = 0; e < IN; ++e)
+        if (i0 + e * NT < all) lay(xl + put[e], v[e]);
     }
     fetch();
   }

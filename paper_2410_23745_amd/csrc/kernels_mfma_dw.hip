@@ -63,6 +63,7 @@ struct DwParams {
   int32_t parts;                       // that kernel takes this plan
   int32_t stream_reach, stream_ring;   // pixels of X read beyond a chunk on either side; pixels in the ring
   uint32_t m_pitch, m_rows;            // ceil(2^32/d) for d = pitch and d = the rows of an image in the stream
+  uint32_t m_groups;                   // the same for the items of an X channel in a chunk with its window (dw_split.h)
   // bf16 (dw_stream_bf16.h): channels of a workgroup's tile, whose slots are (output-channel tile, input-channel tile, tap)
   int32_t stream, tile_o, tile_c;
   int32_t narrow;                      // rows of the image have 1, 2 or 3 pixels, and the record's H x W are 8-pixel items of them (else 0)
@@ -930,6 +931,7 @@ bool fill_dw_split(const syno_plan* plan, DwParams& p) {
   // (exact quotients, also for the positions that are requested past the end)
   if ((stream + 4096) * std::max(p.pitch, c.Ho + 1) >= (1ll << 32)) return false;
   p.m_pitch = magic_of(p.pitch); p.m_rows = magic_of(c.Ho + 1);
+  p.m_groups = magic_of((kStreamChunk + 2 * p.stream_reach) / (p.ct == 1 ? 4 : 8));
   p.n_chunks = (int)((stream + kStreamChunk - 1) / kStreamChunk);
   if (p.n_chunks < 2) return false;
   p.n_oblk = (c.Og + 63) / 64;
