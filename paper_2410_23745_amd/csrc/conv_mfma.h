@@ -44,6 +44,13 @@ struct MfmaParams {
   int32_t xcd_m, xcd_n, xcd_rows_first;
 };
 
+// What the fp32 kernels divide by (their own record: 40 bytes more of arguments made the bf16 kernels of this file 1 to 2 % slower)
+struct MfmaPlace : MfmaParams {
+  // for the block's place and its rows: images, row slots of a whole image, tiles of an XCD's rectangle; ceil(2^32 / d), 0 for d = 1
+  int32_t n_images, img_slots, xcd_sm, xcd_sn;
+  uint32_t m_tiles, m_nblocks, m_xcdn, m_sm, m_sn, m_img;
+};
+
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -60,6 +67,42 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
   u += 0x7fffu + ((u >> 16) & 1u);
   return (uint16_t)(u >> 16);
+}
+
+// The same without a branch
+__device__ __forceinline__ int div_by(int n, uint32_t m) { return (int)__umulhi((uint32_t)n, m) + (n & (m ? 0 : -1)); }
+
+// The tile of block `bid`: `plane` (group, and split), row of tiles, panel of output channels
+__device__ __forceinline__ void tile_of_block(const MfmaPlace& p, int bid, int& plane, int& mb, int& nb) {
+  // (a plane that is dealt to the XCDs holds a multiple of 8 tiles, so the low three bits of the place in it name the XCD)
+  plane = div_by(bid, p.m_tiles);
+  const int local = bid - plane * (p.n_mblocks * p.n_nblocks);
+  if (p.xcd_m > 0) {
+    const int xcd = local & 7, idx = local >> 3;
+    const int xm = div_by(xcd, p.m_xcdn), xn = xcd - xm * p.xcd_n;
+    int im, in;
+    if (p.xcd_rows_first) { in = div_by(idx, p.m_sm); im = idx - in * p.xcd_sm; }
+    else { im = div_by(idx, p.m_sn); in = idx - im * p.xcd_sn; }
+    mb = xm * p.xcd_sm + im;
+    nb = xn * p.xcd_sn + in;
+  } else {
+    mb = div_by(local, p.m_nblocks);
+    nb = local - mb * p.n_nblocks;
+  }
+}
+
+// Image n and row r that slot s of a block holds (first output row h0 of image n0, `first_slots` slots of that image); `shift`: of
+// cyclic rows.  The images after the first begin with their first row.  Whether there is such a row is the caller's to see.
+__device__ __forceinline__ void row_of_slot(const MfmaPlace& p, int R0, int n0, int h0, int first_slots, int shift, int s, int& n, int& r) {
+  if (p.h_wrap) {
+    n = div_by(R0 + s, p.m_ho);
+    r = R0 + s - n * p.Ho + shift;
+    r = r >= p.Hi ? r - p.Hi : r;
+  } else {
+    const int past = s - first_slots, j = div_by(max(past, 0), p.m_img);
+    n = past < 0 ? n0 : n0 + 1 + j;
+    r = past < 0 ? h0 * p.sh + s - p.ph : past - j * p.img_slots - p.ph;
+  }
 }
 
 // Source of each row slot: element offset of the input row inside the tensor, or -1 when the slot
@@ -118,7 +161,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 //      per-SIMD share of the output is only a few MFMA tiles: a wave then still issues TM*TN MFMAs per
 //      LDS round trip); their accumulators are added through LDS at the end.
 template <bool BF, bool WNAT, int WM, int WN, int WK, int TM, int TN, int XI, int WI, bool ONE, int KCB, int U, int WF, bool OUTBF>
-__global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const MfmaParams p, const void* __restrict__ Xv,
+__global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditional_t<BF, MfmaParams, MfmaPlace> p, const void* __restrict__ Xv,
                                                          const void* __restrict__ Wv, void* __restrict__ out) {
   constexpr int NT = WM * WN * WK * 64;
   constexpr int BN = WN * TN * 16;
@@ -131,7 +174,6 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const MfmaParams p,
   using WReg = std::conditional_t<W16, uint4, float>;
   extern __shared__ __align__(16) unsigned char smem[];
   float4* xl = reinterpret_cast<float4*>(smem);
-  int* slot_src = reinterpret_cast<int*>(smem + p.lds_tab_off);
 
   long long* const probe = reinterpret_cast<long long*>(((unsigned long long)p.probe_hi << 32) | p.probe_lo);
   if (probe && threadIdx.x == 0) {
@@ -145,29 +187,39 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const MfmaParams p,
   // wave widx runs on SIMD widx % 4: rotate the wave rows so that the fuller ones spread over the SIMDs,
   // also among the waves that split K
   const int wm = (wtile + wn + ((wk * WM * WN) >> 2)) % WM;
-  int bid = blockIdx.x, nb, mb;
-  if (p.xcd_m > 0) {
-    // (a plane holds a multiple of 8 tiles, so the low three bits of its local index name the XCD)
-    const int tiles = p.n_mblocks * p.n_nblocks;
-    const int plane = bid / tiles, local = bid - plane * tiles;
-    const int xcd = local & 7, idx = local >> 3;
-    const int sm = p.n_mblocks / p.xcd_m, sn = p.n_nblocks / p.xcd_n;
-    const int xm = xcd / p.xcd_n, xn = xcd - xm * p.xcd_n;
-    const int im = p.xcd_rows_first ? idx % sm : idx / sn;
-    mb = xm * sm + im; nb = xn * sn + (p.xcd_rows_first ? idx / sm : idx - im * sn);
-    bid = plane * p.n_mblocks;
+  // fp32: reciprocals and a closed form for the rows (with divisions, a walk over the images and a table of rows 5000 cycles go by before
+  // the first load; calls take 1 / 1.04 to 1 / 1.06 of the time in the mean).  bf16, where 9 taps of packed weights got 13 % slower with it: the table
+  int g, mb, nb, ksp = 0;
+  if constexpr (!BF) {
+    tile_of_block(p, blockIdx.x, g, mb, nb);
   } else {
-    nb = bid % p.n_nblocks; bid /= p.n_nblocks;
-    mb = bid % p.n_mblocks;
+    int bid = blockIdx.x;
+    if (p.xcd_m > 0) {
+      const int tiles = p.n_mblocks * p.n_nblocks;
+      const int plane = bid / tiles, local = bid - plane * tiles;
+      const int xcd = local & 7, idx = local >> 3;
+      const int sm = p.n_mblocks / p.xcd_m, sn = p.n_nblocks / p.xcd_n;
+      const int xm = xcd / p.xcd_n, xn = xcd - xm * p.xcd_n;
+      const int im = p.xcd_rows_first ? idx % sm : idx / sn;
+      mb = xm * sm + im; nb = xn * sn + (p.xcd_rows_first ? idx / sm : idx - im * sn);
+      bid = plane * p.n_mblocks;
+    } else {
+      nb = bid % p.n_nblocks; bid /= p.n_nblocks;
+      mb = bid % p.n_mblocks;
+    }
+    g = bid / p.n_mblocks;
   }
-  int g = bid / p.n_mblocks, ksp = 0;
   if (p.ksplit > 1) { ksp = g / p.G; g -= ksp * p.G; }
   const int R0 = mb * p.TR;
   const int rows = min(p.TR, p.rows_total - R0);
   const int KHW = p.KH * p.KW;
-
-  for (int s = tid; s < p.n_slots; s += NT) slot_src[s] = slot_source(p, R0, rows, g, s);
-  __syncthreads();
+  const int n0 = BF ? 0 : div_by(R0, p.m_ho), h0 = R0 - n0 * p.Ho;
+  const int first_slots = BF || p.h_wrap ? 0 : (min(rows, p.Ho - h0) - 1) * p.sh + p.KH, shift = !BF && p.h_wrap ? (p.h_shift + p.h_shift_g * g) % p.Hi : 0;
+  int* const slot_src = reinterpret_cast<int*>(smem + p.lds_tab_off);
+  if constexpr (BF) {
+    for (int s = tid; s < p.n_slots; s += NT) slot_src[s] = slot_source(p, R0, rows, g, s);
+    __syncthreads();
+  }
 
   // ---- loop-invariant descriptors of what this thread stages per chunk
   const XT* Xg = reinterpret_cast<const XT*>(Xv) + (int64_t)g * p.Cg * p.xs_c;
@@ -180,10 +232,17 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const MfmaParams p,
 #pragma unroll
     for (int k = 0; k < XI; ++k) {
       const int idx = tid + k * NT;
-      const int cg = fdiv(idx, p.m_pcg), rem = idx - cg * per_cg;
-      const int s = fdiv(rem, p.m_vpr), x = min((rem - s * p.vpr) * p.vx, p.Wi - p.vx);
-      const int src = idx < total ? slot_src[s] : -1;
-      x_goff[k] = src >= 0 ? src + x + cg * CI * p.xs_c : -1;
+      const int cg = BF ? fdiv(idx, p.m_pcg) : div_by(idx, p.m_pcg), rem = idx - cg * per_cg;
+      const int s = BF ? fdiv(rem, p.m_vpr) : div_by(rem, p.m_vpr), x = min((rem - s * p.vpr) * p.vx, p.Wi - p.vx);
+      if constexpr (BF) {
+        const int src = idx < total ? slot_src[s] : -1;
+        x_goff[k] = src >= 0 ? src + x + cg * CI * p.xs_c : -1;
+      } else {
+        int n, r;
+        row_of_slot(p, R0, n0, h0, first_slots, shift, s, n, r);
+        const bool live = idx < total && (unsigned)r < (unsigned)p.Hi && n < p.n_images && (s < rows || !p.h_wrap);
+        x_goff[k] = live ? n * p.xs_n + r * p.Wi + x + cg * CI * p.xs_c : -1;
+      }
       x_loff[k] = (cg * p.n_slots + s) * p.Wp + x + p.pw;
       x_cg[k] = cg * CI;
     }
@@ -293,21 +352,27 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const MfmaParams p,
   const int my_tiles = tiles_base + (wm < tiles_extra ? 1 : 0);
   const int my_first = wm * tiles_base + min(wm, tiles_extra);
   const int cg_stride = p.n_slots * p.Wp;          // 16-byte units between channel groups
-  int a_base[TM];                                   // LDS byte address of the lane's A operand at tap (0,0), channel group 0
+  // (fp32: worked out while the first loads travel)
+  auto operand_bases = [&](auto& a, auto& b) {
+    constexpr int N = sizeof(a) / sizeof(int);
 #pragma unroll
-  for (int t = 0; t < TM; ++t) {
-    int m = (my_first + t) * 16 + (lane & 15);
-    if (t >= my_tiles || m >= block_px) m = 0;
-    const int i = fdiv(m, p.m_wo), w = m - i * p.Wo;
-    const int px = slot_of_row(p, R0, i) * p.Wp + w * p.sw;
-    a_base[t] = BF ? (px + (lane >> 4) * cg_stride) * 16 : px * 16 + (lane >> 4) * 4;
-  }
-  int b_base[TN];                                   // same for the B operand (weights)
+    for (int t = 0; t < N; ++t) {
+      int m = (my_first + t) * 16 + (lane & 15);
+      if (t >= my_tiles || m >= block_px) m = 0;
+      const int i = BF ? fdiv(m, p.m_wo) : div_by(m, p.m_wo), w = m - i * p.Wo;
+      // (every image before the row's adds KH - sh)
+      const int slot = BF ? slot_of_row(p, R0, i) : p.h_wrap ? i : i * p.sh + (p.KH - p.sh) * div_by(h0 + i, p.m_ho);
+      const int px = slot * p.Wp + w * p.sw;
+      a[t] = BF ? (px + (lane >> 4) * cg_stride) * 16 : px * 16 + (lane >> 4) * 4;       // LDS byte address of the lane's A operand at tap (0,0), channel group 0
+    }
 #pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    const int ol = (wn * TN + u) * 16 + (lane & 15);
-    b_base[u] = p.lds_w_off + (BF ? (ol * p.w_row + (lane >> 4) * 8) * 2 : (ol * p.w_row + (lane >> 4) * KHW) * 4);
-  }
+    for (int u = 0; u < TN; ++u) {                                                      // the same for the B operand (weights)
+      const int ol = (wn * TN + u) * 16 + (lane & 15);
+      b[u] = p.lds_w_off + (BF ? (ol * p.w_row + (lane >> 4) * 8) * 2 : (ol * p.w_row + (lane >> 4) * KHW) * 4);
+    }
+  };
+  int early_a[TM], early_b[TN];
+  if constexpr (BF) operand_bases(early_a, early_b);
 
   // Everything from here on is instantiated once per possible tile count of a wave, so that the
   // accumulators and fragments of a wave with fewer row tiles do not occupy registers and the MFMA
@@ -559,6 +624,10 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const MfmaParams p,
     const int n16 = p.cgrps * p.n_slots * p.Wp;
     for (int i = tid; i < n16; i += NT) xl[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  int late_a[NA], late_b[TN];
+  if constexpr (!BF) operand_bases(late_a, late_b);
+  auto& a_base = [&]() -> auto& { if constexpr (BF) return early_a; else return late_a; }();
+  auto& b_base = [&]() -> auto& { if constexpr (BF) return early_b; else return late_b; }();
   if constexpr (BF && WF < 0 && ONE) {
     // The same for the backward-data adjoint: the B operand's rows are the forward input channels and its
     // reduction runs over the forward output channels, taps reversed.  A thread again loads 8 channels x
@@ -842,7 +911,7 @@ constexpr Variant kBf16Variants[kNumBf16Variants] = {
     {2, 1, 4, 4, 2, 2, 10, 128, false}, {4, 2, 1, 4, 4, 1, 3, 64, false}};
 
 template <bool BF, int VI, int U, int WF, bool OUTBF>
-void launch_variant(const MfmaParams& p, const void* X, const void* W, void* out, hipStream_t s) {
+void launch_variant(const std::conditional_t<BF, MfmaParams, MfmaPlace>& p, const void* X, const void* W, void* out, hipStream_t s) {
   constexpr Variant v = BF ? kBf16Variants[VI % kNumBf16Variants] : kF32Variants[VI % kNumF32Variants];
   const int grid = p.n_mblocks * p.n_nblocks * p.G * p.ksplit;
   auto kernel = conv_mfma<BF, v.wnat, v.WM, v.WN, v.WK, v.TM, v.TN, v.XI, v.WI, v.one, (BF ? v.KC : 0), U, WF, OUTBF>;
@@ -855,8 +924,8 @@ void launch_variant(const MfmaParams& p, const void* X, const void* W, void* out
 }  // namespace
 
 // Launchers of the instantiated variants; each lives in a translation unit of its own.
-void launch_mfma_f32_lo(int vi, const MfmaParams& p, const void* X, const void* W, void* out, hipStream_t s);    // variants 0-3
-void launch_mfma_f32_hi(int vi, const MfmaParams& p, const void* X, const void* W, void* out, hipStream_t s);    // variants 4-13
+void launch_mfma_f32_lo(int vi, const MfmaPlace& p, const void* X, const void* W, void* out, hipStream_t s);    // variants 0-3
+void launch_mfma_f32_hi(int vi, const MfmaPlace& p, const void* X, const void* W, void* out, hipStream_t s);    // variants 4-13
 void launch_mfma_bf16_f32out(int vi, const MfmaParams& p, const void* X, const void* W, void* out, hipStream_t s);
 void launch_mfma_bf16_bf16out(int vi, const MfmaParams& p, const void* X, const void* W, void* out, hipStream_t s);
 

@@ -6,14 +6,12 @@
 
 namespace syno {
 
-struct SplitParams : MfmaParams {
+struct SplitParams : MfmaPlace {
   int32_t x_bytes, w_bytes;          // one LDS buffer of the source rows and of the weights
   int32_t x_items;                   // X items (one pixel x 8 channels) per thread
   int32_t octet;                     // pixels between channel octets in LDS: a multiple of 16
   int32_t adjoint;                   // weights of backward-data: taps reversed (selects the instantiation)
-  // for the block's place and its rows: images, row slots of a whole image, tiles of a group, those of an XCD; ceil(2^32 / d), 0 for d = 1
-  int32_t n_images, img_slots, xcd_sm, xcd_sn;
-  uint32_t m_tiles, m_nblocks, m_xcdn, m_sm, m_sn, m_img, m_slots;
+  uint32_t m_slots;                  // ceil(2^32 / n_slots), 0 for 1
 };
 
 namespace {
@@ -22,9 +20,6 @@ constexpr int kSplitChannels = 32;   // channels per chunk = one MFMA k-step per
 // taps whose weights lie in LDS at a time: the nine of a 3x3 window go in as five and four
 constexpr int split_taps(int T) { return T == 9 ? 5 : T; }
 constexpr int split_subs(int T) { return T == 9 ? 2 : 1; }
-
-// n / d through m = ceil(2^32 / d), 0 for d = 1 (no branch)
-__device__ __forceinline__ int div_by(int n, uint32_t m) { return (int)__umulhi((uint32_t)n, m) + (n & (m ? 0 : -1)); }
 
 // A 16 x 16 tile of results (pixels m0.. of the block, output channels o0.. of the group) with the fp32 matrix instructions,
 // on the operands where they lie: for tiles with results that the parts cannot give, by the wave that stores them.  A tap's
@@ -116,21 +111,9 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     wm = widx >> 2;
     wk = (widx + wm) & 3;
   }
-  // (precomputed reciprocals: until the first load is out a call does nothing else; 5000 cycles with divisions and a walk over the images)
-  const int g = div_by(blockIdx.x, p.m_tiles), local = blockIdx.x - g * (p.n_mblocks * p.n_nblocks);
-  int nb, mb;
-  if (p.xcd_m > 0) {
-    const int xcd = local & 7, idx = local >> 3;
-    const int xm = div_by(xcd, p.m_xcdn), xn = xcd - xm * p.xcd_n;
-    int im, in;
-    if (p.xcd_rows_first) { in = div_by(idx, p.m_sm); im = idx - in * p.xcd_sm; }
-    else { im = div_by(idx, p.m_sn); in = idx - im * p.xcd_sn; }
-    mb = xm * p.xcd_sm + im;
-    nb = xn * p.xcd_sn + in;
-  } else {
-    mb = div_by(local, p.m_nblocks);
-    nb = local - mb * p.n_nblocks;
-  }
+  // (until the first load is out a call does nothing else: 5000 cycles with divisions and a walk over the images)
+  int g, mb, nb;
+  tile_of_block(p, blockIdx.x, g, mb, nb);
   const int R0 = mb * p.TR;
   const int rows = min(p.TR, p.rows_total - R0);
 
@@ -142,8 +125,6 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   const uint32_t w_off = nb * BN + w_o < p.Og ? (uint32_t)(w_o * p.ws_o + w_c * p.ws_c) * 4u : 0u;
   const int w_loff = p.lds_w_off + ((w_c >> 3) * BN + w_o) * 16 + (w_c & 7) * 2;
   const char* xbase = reinterpret_cast<const char*>(X + (int64_t)g * p.Cg * p.xs_c);
-  // slot s of the first image is its row h0 * sh + s - ph; the images after it begin with their first row.  Cyclic rows (a window of
-  // one row): slot s is row R0 + s, moved on
   const int first_slots = (min(rows, p.Ho - h0) - 1) * p.sh + p.KH;
   const int shift = p.h_wrap ? (p.h_shift + p.h_shift_g * g) % p.Hi : 0;
   uint32_t x_off[XI];
@@ -154,15 +135,7 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     const int cg = div_by(idx, p.m_pcg), rem = idx - cg * per_cg;
     const int s = div_by(rem, p.m_vpr), x = rem - s * p.Wi;
     int n, r;
-    if (p.h_wrap) {
-      n = div_by(R0 + s, p.m_ho);
-      r = R0 + s - n * p.Ho + shift;
-      r = r >= p.Hi ? r - p.Hi : r;
-    } else {
-      const int past = s - first_slots, j = div_by(max(past, 0), p.m_img);
-      n = past < 0 ? n0 : n0 + 1 + j;
-      r = past < 0 ? h0 * p.sh + s - p.ph : past - j * p.img_slots - p.ph;
-    }
+    row_of_slot(p, R0, n0, h0, first_slots, shift, s, n, r);
     const bool live = cg < 4 && (unsigned)r < (unsigned)p.Hi && n < p.n_images;
     const int at = (cg * p.octet + s * p.Wp + x + p.pw) * 48;
     x_cg[k] = cg * 8;

@@ -323,6 +323,9 @@ void fill_problem(const syno_plan* plan, int which, MfmaParams& p) {
   }
 }
 
+// ceil(2^32 / d), 0 for d = 1
+uint32_t reciprocal(int64_t d) { return d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); }
+
 // The tiles of one (group, split) plane dealt to the 8 XCDs.
 // Which tiles share an XCD's L2: with the tiles of a plane dealt as xcd_m x xcd_n rectangles the XCDs together fetch
 // the source xcd_n times and the weights xcd_m times; take the split with the fewest bytes that divides both counts.
@@ -330,7 +333,7 @@ void fill_problem(const syno_plan* plan, int which, MfmaParams& p) {
 // row, or one panel after the other, coming back to the same source rows: unless the whole rectangle is resident at
 // once, the operand it comes back to has to stay in that XCD's L2 (4 MB, half of it left to the streaming one), or
 // every pass fetches it again.
-void deal_to_xcds(const ConvLike& c, bool bf, MfmaParams& p) {
+void deal_to_xcds(const ConvLike& c, bool bf, MfmaPlace& p) {
   const int plane = c.Hi * c.Wi, KHW = c.KH * c.KW;
   p.xcd_m = p.xcd_n = p.xcd_rows_first = 0;
   if (((int64_t)p.n_mblocks * p.n_nblocks) % 8 == 0) {
@@ -352,18 +355,31 @@ void deal_to_xcds(const ConvLike& c, bool bf, MfmaParams& p) {
       }
     }
   }
+  p.n_images = c.N;
+  p.img_slots = (c.Ho - 1) * p.sh + c.KH;
+  p.m_tiles = reciprocal((int64_t)p.n_mblocks * p.n_nblocks); p.m_nblocks = reciprocal(p.n_nblocks); p.m_img = reciprocal(p.img_slots);
+  if (p.xcd_m > 0) {
+    p.xcd_sm = p.n_mblocks / p.xcd_m; p.xcd_sn = p.n_nblocks / p.xcd_n;
+    p.m_xcdn = reciprocal(p.xcd_n); p.m_sm = reciprocal(p.xcd_sm); p.m_sn = reciprocal(p.xcd_sn);
+  }
+}
+
+// Whether a block's place can be divided for in 32 bits
+bool tiles_divide(const MfmaParams& p, int groups) {
+  const int64_t tiles = (int64_t)p.n_mblocks * p.n_nblocks;
+  return groups * tiles * tiles < (1ll << 32);
 }
 
 // Parameter record of contraction `which` for tile variant vi and TR output rows per block.  False when the combination
 // does not fit the kernel's static limits.
-bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaParams& p, int ksplit = 1) {
+bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaPlace& p, int ksplit = 1) {
   const ConvLike& c = plan->conv;
   const bool bf = plan->in_dtype == SYNO_BF16;
   if (vi < 0 || vi >= num_variants(bf) || TR < 1) return false;
   // the kernel addresses its source tensor with 32-bit byte offsets
   if ((which == SYNO_FWD ? plan->x_elems : plan->out_elems) * (bf ? 2 : 4) >= (1ll << 32)) return false;
   const Variant& v = variant_of(bf, vi);
-  p = MfmaParams{};
+  p = MfmaPlace{};
   fill_problem(plan, which, p);
   p.TR = TR;
   p.BN = v.BN();
@@ -427,7 +443,7 @@ bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaParams& p
   p.lds_w_off = x_bytes;
   const int w_bytes = bf ? p.w_block * 2 : p.BN * p.w_row * 4;
   p.lds_tab_off = p.lds_w_off + ((w_bytes + 15) & ~15);
-  p.lds_bytes = p.lds_tab_off + ((p.n_slots * 4 + 15) & ~15);
+  p.lds_bytes = p.lds_tab_off + (bf ? (p.n_slots * 4 + 15) & ~15 : 0);      // (bf16: the table of row slots)
   if (v.WK > 1) p.lds_bytes = std::max(p.lds_bytes, v.WM * v.WN * v.TM * v.TN * 1024);
   if (!bf && p.w_row * p.BN >= (1 << 20)) return false;
   auto magic = [](int64_t d) { return (uint32_t)(((1ull << 32) + d - 1) / std::max<int64_t>(d, 1)); };
@@ -450,7 +466,7 @@ bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaParams& p
     p.split_stride = (int32_t)((result + 3) & ~3ll);
   }
   deal_to_xcds(c, bf, p);
-  return p.lds_bytes <= kMaxLdsBytes;
+  return p.lds_bytes <= kMaxLdsBytes && tiles_divide(p, c.G * p.ksplit);
 }
 
 // ---- fp32 on the bf16 matrix cores (conv_split.h): the record of one tile configuration
@@ -509,18 +525,11 @@ bool fill_split(const syno_plan* plan, int which, int cfg, int TR, SplitParams& 
   if (v.WK > 1) p.lds_bytes = std::max<int>(p.lds_bytes, 8 * (int)((MT + v.WM - 1) / v.WM) * v.TN * 1024);
   if (p.lds_bytes > kMaxLdsBytes) return false;
   auto magic = [](int64_t d) { return d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); };
-  const int64_t tiles = (int64_t)p.n_mblocks * p.n_nblocks;
-  if (2048 * per_cg >= (1ll << 32) || (int64_t)p.rows_total * c.Ho >= (1ll << 32) || c.G * tiles * tiles >= (1ll << 32)) return false;
+  if (2048 * per_cg >= (1ll << 32) || (int64_t)p.rows_total * c.Ho >= (1ll << 32) || !tiles_divide(p, c.G)) return false;
   p.m_wo = magic(c.Wo); p.m_ho = magic(c.Ho); p.m_vpr = magic(c.Wi); p.m_pcg = magic(per_cg);
-  p.n_images = c.N;
-  p.img_slots = (c.Ho - 1) * p.sh + c.KH;
-  p.m_tiles = magic(tiles); p.m_nblocks = magic(p.n_nblocks); p.m_img = magic(p.img_slots); p.m_slots = magic(p.n_slots);
+  p.m_slots = magic(p.n_slots);
   p.ksplit = 1;
   deal_to_xcds(c, false, p);
-  if (p.xcd_m > 0) {
-    p.xcd_sm = p.n_mblocks / p.xcd_m; p.xcd_sn = p.n_nblocks / p.xcd_n;
-    p.m_xcdn = magic(p.xcd_n); p.m_sm = magic(p.xcd_sm); p.m_sn = magic(p.xcd_sn);
-  }
   // (tiles that are all resident at once come back to neither operand: those that start together share the larger one)
   if (p.xcd_m > 0 && (p.n_mblocks / p.xcd_m) * (p.n_nblocks / p.xcd_n) <= 32)
     p.xcd_rows_first = (double)p.Og * p.Cg * T > (double)c.N * p.Cg * c.Hi * c.Wi;
@@ -615,7 +624,7 @@ bool mfma_supports(const syno_plan* p, int which) {
   if (c.ph >= c.KH || c.pw >= c.KW) return false;
   if (c.Og == 1 && c.Cg == 1) return false;          // no contraction to speak of
   if (rows_supports(p, which)) return true;
-  MfmaParams mp;
+  MfmaPlace mp;
   for (int vi = 0; vi < num_variants(p->in_dtype == SYNO_BF16); ++vi)
     for (int TR = 1; TR <= c.N * c.Ho && TR * c.Wo <= 16 * 32; ++TR)
       if (fill_params(p, which, vi, TR, mp)) return true;
@@ -633,7 +642,7 @@ void mfma_configure(syno_plan* plan, int which) {
   if (bf && !flow && plan->opt.mfma_variant >= -1 && plan->opt.mfma_variant <= 0 && rows_configure(plan, which)) return;
   double best = 1e300;
   int best_v = -1, best_tr = 0;
-  MfmaParams mp;
+  MfmaPlace mp;
   // the descriptor's options may name the tile variant and the rows per block (verification and tuning aid).
   // A reduction over thousands of channels whose tiles would leave compute units idle may be split over workgroups
   // (each still runs at least 32 chunks); the option names a split outright
@@ -698,7 +707,7 @@ void mfma_configure(syno_plan* plan, int which) {
   if (plan->opt.mfma_taps == 1) mp.U = 1;     // (option: the one-tap-per-row-step instantiation)
   mp.probe_lo = (uint32_t)reinterpret_cast<uintptr_t>(plan->opt.clock_probe);
   mp.probe_hi = (uint32_t)(reinterpret_cast<uintptr_t>(plan->opt.clock_probe) >> 32);
-  static_assert(sizeof(MfmaParams) <= sizeof(plan->launch[which].params), "parameter record does not fit");
+  static_assert(sizeof(MfmaPlace) <= sizeof(plan->launch[which].params), "parameter record does not fit");
   memcpy(plan->launch[which].params, &mp, sizeof mp);
   plan->launch[which].params_ready = true;
   plan->launch[which].variant = best_v * 4096 + best_tr;
@@ -725,7 +734,7 @@ std::string mfma_describe(const syno_plan* plan, int which) {
     return d;
   }
   const int vi = plan->launch[which].variant / 4096, TR = plan->launch[which].variant % 4096;
-  MfmaParams p;
+  MfmaPlace p;
   if (!fill_params(plan, which, vi, TR, p)) return "unconfigured";
   const Variant& v = variant_of(plan->in_dtype == SYNO_BF16, vi);
   char b[256];
@@ -761,7 +770,7 @@ syno_status launch_mfma(const syno_plan* plan, int which, const void* A, const v
     launch_split(cfg, sp.KH * sp.KW, tiles, sp, static_cast<const float*>(A), static_cast<const float*>(B), static_cast<float*>(out), stream);
     return hipGetLastError() == hipSuccess ? SYNO_OK : SYNO_ERR_HIP;
   }
-  MfmaParams p;
+  MfmaPlace p;
   memcpy(&p, plan->launch[which].params, sizeof p);
   const bool obf = plan->out_dtype == SYNO_BF16;
   // a split reduction leaves its partial results behind the weights in the workspace

@@ -3,7 +3,7 @@
 
 namespace syno {
 
-void launch_mfma_f32_lo(int vi, const MfmaParams& p, const void* X, const void* W, void* out, hipStream_t s) {
+void launch_mfma_f32_lo(int vi, const MfmaPlace& p, const void* X, const void* W, void* out, hipStream_t s) {
 #define SYNO_CASE(VI)                                              \
   case VI:                                                         \
     if (p.U == 3) launch_variant<false, VI, 3, 0, false>(p, X, W, out, s); \
