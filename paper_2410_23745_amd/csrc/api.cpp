@@ -173,7 +173,8 @@ syno_status run(const syno_plan* plan, int which, const void* A, const void* B, 
       syno_status st = syno::launch_phase_weight_build(c, ps, window, (int)esz, B, Wpp, stream);
       if (st != SYNO_OK) return st;
       const int pass = window == 2 ? SYNO_BWD_DATA : SYNO_FWD;
-      st = run(plan->phase_conv_dx, pass, A, Wpp, dXp, rest, stream);
+      st = run(plan->phase_conv_dx, pass, A, Wpp, plan->phase_direct ? out : dXp, rest, stream);
+      if (plan->phase_direct) return st;
       if (st != SYNO_OK) return st;
       if (ps == 2) return syno::launch_phase_planes(c, false, (int)osz, dXp, out, stream);
       const void* one = unit_weight(plan->out_dtype);

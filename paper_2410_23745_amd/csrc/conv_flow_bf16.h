@@ -22,6 +22,7 @@ struct FlowParams {
   int32_t x_bytes, w_bytes, lds_bytes, G;
   int32_t xcd_m, xcd_n, sm, sn, xcd_rows_first;      // as in conv_mfma; sm x sn tiles to an XCD
   int32_t out_bf16;
+  int32_t phases;                     // 2x2 windows: the result is an image in the place of its phase planes, as in conv_split
   // ceil(2^32 / d), 0 for d = 1
   uint32_t m_tiles, m_nblocks, m_xcdn, m_sm, m_sn, m_ho, m_wo, m_pcg, m_vpr, m_img, m_edge;
   int32_t probe_lo, probe_hi;
@@ -404,11 +405,27 @@ __global__ __launch_bounds__(512) void conv_flow_bf16(const FlowParams p, const 
     auto element = [&](int m, int& px) -> int64_t {       // pixel m of the block -> element of the result
       const int i = flow_div(m, p.m_wo), n = flow_div(h0 + i, p.m_ho);
       px = (h0 + i - n * p.Ho) * p.Wo + (m - i * p.Wo);
+      if constexpr (T == 4)
+        if (p.phases) return (int64_t)(n0 + n) * p.os_n + (int64_t)(o >> 2) * (4 * p.os_o) + (2 * (h0 + i - n * p.Ho) + (o >> 1 & 1)) * (2 * p.Wo) + 2 * (m - i * p.Wo) + (o & 1);
       return (int64_t)(n0 + n) * p.os_n + (int64_t)g * p.os_g + (int64_t)o * p.os_o + px;
     };
     int px;
-    const int64_t off = element(m0, px);
-    if (m0 + 3 < block_px && px + 3 < img_px) {
+    int64_t off = element(m0, px);
+    bool four = m0 + 3 < block_px && px + 3 < img_px;
+    if constexpr (T == 4)
+      if (p.phases) {
+        // four pixels of a row of one phase: the lane beside this one has the same of the phase between them, and each of the two
+        // stores four adjacent pixels of the image
+        four = (p.Wo & 3) == 0;
+        const bool b = o & 1;
+        const float take0 = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, b ? v[0] : v[2]), 0xb1, 0xf, 0xf, true));
+        const float take1 = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, b ? v[1] : v[3]), 0xb1, 0xf, 0xf, true));
+        if (four) {
+          v = b ? flow_f4{take0, v[2], take1, v[3]} : flow_f4{v[0], take0, v[1], take1};
+          off += b ? 3 : 0;            // (from the odd phase's first pixel to the pair after next)
+        }
+      }
+    if (four) {
       if (p.out_bf16) {
         flow_u2_any d;
         d[0] = flow_round_pair(v[0], v[1]); d[1] = flow_round_pair(v[2], v[3]);

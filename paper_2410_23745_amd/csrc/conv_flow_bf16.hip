@@ -173,6 +173,14 @@ bool flow_configure(syno_plan* plan, int which, bool* sure) {
   return true;
 }
 
+bool flow_store_phases(syno_plan* plan) {
+  FlowRecord p;
+  memcpy(&p, plan->launch[SYNO_BWD_DATA].params, sizeof p);
+  p.phases = 1;
+  memcpy(plan->launch[SYNO_BWD_DATA].params, &p, sizeof p);
+  return true;
+}
+
 std::string flow_describe(const syno_plan* plan, int which) {
   FlowRecord p;
   memcpy(&p, plan->launch[which].params, sizeof p);

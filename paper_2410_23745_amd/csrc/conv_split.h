@@ -12,6 +12,8 @@ struct SplitParams : MfmaPlace {
   int32_t octet;                     // pixels between channel octets in LDS: a multiple of 16
   int32_t adjoint;                   // weights of backward-data: taps reversed (selects the instantiation)
   uint32_t m_slots;                  // ceil(2^32 / n_slots), 0 for 1
+  int32_t phases;                    // 2x2 windows: output channels are (c, a, b) and the result is the image whose pixel (2h + a, 2w + b) of
+                                     // channel c that is, in the place of the phase planes
 };
 
 namespace {
@@ -453,6 +455,8 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
   bool odd = false;                // some result of this lane is none that the parts can give
   auto element = [&](int m, int o) -> int64_t {       // pixel m of the block, output channel o -> element of the result
     const int i = fdiv(m, p.m_wo), r = R0 + i, n = fdiv(r, p.m_ho);
+    if constexpr (T == 4)
+      if (p.phases) return (int64_t)n * p.os_n + (int64_t)(o >> 2) * (4 * p.os_o) + (2 * (r - n * p.Ho) + (o >> 1 & 1)) * (2 * p.Wo) + 2 * (m - i * p.Wo) + (o & 1);
     return (int64_t)n * p.os_n + (int64_t)(g * p.Og + o) * p.os_o + (r - n * p.Ho) * p.Wo + (m - i * p.Wo);
   };
   auto store = [&](int t, int u, floatx4 v) {
@@ -465,7 +469,19 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
     v *= kResultScale;
     // (one test for the four values; each is looked at again below)
     odd |= !trusted_result(fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]));
-    if (m0 + 3 < block_px && px + 3 < img_px && (off & 3) == 0) {
+    if constexpr (T == 4)
+      if (p.phases && (p.Wo & 3) == 0) {
+        // four pixels of a row of one phase: the lane beside this one has the same of the phase between them, and each of the two
+        // stores four adjacent pixels of the image (the planes and their way back were 11 of 62 us at 32x64x56x56)
+        const bool b = o & 1;
+        const float give0 = b ? v[0] : v[2], give1 = b ? v[1] : v[3];
+        const float take0 = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, give0), 0xb1, 0xf, 0xf, true));
+        const float take1 = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, give1), 0xb1, 0xf, 0xf, true));
+        const f32x4_unaligned w = {b ? take0 : v[0], b ? v[2] : take0, b ? take1 : v[1], b ? v[3] : take1};
+        *reinterpret_cast<f32x4_unaligned*>(out + (element(m0, o & ~1) + (b ? 4 : 0))) = w;
+        return;
+      }
+    if ((T != 4 || !p.phases) && m0 + 3 < block_px && px + 3 < img_px && (off & 3) == 0) {
       *reinterpret_cast<float4*>(out + off) = make_float4(v[0], v[1], v[2], v[3]);
     } else {
 #pragma unroll
@@ -496,8 +512,9 @@ __global__ __launch_bounds__(512) void conv_split(const SplitParams p, const flo
       store(i / TN, i % TN, v);
     }
   }
-  // (see split_pair)
+  // (see split_pair; with phases a lane's results were stored by the lane beside it, in the same instructions)
   if (__any(odd)) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
 #pragma unroll 1
     for (int i = first_tile; i < NTL * TN; i += tile_step) {
       const int t = i / TN, o0 = nb * BN + (wn * TN + i % TN) * 16, o = o0 + (lane & 15);

@@ -717,6 +717,17 @@ void mfma_configure(syno_plan* plan, int which) {
   plan->launch[which].workspace = weight_workspace_bytes(mp, bf) + (mp.ksplit > 1 ? (size_t)mp.ksplit * mp.split_stride * 4 : 0);
 }
 
+bool mfma_store_phases(syno_plan* plan) {
+  Launch& L = plan->launch[SYNO_BWD_DATA];
+  if (!L.params_ready || L.variant > -2 || plan->conv.KH != 2 || plan->conv.KW != 2 || plan->conv.G != 1) return false;
+  if (plan->in_dtype == SYNO_BF16) return flow_store_phases(plan);
+  SplitParams p;
+  memcpy(&p, L.params, sizeof p);
+  p.phases = 1;
+  memcpy(L.params, &p, sizeof p);
+  return true;
+}
+
 std::string mfma_describe(const syno_plan* plan, int which) {
   if (plan->launch[which].variant == -1) return rows_describe(plan, which);
   if (plan->launch[which].variant <= -2 && plan->in_dtype == SYNO_BF16) return flow_describe(plan, which);

@@ -161,6 +161,7 @@ struct syno_plan {
   // windows of those convolutions, per gradient: 3 (pad 1), 2 (rows and columns -1 and 0) or 1.  With window 2 dX is that
   // convolution's backward-data, else the forward contraction of its adjoint
   int32_t phase_window_dw = 0, phase_window_dx = 0;
+  bool phase_direct = false;     // phase_conv_dx writes dX itself: no planes, no way back
   int32_t phase_s = 0;           // phases per image axis that take part: s, or 1 for a 1x1 window, which only reads phase
                                  // (0, 0) - the view is then the sub-sampling X[.., s*h', s*w'] itself
   ~syno_plan() { for (syno_plan* s : sliced) delete s; delete inner; delete inner_dx; delete phase_view_x; delete phase_view_dx; delete phase_conv_dw; delete phase_conv_dx; }
@@ -230,6 +231,9 @@ syno_status launch_rows(const syno_plan* p, int which, const void* A, const void
 bool flow_configure(syno_plan* p, int which, bool* sure);
 std::string flow_describe(const syno_plan* p, int which);
 syno_status launch_flow(const syno_plan* p, int which, const void* A, const void* B, void* out, hipStream_t stream);
+// kernels_mfma.hip: has backward-data of a 2x2 window on a stride's phase planes leave the image itself; false where its kernel cannot
+bool mfma_store_phases(syno_plan* p);
+bool flow_store_phases(syno_plan* p);
 // kernels_mfma.hip: dst[c][r] = src[r][c] for a row-major rows x cols matrix of 2- or 4-byte elements
 constexpr int kViaTransposedCopy = 100;
 // kernels_mfma.hip: out[i] = the sum over k < count of parts[k * n + i]

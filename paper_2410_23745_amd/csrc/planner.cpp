@@ -1451,6 +1451,7 @@ syno_status build_plan(const syno_desc* desc, syno_plan* plan, std::string* why)
                 // (its weights are smaller by more than what packing them takes, but for the smallest: the 3x3 window's workspace does)
                 L.workspace = std::max(L.workspace, round_up((size_t)CP * c.Og * 4 * esz) + round_up((size_t)plane_elems * osz) + L2.workspace);
                 plan->phase_conv_dx = c2; plan->phase_window_dx = 2;
+                plan->phase_direct = ps == 2 && mfma_store_phases(c2);
                 delete cx;
               } else {
                 delete c2;

@@ -62,3 +62,27 @@ def test_what_lies_beside_the_operands(syno, cfg):  # noqa: F811
         fine = torch.isfinite(b)
         # 360 products, exact in fp32, in any order on either side: 2 * 360 roundings of sums below 360 * max|X| * max|W|
         assert float((a - b)[fine].abs().max()) <= 2 * 360 * 2.0 ** -24 * float(b[fine].abs().max()) * 8
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,W", [(8, 12), (7, 9), (5, 16)])
+@pytest.mark.parametrize("kind", ("f32", "bf16", "bf16_results"))
+def test_input_gradients_of_strided_convolutions_are_stored_as_the_image(syno, oracle, H, W, kind):  # noqa: F811
+    """3x3 with stride 2 on 2x2 windows of the phase planes: lanes side by side hold the two phases of a row and exchange halves where
+    rows are whole quads (12 and 16 pixels), else store every second pixel."""
+    w = wl.make_conv(32 if kind == "f32" else 3, 96, H, seed=81, bf16=kind != "f32", Co=192, Wd=W, stride=2, with_grad=True, out_bf16=kind == "bf16_results")
+    plan = syno.Plan(w.desc)
+    assert "(window=2): " in plan.describe(1) and ("bf16-parts" if kind == "f32" else "in-chunks") in plan.describe(1), plan.describe(1)
+    run_all(syno, oracle, w, 0, directions=(1,))
+    if kind == "f32":
+        # infinities and NaNs are summed again, from results that the lane beside has stored
+        plain = syno.Plan(w.desc, kernel_policy=1)
+        gen = torch.Generator(device="cuda").manual_seed(9)
+        G, V = torch.randn(plan.out_shape, generator=gen, device="cuda"), torch.randn(plan.w_shape, generator=gen, device="cuda") / 40
+        G[0, 3, 2, 5], G[1, 7, H - 1, W - 1], G[31, 9, 0, 0] = float("inf"), float("nan"), float("-inf")
+        a, b = plan.backward_data(G, V), plain.backward_data(G, V)
+        # (the taps that a 2x2 window on the planes has and the 3x3 one has not are products with zero: NaN beside an infinity)
+        fine = torch.isfinite(a)
+        assert bool(torch.isfinite(b)[fine].all()) and int((~fine).sum()) <= 3 * 96 * 16
+        # up to 4 * 192 terms in fp32 on either side
+        assert float((a - b)[fine].abs().max()) <= 2 * 768 * 2.0 ** -24 * 8 * float(b[fine].abs().max())
