@@ -593,24 +593,32 @@ __global__ __launch_bounds__(256) void dw_reduce_tiles(const DwParams p, const f
 
 // The same sums for many splits and few tiles: a block owns one slot (64 quadruples, one tap of a 16x16 tile), which
 // keeps enough blocks in flight when dW is small; the stores are scattered, which does not matter at that size.
-__global__ __launch_bounds__(256) void dw_reduce_slots(const DwParams p, const float4* __restrict__ partial,
-                                                       float* __restrict__ dW) {
-  __shared__ double4 sums[4][64];
+// W waves take turns with the partials: 4, or 16 from 72 partials on where there are at most 256 slots: the chains of loads are then a
+// fourth as long (weight gradients of one tile, the whole call: 72 to 95 partials 1.04 to 1.09 times as fast, from 96 on 1.03 to 1.13;
+// 48 to 71 0.98 to 1.01, 24 to 47 0.99; with 600 slots 16 waves each take longer to start than they save).
+template <int W>
+__global__ __launch_bounds__(W * 64) void dw_reduce_slots(const DwParams p, const float4* __restrict__ partial,
+                                                          float* __restrict__ dW) {
+  __shared__ double4 sums[W][64];
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int64_t n4 = (int64_t)p.n_tiles * p.slots * 64;
   const int64_t e = (int64_t)blockIdx.x * 64 + lane;
   double4 s = make_double4(0., 0., 0., 0.);
 #pragma unroll 4
-  for (int k = grp; k < p.n_splits; k += 4) {
+  for (int k = grp; k < p.n_splits; k += W) {
     const float4 v = partial[(int64_t)k * n4 + e];
     s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
   }
   sums[grp][lane] = s;
   __syncthreads();
   if (grp != 0) return;
-  const double4 a = sums[0][lane], b = sums[1][lane], c4 = sums[2][lane], d = sums[3][lane];
-  const float r[4] = {(float)((a.x + b.x) + (c4.x + d.x)), (float)((a.y + b.y) + (c4.y + d.y)), (float)((a.z + b.z) + (c4.z + d.z)),
-                      (float)((a.w + b.w) + (c4.w + d.w))};
+  double4 all = make_double4(0., 0., 0., 0.);
+#pragma unroll
+  for (int j = 0; j < W; j += 4) {
+    const double4 a = sums[j][lane], b = sums[j + 1][lane], c4 = sums[j + 2][lane], d = sums[j + 3][lane];
+    all.x += (a.x + b.x) + (c4.x + d.x); all.y += (a.y + b.y) + (c4.y + d.y); all.z += (a.z + b.z) + (c4.z + d.z); all.w += (a.w + b.w) + (c4.w + d.w);
+  }
+  const float r[4] = {(float)all.x, (float)all.y, (float)all.z, (float)all.w};
   const int T = p.KH * p.KW;
   int q = blockIdx.x;
   const int slot = q % p.slots; q /= p.slots;
@@ -1101,8 +1109,12 @@ syno_status launch_mfma_dw(const syno_plan* plan, const void* A, const void* B, 
   if (p.n_splits == 1) {
     // (written by the contraction itself)
   } else if (p.n_splits > 4 && p.n_tiles * (p.slots / (p.KH * p.KW)) < 256)
-    hipLaunchKernelGGL(dw_reduce_slots, dim3(p.n_tiles * p.slots), dim3(256), 0, stream, p,
-                       reinterpret_cast<const float4*>(ws), static_cast<float*>(out));
+  {
+    const int blocks = p.n_tiles * p.slots;
+    const float4* const parts = reinterpret_cast<const float4*>(ws);
+    if (p.n_splits >= 72 && blocks <= 256) hipLaunchKernelGGL(dw_reduce_slots<16>, dim3(blocks), dim3(1024), 0, stream, p, parts, static_cast<float*>(out));
+    else hipLaunchKernelGGL(dw_reduce_slots<4>, dim3(blocks), dim3(256), 0, stream, p, parts, static_cast<float*>(out));
+  }
   else
     hipLaunchKernelGGL(dw_reduce_tiles, dim3(p.n_tiles * (p.slots / (p.KH * p.KW))), dim3(256), 0, stream, p,
                        reinterpret_cast<const float4*>(ws), static_cast<float*>(out));
