@@ -48,6 +48,12 @@ typedef const SYNO_GLOBAL char* flow_ptr;      // (keeps its address space throu
 // n / d through m = ceil(2^32 / d), 0 for d = 1 (no branch)
 __device__ __forceinline__ int flow_div(int n, uint32_t m) { return (int)__umulhi((uint32_t)n, m) + (n & (m ? 0 : -1)); }
 
+// The same for any n below 2^31 (the estimate is at most one too large): a launch may have millions of blocks
+__device__ __forceinline__ int flow_div_large(int n, int d, uint32_t m) {
+  const int q = flow_div(n, m);
+  return q - ((uint32_t)n < (uint32_t)q * (uint32_t)d ? 1 : 0);
+}
+
 template <int I, int N, class F>
 __device__ __forceinline__ void flow_for(F&& f) {
   if constexpr (I < N) {
@@ -101,18 +107,18 @@ __global__ __launch_bounds__(512) void conv_flow_bf16(const FlowParams p, const 
   const int wm = WM == 8 ? wave : WM == 4 ? (wave + 2 * wn) & 3 : wave >> 2;
 
   // ---- this block's tile
-  const int g = flow_div(blockIdx.x, p.m_tiles), local = blockIdx.x - g * (p.n_mblocks * p.n_nblocks);
+  const int tiles = p.n_mblocks * p.n_nblocks, g = flow_div_large(blockIdx.x, tiles, p.m_tiles), local = blockIdx.x - g * tiles;
   int mb, nb;
   if (p.xcd_m > 0) {
     const int xcd = local & 7, idx = local >> 3;
     const int xm = flow_div(xcd, p.m_xcdn), xn = xcd - xm * p.xcd_n;
     int im, in;
-    if (p.xcd_rows_first) { in = flow_div(idx, p.m_sm); im = idx - in * p.sm; }
-    else { im = flow_div(idx, p.m_sn); in = idx - im * p.sn; }
+    if (p.xcd_rows_first) { in = flow_div_large(idx, p.sm, p.m_sm); im = idx - in * p.sm; }
+    else { im = flow_div_large(idx, p.sn, p.m_sn); in = idx - im * p.sn; }
     mb = xm * p.sm + im;
     nb = xn * p.sn + in;
   } else {
-    mb = flow_div(local, p.m_nblocks);
+    mb = flow_div_large(local, p.n_nblocks, p.m_nblocks);
     nb = local - mb * p.n_nblocks;
   }
   const int R0 = mb * p.TR, rows = min(p.TR, p.rows_total - R0);

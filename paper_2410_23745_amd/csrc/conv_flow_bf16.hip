@@ -74,7 +74,7 @@ bool fill_flow(const syno_plan* plan, int which, int cfg, int TR, FlowRecord& p)
   if (v.WK > 1) p.lds_bytes = std::max(p.lds_bytes, 8 * p.tiles * v.TN * 1024);
   if (p.lds_bytes > kFlowLdsBytes) return false;
   const int64_t tiles = (int64_t)p.n_mblocks * p.n_nblocks, most = 1ll << 32;
-  if (c.G * tiles * tiles >= most || c.G * tiles >= (1ll << 31) || (int64_t)p.rows_total * p.Ho >= most) return false;
+  if (c.G * tiles >= (1ll << 23) || (int64_t)p.rows_total * p.Ho >= most) return false;
   auto magic = [](int64_t d) { return d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); };
   p.m_tiles = magic(tiles); p.m_nblocks = magic(p.n_nblocks);
   p.m_ho = magic(p.Ho); p.m_wo = magic(p.Wo); p.m_pcg = magic(per); p.m_vpr = magic(p.vpr); p.m_img = magic(p.img_slots);

@@ -72,21 +72,28 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 // The same without a branch
 __device__ __forceinline__ int div_by(int n, uint32_t m) { return (int)__umulhi((uint32_t)n, m) + (n & (m ? 0 : -1)); }
 
+// The same for any n below 2^31 (the estimate is at most one too large): a launch may have millions of blocks
+__device__ __forceinline__ int div_large(int n, int d, uint32_t m) {
+  const int q = div_by(n, m);
+  return q - ((uint32_t)n < (uint32_t)q * (uint32_t)d ? 1 : 0);
+}
+
 // The tile of block `bid`: `plane` (group, and split), row of tiles, panel of output channels
 __device__ __forceinline__ void tile_of_block(const MfmaPlace& p, int bid, int& plane, int& mb, int& nb) {
   // (a plane that is dealt to the XCDs holds a multiple of 8 tiles, so the low three bits of the place in it name the XCD)
-  plane = div_by(bid, p.m_tiles);
-  const int local = bid - plane * (p.n_mblocks * p.n_nblocks);
+  const int tiles = p.n_mblocks * p.n_nblocks;
+  plane = div_large(bid, tiles, p.m_tiles);
+  const int local = bid - plane * tiles;
   if (p.xcd_m > 0) {
     const int xcd = local & 7, idx = local >> 3;
     const int xm = div_by(xcd, p.m_xcdn), xn = xcd - xm * p.xcd_n;
     int im, in;
-    if (p.xcd_rows_first) { in = div_by(idx, p.m_sm); im = idx - in * p.xcd_sm; }
-    else { im = div_by(idx, p.m_sn); in = idx - im * p.xcd_sn; }
+    if (p.xcd_rows_first) { in = div_large(idx, p.xcd_sm, p.m_sm); im = idx - in * p.xcd_sm; }
+    else { im = div_large(idx, p.xcd_sn, p.m_sn); in = idx - im * p.xcd_sn; }
     mb = xm * p.xcd_sm + im;
     nb = xn * p.xcd_sn + in;
   } else {
-    mb = div_by(local, p.m_nblocks);
+    mb = div_large(local, p.n_nblocks, p.m_nblocks);
     nb = local - mb * p.n_nblocks;
   }
 }

@@ -364,12 +364,6 @@ void deal_to_xcds(const ConvLike& c, bool bf, MfmaPlace& p) {
   }
 }
 
-// Whether a block's place can be divided for in 32 bits
-bool tiles_divide(const MfmaParams& p, int groups) {
-  const int64_t tiles = (int64_t)p.n_mblocks * p.n_nblocks;
-  return groups * tiles * tiles < (1ll << 32);
-}
-
 // Parameter record of contraction `which` for tile variant vi and TR output rows per block.  False when the combination
 // does not fit the kernel's static limits.
 bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaPlace& p, int ksplit = 1) {
@@ -466,7 +460,7 @@ bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaPlace& p,
     p.split_stride = (int32_t)((result + 3) & ~3ll);
   }
   deal_to_xcds(c, bf, p);
-  return p.lds_bytes <= kMaxLdsBytes && tiles_divide(p, c.G * p.ksplit);
+  return p.lds_bytes <= kMaxLdsBytes;
 }
 
 // ---- fp32 on the bf16 matrix cores (conv_split.h): the record of one tile configuration
@@ -525,7 +519,7 @@ bool fill_split(const syno_plan* plan, int which, int cfg, int TR, SplitParams& 
   if (v.WK > 1) p.lds_bytes = std::max<int>(p.lds_bytes, 8 * (int)((MT + v.WM - 1) / v.WM) * v.TN * 1024);
   if (p.lds_bytes > kMaxLdsBytes) return false;
   auto magic = [](int64_t d) { return d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); };
-  if (2048 * per_cg >= (1ll << 32) || (int64_t)p.rows_total * c.Ho >= (1ll << 32) || !tiles_divide(p, c.G)) return false;
+  if (2048 * per_cg >= (1ll << 32) || (int64_t)p.rows_total * c.Ho >= (1ll << 32)) return false;
   p.m_wo = magic(c.Wo); p.m_ho = magic(c.Ho); p.m_vpr = magic(c.Wi); p.m_pcg = magic(per_cg);
   p.m_slots = magic(p.n_slots);
   p.ksplit = 1;

@@ -86,3 +86,18 @@ def test_input_gradients_of_strided_convolutions_are_stored_as_the_image(syno, o
         assert bool(torch.isfinite(b)[fine].all()) and int((~fine).sum()) <= 3 * 96 * 16
         # up to 4 * 192 terms in fp32 on either side
         assert float((a - b)[fine].abs().max()) <= 2 * 768 * 2.0 ** -24 * 8 * float(b[fine].abs().max())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,N", [(7, 9001), (8, 8200)])
+@pytest.mark.parametrize("kind,options", [("in-chunks", {"mfma_variant": -2}), ("bf16-parts", {"mfma_variant": -2}), ("variant=4", {"mfma_variant": 5})])
+def test_more_than_65536_tiles(syno, H, N, kind, options):  # noqa: F811
+    """A block finds its tile by multiplying with a reciprocal, which is one off for some numbers from 2^16 tiles on if it is not put right.
+    Rows per block do not change a result's sums."""
+    d = wl.conv2d(N, 8 if kind == "in-chunks" else 32, 80, H, 8, 3, 3, BF16 if kind == "in-chunks" else F32, F32)
+    many, few = (syno.Plan(d, mfma_rows=rows, **options) for rows in (1, H))
+    assert f"{kind} " in many.describe(0) and "rows/block=1 " in many.describe(0), many.describe(0)
+    assert int(many.describe(0).split("grid=")[1].split()[0]) > 65536
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    X, W = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16 if kind == "in-chunks" else torch.float32) for shape in (many.x_shape, many.w_shape))
+    assert torch.equal(many.forward(X, W), few.forward(X, W))
