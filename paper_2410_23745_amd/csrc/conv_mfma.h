@@ -153,6 +153,11 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
+// Whether a kernel finds its rows through a table in LDS, not in closed form: bf16, whose small calls lose 1 to 2 % to 40 bytes more of
+// kernel arguments, and the fp32 variant that gathers its weights one by one with 14 accumulators (0), out of registers already (the
+// closed form: 0.98 to 1.0 times as fast over 800 calls; the other fp32 variants 1.01 to 1.08).
+constexpr bool slot_table(bool bf, bool wnat, int TM, int TN) { return bf || (!wnat && TM * TN >= 14); }
+
 // BF = false: fp32 inputs, CI = 4, v_mfma_f32_16x16x4_f32  (A: lane -> row l%16, k = l/16).
 // BF = true : bf16 inputs, CI = 8, v_mfma_f32_16x16x32_bf16 (A: lane -> row l%16, k = 8*(l/16)..+7);
 //             `Wv` is the packed copy.
@@ -168,10 +173,11 @@ __device__ __forceinline__ void static_for(F&& f) {
 //      per-SIMD share of the output is only a few MFMA tiles: a wave then still issues TM*TN MFMAs per
 //      LDS round trip); their accumulators are added through LDS at the end.
 template <bool BF, bool WNAT, int WM, int WN, int WK, int TM, int TN, int XI, int WI, bool ONE, int KCB, int U, int WF, bool OUTBF>
-__global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditional_t<BF, MfmaParams, MfmaPlace> p, const void* __restrict__ Xv,
+__global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditional_t<slot_table(BF, WNAT, TM, TN), MfmaParams, MfmaPlace> p, const void* __restrict__ Xv,
                                                          const void* __restrict__ Wv, void* __restrict__ out) {
   constexpr int NT = WM * WN * WK * 64;
   constexpr int BN = WN * TN * 16;
+  constexpr bool TABLE = slot_table(BF, WNAT, TM, TN);
   constexpr int CI = BF ? 8 : 4;
   constexpr int CG_STEP = BF ? 4 : 1;        // channel groups one MFMA consumes
   using XT = std::conditional_t<BF, uint16_t, float>;
@@ -197,7 +203,7 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
   // fp32: reciprocals and a closed form for the rows (with divisions, a walk over the images and a table of rows 5000 cycles go by before
   // the first load; calls take 1 / 1.04 to 1 / 1.06 of the time in the mean).  bf16, where 9 taps of packed weights got 13 % slower with it: the table
   int g, mb, nb, ksp = 0;
-  if constexpr (!BF) {
+  if constexpr (!TABLE) {
     tile_of_block(p, blockIdx.x, g, mb, nb);
   } else {
     int bid = blockIdx.x;
@@ -220,10 +226,10 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
   const int R0 = mb * p.TR;
   const int rows = min(p.TR, p.rows_total - R0);
   const int KHW = p.KH * p.KW;
-  const int n0 = BF ? 0 : div_by(R0, p.m_ho), h0 = R0 - n0 * p.Ho;
-  const int first_slots = BF || p.h_wrap ? 0 : (min(rows, p.Ho - h0) - 1) * p.sh + p.KH, shift = !BF && p.h_wrap ? (p.h_shift + p.h_shift_g * g) % p.Hi : 0;
+  const int n0 = TABLE ? 0 : div_by(R0, p.m_ho), h0 = R0 - n0 * p.Ho;
+  const int first_slots = TABLE || p.h_wrap ? 0 : (min(rows, p.Ho - h0) - 1) * p.sh + p.KH, shift = !TABLE && p.h_wrap ? (p.h_shift + p.h_shift_g * g) % p.Hi : 0;
   int* const slot_src = reinterpret_cast<int*>(smem + p.lds_tab_off);
-  if constexpr (BF) {
+  if constexpr (TABLE) {
     for (int s = tid; s < p.n_slots; s += NT) slot_src[s] = slot_source(p, R0, rows, g, s);
     __syncthreads();
   }
@@ -239,9 +245,9 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
 #pragma unroll
     for (int k = 0; k < XI; ++k) {
       const int idx = tid + k * NT;
-      const int cg = BF ? fdiv(idx, p.m_pcg) : div_by(idx, p.m_pcg), rem = idx - cg * per_cg;
-      const int s = BF ? fdiv(rem, p.m_vpr) : div_by(rem, p.m_vpr), x = min((rem - s * p.vpr) * p.vx, p.Wi - p.vx);
-      if constexpr (BF) {
+      const int cg = TABLE ? fdiv(idx, p.m_pcg) : div_by(idx, p.m_pcg), rem = idx - cg * per_cg;
+      const int s = TABLE ? fdiv(rem, p.m_vpr) : div_by(rem, p.m_vpr), x = min((rem - s * p.vpr) * p.vx, p.Wi - p.vx);
+      if constexpr (TABLE) {
         const int src = idx < total ? slot_src[s] : -1;
         x_goff[k] = src >= 0 ? src + x + cg * CI * p.xs_c : -1;
       } else {
@@ -366,9 +372,9 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
     for (int t = 0; t < N; ++t) {
       int m = (my_first + t) * 16 + (lane & 15);
       if (t >= my_tiles || m >= block_px) m = 0;
-      const int i = BF ? fdiv(m, p.m_wo) : div_by(m, p.m_wo), w = m - i * p.Wo;
+      const int i = TABLE ? fdiv(m, p.m_wo) : div_by(m, p.m_wo), w = m - i * p.Wo;
       // (every image before the row's adds KH - sh)
-      const int slot = BF ? slot_of_row(p, R0, i) : p.h_wrap ? i : i * p.sh + (p.KH - p.sh) * div_by(h0 + i, p.m_ho);
+      const int slot = TABLE ? slot_of_row(p, R0, i) : p.h_wrap ? i : i * p.sh + (p.KH - p.sh) * div_by(h0 + i, p.m_ho);
       const int px = slot * p.Wp + w * p.sw;
       a[t] = BF ? (px + (lane >> 4) * cg_stride) * 16 : px * 16 + (lane >> 4) * 4;       // LDS byte address of the lane's A operand at tap (0,0), channel group 0
     }
@@ -379,7 +385,7 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
     }
   };
   int early_a[TM], early_b[TN];
-  if constexpr (BF) operand_bases(early_a, early_b);
+  if constexpr (TABLE) operand_bases(early_a, early_b);
 
   // Everything from here on is instantiated once per possible tile count of a wave, so that the
   // accumulators and fragments of a wave with fewer row tiles do not occupy registers and the MFMA
@@ -632,9 +638,9 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
     for (int i = tid; i < n16; i += NT) xl[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   int late_a[NA], late_b[TN];
-  if constexpr (!BF) operand_bases(late_a, late_b);
-  auto& a_base = [&]() -> auto& { if constexpr (BF) return early_a; else return late_a; }();
-  auto& b_base = [&]() -> auto& { if constexpr (BF) return early_b; else return late_b; }();
+  if constexpr (!TABLE) operand_bases(late_a, late_b);
+  auto& a_base = [&]() -> auto& { if constexpr (TABLE) return early_a; else return late_a; }();
+  auto& b_base = [&]() -> auto& { if constexpr (TABLE) return early_b; else return late_b; }();
   if constexpr (BF && WF < 0 && ONE) {
     // The same for the backward-data adjoint: the B operand's rows are the forward input channels and its
     // reduction runs over the forward output channels, taps reversed.  A thread again loads 8 channels x

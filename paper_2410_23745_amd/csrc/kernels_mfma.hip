@@ -437,7 +437,7 @@ bool fill_params(const syno_plan* plan, int which, int vi, int TR, MfmaPlace& p,
   p.lds_w_off = x_bytes;
   const int w_bytes = bf ? p.w_block * 2 : p.BN * p.w_row * 4;
   p.lds_tab_off = p.lds_w_off + ((w_bytes + 15) & ~15);
-  p.lds_bytes = p.lds_tab_off + (bf ? (p.n_slots * 4 + 15) & ~15 : 0);      // (bf16: the table of row slots)
+  p.lds_bytes = p.lds_tab_off + (slot_table(bf, v.wnat, v.TM, v.TN) ? (p.n_slots * 4 + 15) & ~15 : 0);
   if (v.WK > 1) p.lds_bytes = std::max(p.lds_bytes, v.WM * v.WN * v.TM * v.TN * 1024);
   if (!bf && p.w_row * p.BN >= (1 << 20)) return false;
   auto magic = [](int64_t d) { return (uint32_t)(((1ull << 32) + d - 1) / std::max<int64_t>(d, 1)); };
