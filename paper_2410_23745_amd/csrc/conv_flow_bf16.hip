@@ -139,21 +139,18 @@ double flow_cost(const FlowRecord& p, const ConvLike& c) {
 
 }  // namespace
 
-// Fills launch[which] with the tiles of the lowest estimate; false where the kernel does not take the pass.  The options name a
-// configuration (mfma_variant -2 and below) and the rows per block.  On 30000 passes drawn (8 to 512
+// Fills launch[which] with the tiles of the lowest estimate; false where the kernel does not take the pass.  `named`: the one configuration
+// asked for, or -1; `rows`: the rows per block asked for, or 0.  On 30000 passes drawn (8 to 512
 // channels, 1 to 128 images of 5 to 64 pixels, strides 1 and 2) it takes 1 / 1.47 (forward), 1 / 1.79 (backward-data) and 1 / 1.45 (stride 2)
 // of the other kernels' time in the mean.  `*sure`: not one of the forward passes in several rounds of workgroups that wider or
 // narrower panels of output channels, or a single chunk, may suit better (0.72 to 1.7 times as fast).
-bool flow_configure(syno_plan* plan, int which, bool* sure) {
+bool flow_configure(syno_plan* plan, int which, int named, int rows, bool* sure) {
   const ConvLike& c = plan->conv;
-  const syno_plan_options& o = plan->opt;
-  if (o.mfma_variant > 0 || o.mfma_variant == -1 || o.mfma_splits || o.mfma_taps) return false;
-  const int named = o.mfma_variant <= -2 ? -2 - o.mfma_variant : -1;
   FlowRecord best{}, p;
   double least = 1e300;
   for (int cfg = 0; cfg < kNumFlowConfigs; ++cfg)
     for (int TR = 1; TR <= c.N * c.Ho && TR * c.Wo <= 16 * 32; ++TR) {
-      if ((named >= 0 && cfg != named) || (o.mfma_rows > 0 && TR != o.mfma_rows)) continue;
+      if ((named >= 0 && cfg != named) || (rows > 0 && TR != rows)) continue;
       if (!fill_flow(plan, which, cfg, TR, p)) continue;
       const double cost = flow_cost(p, c);
       if (cost < least) { least = cost; best = p; }

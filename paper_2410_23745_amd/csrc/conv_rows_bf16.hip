@@ -470,12 +470,13 @@ bool rows_supports(const syno_plan* plan, int which) {
 }
 
 // Picks the tile size and fills launch[which]; false when the kernel cannot take the pass.
-bool rows_configure(syno_plan* plan, int which) {
+// `named`: asked for by name; `rows`: the rows per block asked for, or 0
+bool rows_configure(syno_plan* plan, int which, bool named, int rows) {
   const ConvLike& c = plan->conv;
   RowsParams best{}, p;
   double best_cost = 1e300;
   for (int TR = 1; TR <= c.Ho; ++TR) {
-    if (plan->opt.mfma_rows > 0 && TR != plan->opt.mfma_rows) continue;
+    if (rows > 0 && TR != rows) continue;
     if (!rows_fill(plan, which, TR, p)) continue;
     rows_grid(p);
     const double cost = rows_cost(p);
@@ -484,7 +485,7 @@ bool rows_configure(syno_plan* plan, int which) {
   if (best_cost >= 1e300) return false;
   // a workgroup that walks over several tiles is not yet faster than the tiled kernel of this family: leave those
   // shapes there unless this kernel is named explicitly
-  if (best.S < best.n_tiles && plan->opt.mfma_variant != -1) return false;
+  if (best.S < best.n_tiles && !named) return false;
   Launch& L = plan->launch[which];
   static_assert(sizeof(RowsParams) <= sizeof(L.params), "parameter record does not fit");
   memcpy(L.params, &best, sizeof best);

@@ -628,12 +628,6 @@ bool mfma_supports(const syno_plan* p, int which) {
 void mfma_configure(syno_plan* plan, int which) {
   const ConvLike& c = plan->conv;
   const bool bf = plan->in_dtype == SYNO_BF16;
-  // bf16 windows of 3x3 go to the kernel in chunks, others whose whole reduction fits LDS to the row-streaming one (unless a tile
-  // variant is named)
-  bool sure = false;
-  const bool flow = bf && flow_configure(plan, which, &sure);
-  if (flow && sure) return;
-  if (bf && !flow && plan->opt.mfma_variant >= -1 && plan->opt.mfma_variant <= 0 && rows_configure(plan, which)) return;
   double best = 1e300;
   int best_v = -1, best_tr = 0;
   MfmaPlace mp;
@@ -646,6 +640,20 @@ void mfma_configure(syno_plan* plan, int which) {
   if (plan->opt.mfma_variant > 0 && fill_params(plan, which, plan->opt.mfma_variant - 1, plan->opt.mfma_rows, mp, forced ? forced : 1)) {
     best_v = plan->opt.mfma_variant - 1; best_tr = plan->opt.mfma_rows; best_ks = forced ? forced : 1;
   }
+  // bf16 windows of 3x3 go to the kernel in chunks, others whose whole reduction fits LDS to the row-streaming one.  What the options name
+  // counts where it fits this pass; elsewhere the pass runs as if they named nothing.
+  bool flow = false;          // the kernel in chunks is configured, and one of the tile variants may still be the better one
+  auto settled = [&](int variant, int rows) {
+    bool sure = false;
+    flow = variant != -1 && flow_configure(plan, which, variant <= -2 ? -2 - variant : -1, rows, &sure);
+    return flow ? sure : variant >= -1 && rows_configure(plan, which, variant == -1, rows);
+  };
+  if (bf && best_v < 0 && !forced) {
+    const int variant = std::min(plan->opt.mfma_variant, 0), rows = plan->opt.mfma_variant <= 0 ? plan->opt.mfma_rows : 0;
+    if (settled(variant, rows)) return;
+    if (!flow && (variant || rows) && settled(0, 0)) return;
+  }
+  if (bf && forced && plan->opt.mfma_variant <= 0 && rows_configure(plan, which, plan->opt.mfma_variant == -1, plan->opt.mfma_rows)) return;
   if (best_v < 0)
     for (int vi = 0; vi < num_variants(bf); ++vi)
       for (int TR = 1; TR <= c.N * c.Ho && TR * c.Wo <= 16 * 32; ++TR) {
@@ -660,6 +668,7 @@ void mfma_configure(syno_plan* plan, int which) {
           if (forced) break;
         }
       }
+  if (bf && best_v < 0 && forced && settled(0, 0)) return;
   if (best_v < 0 && forced)      // (the named split does not fit this operator: the planner's own choice)
     for (int vi = 0; vi < num_variants(bf); ++vi)
       for (int TR = 1; TR <= c.N * c.Ho && TR * c.Wo <= 16 * 32; ++TR) {
@@ -667,6 +676,10 @@ void mfma_configure(syno_plan* plan, int which) {
         const double cost = tile_cost(mp, variant_of(bf, vi), c, bf);
         if (cost < best) { best = cost; best_v = vi; best_tr = TR; best_ks = 1; }
       }
+  if (bf && best_v < 0) {        // (no tile variant takes the pass: the other kernels, whatever they are estimated at)
+    if (!flow) rows_configure(plan, which, true, 0);
+    return;
+  }
   // (0, 4, 5 and 6: panels of 64, 32 and 16 output channels, and the single chunk)
   if (flow && best_v != 0 && best_v != 4 && best_v != 5 && best_v != 6) return;
   // fp32: the bf16-parts kernel where the operator fits it and it is estimated to be faster; the options name it too

@@ -224,11 +224,11 @@ bool window_supports(const syno_plan* p, int which);
 void window_configure(syno_plan* p, int which);      // fills launch[which].params and .workspace
 // conv_rows_bf16.hip: the row-streaming member of the MFMA family (bf16, whole reduction in LDS)
 bool rows_supports(const syno_plan* p, int which);
-bool rows_configure(syno_plan* p, int which);
+bool rows_configure(syno_plan* p, int which, bool named, int rows);
 std::string rows_describe(const syno_plan* p, int which);
 syno_status launch_rows(const syno_plan* p, int which, const void* A, const void* B, void* out, void* ws, hipStream_t stream);
 // conv_flow_bf16.hip: the bf16 convolutions that take several chunks of channels
-bool flow_configure(syno_plan* p, int which, bool* sure);
+bool flow_configure(syno_plan* p, int which, int named, int rows, bool* sure);
 std::string flow_describe(const syno_plan* p, int which);
 syno_status launch_flow(const syno_plan* p, int which, const void* A, const void* B, void* out, hipStream_t stream);
 // kernels_mfma.hip: has backward-data of a 2x2 window on a stride's phase planes leave the image itself; false where its kernel cannot

@@ -492,6 +492,22 @@ def test_adjacent_reduced_axes_count_as_one_channel_axis(syno):
     assert [other.kernel(k) for k in range(3)] == ["generic_index_program"] * 3
 
 
+@pytest.mark.parametrize("desc", [
+    wl.grouped_shift_unfold(4, in_dtype=BF16), wl.conv2d(2, 64, 64, 14, 14, 1, 1, BF16, F32), wl.conv2d(2, 30, 30, 14, 14, 3, 3, BF16, F32),
+    wl.conv2d(4, 128, 128, 14, 14, 3, 3, BF16, F32), wl.conv2d(4, 256, 256, 14, 14, 1, 1, BF16, BF16),
+], ids=["cyclic", "1x1", "30_channels", "3x3", "1x1_chunks"])
+def test_options_that_do_not_fit_are_ignored(syno, desc):
+    plan = syno.Plan(desc)
+    chunks = "in-chunks" in plan.describe(0)
+    for options in ([{"mfma_variant": -5}, {"mfma_variant": -100}, {"mfma_variant": -2, "mfma_rows": 999}, {"mfma_variant": 99, "mfma_rows": 2},
+                     {"mfma_variant": 1}, {"mfma_variant": -1, "mfma_rows": 999}, {"mfma_rows": 999}, {"mfma_splits": 7}, {"mfma_taps": 1}]
+                    + [{"mfma_variant": -2 - cfg} for cfg in range(0 if chunks else 3)] + [{"mfma_variant": -1}] * chunks):
+        named = syno.Plan(desc, **options)
+        for which in (0, 1):
+            assert named.describe(which) == plan.describe(which), options
+            assert named.workspace_bytes(which) == plan.workspace_bytes(which)
+
+
 @pytest.mark.parametrize("N,C,Co,H,W,bf16,window", [
     (32, 64, 128, 28, 28, False, 2), (1, 32, 32, 3, 5, False, 2), (4, 256, 512, 7, 7, False, 2),
     (1, 32, 64, 14, 14, True, 3), (64, 8, 64, 7, 7, True, 3), (4, 16, 32, 56, 56, True, 3),      # up to 64 channels of G: row-streaming
