@@ -365,27 +365,29 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
   const int my_tiles = tiles_base + (wm < tiles_extra ? 1 : 0);
   const int my_first = wm * tiles_base + min(wm, tiles_extra);
   const int cg_stride = p.n_slots * p.Wp;          // 16-byte units between channel groups
-  // (fp32: worked out while the first loads travel)
-  auto operand_bases = [&](auto& a, auto& b) {
-    constexpr int N = sizeof(a) / sizeof(int);
+  // LDS byte addresses of the lane's operands at tap (0,0), channel group 0
+  auto weight_bases = [&](auto& b) {
 #pragma unroll
-    for (int t = 0; t < N; ++t) {
-      int m = (my_first + t) * 16 + (lane & 15);
-      if (t >= my_tiles || m >= block_px) m = 0;
-      const int i = TABLE ? fdiv(m, p.m_wo) : div_by(m, p.m_wo), w = m - i * p.Wo;
-      // (every image before the row's adds KH - sh)
-      const int slot = TABLE ? slot_of_row(p, R0, i) : p.h_wrap ? i : i * p.sh + (p.KH - p.sh) * div_by(h0 + i, p.m_ho);
-      const int px = slot * p.Wp + w * p.sw;
-      a[t] = BF ? (px + (lane >> 4) * cg_stride) * 16 : px * 16 + (lane >> 4) * 4;       // LDS byte address of the lane's A operand at tap (0,0), channel group 0
-    }
-#pragma unroll
-    for (int u = 0; u < TN; ++u) {                                                      // the same for the B operand (weights)
+    for (int u = 0; u < TN; ++u) {
       const int ol = (wn * TN + u) * 16 + (lane & 15);
       b[u] = p.lds_w_off + (BF ? (ol * p.w_row + (lane >> 4) * 8) * 2 : (ol * p.w_row + (lane >> 4) * KHW) * 4);
     }
   };
   int early_a[TM], early_b[TN];
-  if constexpr (TABLE) operand_bases(early_a, early_b);
+  if constexpr (TABLE) {
+    // (not in a function shared with the closed form: with that some kernels with bf16 results read their arguments again between the
+    // stores, 66 to 333 loads more, and fp32 ones with one tap per row-step kept 3000 scalars in vector lanes.  Calls, time with it to
+    // without: bf16 variant 5 1.04, 10 1.02 (to 1.09); fp32 variants 1 and 3 with one tap 1.05 and 1.04; the others 0.99 to 1.01)
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+      int m = (my_first + t) * 16 + (lane & 15);
+      if (t >= my_tiles || m >= block_px) m = 0;
+      const int i = fdiv(m, p.m_wo), w = m - i * p.Wo;
+      const int px = slot_of_row(p, R0, i) * p.Wp + w * p.sw;
+      early_a[t] = BF ? (px + (lane >> 4) * cg_stride) * 16 : px * 16 + (lane >> 4) * 4;
+    }
+    weight_bases(early_b);
+  }
 
   // Everything from here on is instantiated once per possible tile count of a wave, so that the
   // accumulators and fragments of a wave with fewer row tiles do not occupy registers and the MFMA
@@ -638,7 +640,17 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
     for (int i = tid; i < n16; i += NT) xl[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   int late_a[NA], late_b[TN];
-  if constexpr (!TABLE) operand_bases(late_a, late_b);
+  if constexpr (!TABLE) {      // (while the first loads travel; every image before the row's adds KH - sh slots)
+#pragma unroll
+    for (int t = 0; t < NA; ++t) {
+      int m = (my_first + t) * 16 + (lane & 15);
+      if (t >= my_tiles || m >= block_px) m = 0;
+      const int i = div_by(m, p.m_wo), w = m - i * p.Wo;
+      const int slot = p.h_wrap ? i : i * p.sh + (p.KH - p.sh) * div_by(h0 + i, p.m_ho);
+      late_a[t] = (slot * p.Wp + w * p.sw) * 16 + (lane >> 4) * 4;
+    }
+    weight_bases(late_b);
+  }
   auto& a_base = [&]() -> auto& { if constexpr (TABLE) return early_a; else return late_a; }();
   auto& b_base = [&]() -> auto& { if constexpr (TABLE) return early_b; else return late_b; }();
   if constexpr (BF && WF < 0 && ONE) {
