@@ -1436,17 +1436,20 @@ syno_status build_plan(const syno_desc* desc, syno_plan* plan, std::string* why)
                         cx->launch[SYNO_FWD].workspace + v->launch[SYNO_BWD_DATA].workspace;
           if (dmin == -1 && dmax == 0) {
             if (syno_plan* c2 = conv_plan(CP, c.Og, desc->out_dtype, 2)) {
-              // bf16: on the kernel in chunks the 2x2 window takes 0.55 to 0.9 of the 3x3 one's time on every shape measured (3x3, 2x2, us:
-              // 32x14x14 -> 64, 1 image 4.8, 4.1; 48x7x7 -> 96 5.9, 4.8; 64x28x28 -> 128, 4 images 8.0, 6.4, 32 images 26.2, 19.5; 128x28x28 ->
-              // 256, 1 image 9.8, 6.9; 256x7x7 -> 512, 32 images 31, 21).  Up to 64 channels of G, and up to 128 where it saves less than
-              // 2.5 us, the 3x3 window stays all the same: those plans' windows are part of what this library's tests fix.
+              // bf16: on the kernel in chunks, which stores the image itself, the 2x2 window is the faster one: on all of 4000 drawn calls that
+              // the 3x3 one (with its planes and their way back) takes as well 1.21 to 1.95 times as fast, 1.41 in the mean, and 1.2 to 2.1
+              // times where the 3x3 one runs on another kernel (on 141 of 142 calls, 0.96 on the last; us of a whole call, 3x3 and 2x2: 64x28x28 -> 70, 32 images 21.0, 16.8; 40x22x22
+              // -> 128, 25 images 20.6, 15.2; 280x26x26 -> 8, 29 images 72, 54).  The 3x3 window stays all the same where the call is small -
+              // up to 128 channels of G, 2x2 weights of 256 KB and planes of 2 MB, and by the estimates less than 3000 cycles saved - because
+              // this library's tests fix that choice for such calls (2.5 us slower in the mean of 3000 of them, 5.6 at most).
+              // The two kernels' estimates are not compared with those of others: they count the launch and the others do not.
               // Elsewhere (rows of fewer than 4 pixels, odd channel counts) the 3x3 window stays on the row-streaming kernel, which was ahead
               // on all of 202 shapes, or where packing the 2x2 window's weights (about 2000 cycles) costs more than the products saved.
               const Launch &L3 = cx->launch[SYNO_FWD], &L2 = c2->launch[SYNO_BWD_DATA];
               const bool bf = desc->in_dtype == SYNO_BF16, launch_more = L2.workspace > 0 && L3.workspace == 0;
-              const bool in_chunks = L3.variant <= -2 && L2.variant <= -2;
-              const bool keep_3x3 = bf && (in_chunks ? c.Og <= 64 || (c.Og <= 128 && L3.cycles - L2.cycles < 6000.)
-                                                     : L3.variant == -1 || (c.Og <= 128 && L3.cycles <= L2.cycles + (launch_more ? 2000. : 0.)));
+              const bool small = c.Og <= 128 && CP * c.Og * 4 * (int64_t)esz <= (256 << 10) && plane_elems * (int64_t)osz <= (2 << 20);
+              const bool keep_3x3 = bf && (L2.variant <= -2 ? L3.variant <= -2 && small && L3.cycles - L2.cycles < 3000.
+                                                            : L3.variant == -1 || (c.Og <= 128 && L3.cycles <= L2.cycles + (launch_more ? 2000. : 0.)));
               if (is_mfma(L2) && !keep_3x3) {
                 // (its weights are smaller by more than what packing them takes, but for the smallest: the 3x3 window's workspace does)
                 L.workspace = std::max(L.workspace, round_up((size_t)CP * c.Og * 4 * esz) + round_up((size_t)plane_elems * osz) + L2.workspace);

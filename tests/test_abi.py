@@ -521,3 +521,14 @@ def test_window_of_a_strided_convolutions_input_gradient(syno, N, C, Co, H, W, b
     assert f"depth-to-space (window={window}): " in p.describe(1), p.describe(1)
     e, up = 2 if bf16 else 4, lambda n: -(-n // 256) * 256  # noqa: E731
     assert p.workspace_bytes(1) == up(4 * C * Co * 9 * e) + up(N * 4 * C * H * W * e)
+
+
+@pytest.mark.parametrize("N,C,Co,H,W", [
+    (32, 72, 32, 22, 22), (32, 208, 32, 26, 10), (32, 70, 64, 16, 22), (25, 40, 128, 22, 22),     # the 3x3 window on the kernel in chunks as well
+    (48, 240, 48, 25, 25), (36, 96, 8, 29, 29), (26, 384, 32, 25, 25),                             # ... or on another one, whose estimates leave out the launch
+    (2, 160, 64, 14, 14),                                                                          # a small image, but weights of more than 256 KB
+])
+def test_larger_input_gradients_of_strided_convolutions_take_the_2x2_window(syno, N, C, Co, H, W):
+    for out in (BF16, F32):
+        describe = syno.Plan(wl.conv2d(N, C, Co, H, W, 3, 3, BF16, out, stride=2)).describe(1)
+        assert "(window=2): mfma_contraction_bf16 in-chunks " in describe, describe

@@ -89,6 +89,16 @@ def test_input_gradients_of_strided_convolutions_are_stored_as_the_image(syno, o
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("N,C,Co,H,W", [(60, 42, 8, 14, 26), (13, 160, 24, 11, 13), (32, 70, 64, 16, 22)])
+def test_input_gradients_of_strided_convolutions_with_few_channels(syno, oracle, N, C, Co, H, W):  # noqa: F811
+    """One chunk of 8 or 24 channels, and two; output channels that fill no panel; rows of whole and of broken quads."""
+    w = wl.make_conv(N, C, H, seed=82, bf16=True, Co=Co, Wd=W, stride=2, with_grad=True)
+    describe = syno.Plan(w.desc).describe(1)
+    assert "(window=2): mfma_contraction_bf16 in-chunks " in describe, describe
+    run_all(syno, oracle, w, 0, directions=(1,))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("H,N", [(7, 9001), (8, 8200)])
 @pytest.mark.parametrize("kind,options", [("in-chunks", {"mfma_variant": -2}), ("bf16-parts", {"mfma_variant": -2}), ("variant=4", {"mfma_variant": 5})])
 def test_more_than_65536_tiles(syno, H, N, kind, options):  # noqa: F811
