@@ -373,11 +373,21 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
       b[u] = p.lds_w_off + (BF ? (ol * p.w_row + (lane >> 4) * 8) * 2 : (ol * p.w_row + (lane >> 4) * KHW) * 4);
     }
   };
+  auto pixel_bases = [&](auto& a) {      // fp32, rows in closed form: every image before the row's adds KH - sh slots
+    constexpr int N = sizeof(a) / sizeof(int);
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+      int m = (my_first + t) * 16 + (lane & 15);
+      if (t >= my_tiles || m >= block_px) m = 0;
+      const int i = div_by(m, p.m_wo), w = m - i * p.Wo;
+      const int slot = p.h_wrap ? i : i * p.sh + (p.KH - p.sh) * div_by(h0 + i, p.m_ho);
+      a[t] = (slot * p.Wp + w * p.sw) * 16 + (lane >> 4) * 4;
+    }
+  };
   int early_a[TM], early_b[TN];
   if constexpr (TABLE) {
-    // (not in a function shared with the closed form: with that some kernels with bf16 results read their arguments again between the
-    // stores, 66 to 333 loads more, and fp32 ones with one tap per row-step kept 3000 scalars in vector lanes.  Calls, time with it to
-    // without: bf16 variant 5 1.04, 10 1.02 (to 1.09); fp32 variants 1 and 3 with one tap 1.05 and 1.04; the others 0.99 to 1.01)
+    // (in line: in a function shared with the closed form it made some kernels with bf16 results read their arguments again between the
+    // stores, 66 to 333 loads more, and their calls took 1.02 (variant 10, to 1.09) and 1.04 (variant 5) of the time)
 #pragma unroll
     for (int t = 0; t < TM; ++t) {
       int m = (my_first + t) * 16 + (lane & 15);
@@ -640,14 +650,20 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
     for (int i = tid; i < n16; i += NT) xl[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   int late_a[NA], late_b[TN];
-  if constexpr (!TABLE) {      // (while the first loads travel; every image before the row's adds KH - sh slots)
+  if constexpr (!TABLE) {      // (while the first loads travel)
+    // (one tap per row-step: in line, without which variants 1 and 3 keep up to 3000 scalars in vector lanes: their calls take 1 / 1.05 and
+    // 1 / 1.04 of the time, those of variant 2 1 / 1.01, the others the same.  Three taps: variant 1 would take 1.01 of the time)
+    if constexpr (U == 1) {
 #pragma unroll
-    for (int t = 0; t < NA; ++t) {
-      int m = (my_first + t) * 16 + (lane & 15);
-      if (t >= my_tiles || m >= block_px) m = 0;
-      const int i = div_by(m, p.m_wo), w = m - i * p.Wo;
-      const int slot = p.h_wrap ? i : i * p.sh + (p.KH - p.sh) * div_by(h0 + i, p.m_ho);
-      late_a[t] = (slot * p.Wp + w * p.sw) * 16 + (lane >> 4) * 4;
+      for (int t = 0; t < NA; ++t) {
+        int m = (my_first + t) * 16 + (lane & 15);
+        if (t >= my_tiles || m >= block_px) m = 0;
+        const int i = div_by(m, p.m_wo), w = m - i * p.Wo;
+        const int slot = p.h_wrap ? i : i * p.sh + (p.KH - p.sh) * div_by(h0 + i, p.m_ho);
+        late_a[t] = (slot * p.Wp + w * p.sw) * 16 + (lane >> 4) * 4;
+      }
+    } else {
+      pixel_bases(late_a);
     }
     weight_bases(late_b);
   }
@@ -832,18 +848,28 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
   }
 
   // ---- store: lane holds 4 consecutive pixels (rows of D) of one channel (column of D)
-  const int img_px = p.Ho * p.Wo;
+  // (128 output channels, 16 tiles to store: what the stores need stays in scalar registers from here on, instead of being kept in vector lanes
+  // over the products or read again between the stores.  bf16 1x1 windows, whole calls: 1.06 times as fast with 1 or 2 chunks, 1.04 with 4,
+  // the same from 6 on.  The other variants' times go up or down with it)
+  constexpr bool kept = OUTBF && TN == 4;
+  struct { int32_t Og, os_n, os_o, Ho, Wo; uint32_t m_wo, m_ho; } held;
+  if constexpr (kept) {
+    held = {p.Og, p.os_n, p.os_o, p.Ho, p.Wo, p.m_wo, p.m_ho};
+    asm volatile("" : "+s"(held.Og), "+s"(held.os_n), "+s"(held.os_o), "+s"(held.Ho), "+s"(held.Wo), "+s"(held.m_wo), "+s"(held.m_ho));
+  }
+#define SYNO_STORED(field) (kept ? held.field : p.field)
+  const int img_px = SYNO_STORED(Ho) * SYNO_STORED(Wo);
 #pragma unroll
   for (int t = 0; t < NTL; ++t) {
     const int m0 = (my_first + t) * 16 + 4 * (lane >> 4);
 #pragma unroll
     for (int u = 0; u < TN; ++u) {
       const int o = nb * BN + (wn * TN + u) * 16 + (lane & 15);
-      if (o >= p.Og || m0 >= block_px) continue;
+      if (o >= SYNO_STORED(Og) || m0 >= block_px) continue;
       // pixel m0 of the block -> (image, pixel inside the image)
-      const int i0 = fdiv(m0, p.m_wo), rho = R0 + i0;
-      const int n = fdiv(rho, p.m_ho), px = (rho - n * p.Ho) * p.Wo + (m0 - i0 * p.Wo);
-      const int64_t off = (int64_t)n * p.os_n + (int64_t)(g * p.Og + o) * p.os_o + px;
+      const int i0 = fdiv(m0, SYNO_STORED(m_wo)), rho = R0 + i0;
+      const int n = fdiv(rho, SYNO_STORED(m_ho)), px = (rho - n * SYNO_STORED(Ho)) * SYNO_STORED(Wo) + (m0 - i0 * SYNO_STORED(Wo));
+      const int64_t off = (int64_t)n * SYNO_STORED(os_n) + (int64_t)(g * SYNO_STORED(Og) + o) * SYNO_STORED(os_o) + px;
       const bool together = m0 + 3 < block_px && px + 3 < img_px;
       if constexpr (OUTBF) {
         uint16_t* op = reinterpret_cast<uint16_t*>(out);
@@ -856,8 +882,8 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
 #pragma unroll
           for (int j = 0; j < 4; ++j)
             if (m0 + j < block_px) {
-              const int ij = fdiv(m0 + j, p.m_wo), rj = R0 + ij, nj = fdiv(rj, p.m_ho);
-              op[(int64_t)nj * p.os_n + (int64_t)(g * p.Og + o) * p.os_o + (rj - nj * p.Ho) * p.Wo + (m0 + j - ij * p.Wo)] =
+              const int ij = fdiv(m0 + j, SYNO_STORED(m_wo)), rj = R0 + ij, nj = fdiv(rj, SYNO_STORED(m_ho));
+              op[(int64_t)nj * SYNO_STORED(os_n) + (int64_t)(g * SYNO_STORED(Og) + o) * SYNO_STORED(os_o) + (rj - nj * SYNO_STORED(Ho)) * SYNO_STORED(Wo) + (m0 + j - ij * SYNO_STORED(Wo))] =
                   f32_to_bf16_rne(acc[t][u][j]);
             }
         }
@@ -869,14 +895,15 @@ __global__ __launch_bounds__(WM* WN* WK * 64) void conv_mfma(const std::conditio
 #pragma unroll
           for (int j = 0; j < 4; ++j)
             if (m0 + j < block_px) {
-              const int ij = fdiv(m0 + j, p.m_wo), rj = R0 + ij, nj = fdiv(rj, p.m_ho);
-              op[(int64_t)nj * p.os_n + (int64_t)(g * p.Og + o) * p.os_o + (rj - nj * p.Ho) * p.Wo + (m0 + j - ij * p.Wo)] =
+              const int ij = fdiv(m0 + j, SYNO_STORED(m_wo)), rj = R0 + ij, nj = fdiv(rj, SYNO_STORED(m_ho));
+              op[(int64_t)nj * SYNO_STORED(os_n) + (int64_t)(g * SYNO_STORED(Og) + o) * SYNO_STORED(os_o) + (rj - nj * SYNO_STORED(Ho)) * SYNO_STORED(Wo) + (m0 + j - ij * SYNO_STORED(Wo))] =
                   acc[t][u][j];
             }
         }
       }
     }
   }
+#undef SYNO_STORED
   };
   static_assert(TM <= 8, "extend the dispatch below");
   switch (my_tiles) {
