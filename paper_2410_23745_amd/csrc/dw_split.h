@@ -171,7 +171,9 @@ __global__ __launch_bounds__(512) void dw_split(const DwParams p, const float* _
   // they cost a memory round trip each, 4 at 56x56)
   int base = 0;                        // ring position of the current chunk's first pixel
   {
-    constexpr int IN = 3;              // items of X on their way at a time (a wave's 64 exist or do not: their number is a multiple of 64)
+    // items of X on their way at a time (a wave's 64 exist or do not: their number is a multiple of 64).  Odd widths, whose items are
+    // single loads: one with G's, and the windows' others after it (whole calls of 3x3 windows 1 / 1.01 of the time with three, 1x1 the same)
+    constexpr int IN = VEC == 1 && T > 1 ? 1 : 3;
     const int groups = (kStreamChunk + 2 * B) / XE, all = CX * groups;
     request(gbase, g_at, gr);
     for (int i0 = tid; i0 < all; i0 += IN * NT) {
