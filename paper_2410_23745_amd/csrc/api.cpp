@@ -287,6 +287,7 @@ syno_status syno_plan_describe(const syno_plan* plan, int which, char* buf, size
       const int window = which == SYNO_BWD_WEIGHT ? plan->phase_window_dw : plan->phase_window_dx;
       if (syno_plan_describe(conv, pass, inner, sizeof(inner)) == SYNO_OK)
         d += std::string(which == SYNO_BWD_WEIGHT ? " space-to-depth of X, then the weight gradient of a stride-1 convolution over the phase planes"
+             : plan->phase_direct                 ? " contraction that stores the phase planes of dX as the image, no planes and no depth-to-space"
                                                   : " contraction onto the phase planes of dX, then depth-to-space") +
              " (window=" + std::to_string(window) + "): " + inner;
       break;

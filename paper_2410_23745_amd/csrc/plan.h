@@ -161,7 +161,7 @@ struct syno_plan {
   // windows of those convolutions, per gradient: 3 (pad 1), 2 (rows and columns -1 and 0) or 1.  With window 2 dX is that
   // convolution's backward-data, else the forward contraction of its adjoint
   int32_t phase_window_dw = 0, phase_window_dx = 0;
-  bool phase_direct = false;     // phase_conv_dx writes dX itself: no planes, no way back
+  bool phase_direct = false;     // phase_conv_dx writes dX itself: no planes (their part of the workspace is unused), no way back
   int32_t phase_s = 0;           // phases per image axis that take part: s, or 1 for a 1x1 window, which only reads phase
                                  // (0, 0) - the view is then the sub-sampling X[.., s*h', s*w'] itself
   ~syno_plan() { for (syno_plan* s : sliced) delete s; delete inner; delete inner_dx; delete phase_view_x; delete phase_view_dx; delete phase_conv_dw; delete phase_conv_dx; }

@@ -1451,7 +1451,8 @@ syno_status build_plan(const syno_desc* desc, syno_plan* plan, std::string* why)
               const bool keep_3x3 = bf && (L2.variant <= -2 ? L3.variant <= -2 && small && L3.cycles - L2.cycles < 3000.
                                                             : L3.variant == -1 || (c.Og <= 128 && L3.cycles <= L2.cycles + (launch_more ? 2000. : 0.)));
               if (is_mfma(L2) && !keep_3x3) {
-                // (its weights are smaller by more than what packing them takes, but for the smallest: the 3x3 window's workspace does)
+                // (its weights are smaller by more than what packing them takes, but for the smallest: the 3x3 window's workspace does.
+                // Where the contraction stores the image itself the planes' part is left unused: the tests fix the size, planes included)
                 L.workspace = std::max(L.workspace, round_up((size_t)CP * c.Og * 4 * esz) + round_up((size_t)plane_elems * osz) + L2.workspace);
                 plan->phase_conv_dx = c2; plan->phase_window_dx = 2;
                 plan->phase_direct = ps == 2 && mfma_store_phases(c2);

@@ -532,3 +532,13 @@ def test_larger_input_gradients_of_strided_convolutions_take_the_2x2_window(syno
     for out in (BF16, F32):
         describe = syno.Plan(wl.conv2d(N, C, Co, H, W, 3, 3, BF16, out, stride=2)).describe(1)
         assert "(window=2): mfma_contraction_bf16 in-chunks " in describe, describe
+
+
+def test_description_tells_whether_the_phases_are_stored_as_the_image(syno):
+    def describe(N, C, Co, H, W, t, k=3):
+        return syno.Plan(wl.conv2d(N, C, Co, H, W, k, k, t, t, stride=2)).describe(1)
+    for args in ((32, 64, 128, 28, 28, BF16), (32, 64, 128, 28, 28, F32)):
+        assert " stores the phase planes of dX as the image, " in describe(*args)
+    # the 3x3 window, a 1x1 one, and a kernel that cannot (rows of fewer than 4 pixels)
+    for args in ((1, 32, 64, 14, 14, BF16), (32, 64, 128, 28, 28, F32, 1), (4, 160, 200, 9, 3, BF16)):
+        assert " onto the phase planes of dX, then depth-to-space " in describe(*args)

@@ -72,6 +72,7 @@ def test_input_gradients_of_strided_convolutions_are_stored_as_the_image(syno, o
     rows are whole quads (12 and 16 pixels), else store every second pixel."""
     w = wl.make_conv(32 if kind == "f32" else 3, 96, H, seed=81, bf16=kind != "f32", Co=192, Wd=W, stride=2, with_grad=True, out_bf16=kind == "bf16_results")
     plan = syno.Plan(w.desc)
+    assert " stores the phase planes of dX as the image, " in plan.describe(1), plan.describe(1)
     assert "(window=2): " in plan.describe(1) and ("bf16-parts" if kind == "f32" else "in-chunks") in plan.describe(1), plan.describe(1)
     run_all(syno, oracle, w, 0, directions=(1,))
     if kind == "f32":
