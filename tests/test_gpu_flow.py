@@ -2,7 +2,7 @@
 import pytest
 import torch
 
-from syno_inputs import BF16, F32, workloads as wl
+from syno_inputs import BF16, F32, Builder, workloads as wl
 from test_gpu_parity import run_all, syno  # noqa: F401  (fixture)
 
 # tile configurations: 0 = waves along the pixels, 32 output channels; 1 = 64; 2 = 32, with 64 channels to a
@@ -17,10 +17,13 @@ CASES = {
     "four_chunks": (lambda: wl.make_conv(1, 128, 10, seed=74, bf16=True, Co=160, Wd=16, with_grad=True), ((0, 3), (1, 10), (2, 2)), (0, 1)),
     # two X items to a thread
     "wide": (lambda: wl.make_conv(1, 64, 9, seed=75, bf16=True, Co=40, Wd=60, with_grad=True), ((0, 8), (1, 4), (2, 1)), (0, 1)),
-    # an odd number of output channels (the runs of taps of backward-data begin at odd and at even elements), bf16 results
+    # bf16 results; the runs of taps of backward-data begin at odd and at even elements
     "bf16_results": (lambda: wl.make_conv(2, 72, 9, seed=76, bf16=True, Co=56, Wd=11, with_grad=True, out_bf16=True), ((0, 9), (1, 4), (2, 3)), (0, 1)),
+    # odd numbers of output channels, of results of backward-data, and the fewest of those that it takes
     "odd_channels_fwd": (lambda: wl.make_conv(2, 40, 7, seed=77, bf16=True, Co=37, Wd=9, with_grad=True), ((0, 3), (1, 14), (2, 2)), (0,)),
     "odd_channels_dx": (lambda: wl.make_conv(2, 37, 7, seed=78, bf16=True, Co=40, Wd=9, with_grad=True), ((0, 3), (1, 14), (2, 2)), (1,)),
+    "three_channels_dx": (lambda: wl.make_conv(2, 3, 7, seed=83, bf16=True, Co=40, Wd=9, with_grad=True), ((0, 3), (1, 14), (2, 2)), (1,)),
+    "two_channels_dx": (lambda: wl.make_conv(2, 2, 7, seed=84, bf16=True, Co=16, Wd=8, with_grad=True), ((0, 3), (1, 14), (2, 2)), (1,)),
     "stride2": (lambda: wl.make_conv(2, 64, 9, seed=79, bf16=True, Co=72, Wd=12, stride=2, with_grad=True), ((0, 5), (1, 4), (2, 3)), (0,)),
     "2x2": (lambda: wl.make_conv(3, 40, 13, seed=80, bf16=True, Co=72, Wd=19, K=2, with_grad=True), ((0, 5), (0, 20), (1, 7), (2, 4)), (1,)),
 }
@@ -35,6 +38,36 @@ def test_parity_at_the_edges(syno, oracle, name, cfg, rows):  # noqa: F811
     for which in directions:
         assert f"in-chunks tiles={cfg} rows/block={rows} " in plan.describe(which), plan.describe(which)
         assert plan.workspace_bytes(which) == 0
+    run_all(syno, oracle, w, 0, directions=directions, mfma_variant=-2 - cfg, mfma_rows=rows)
+
+
+def grouped_conv(N, groups, Cg, Og, H, W, out):
+    """out[n,g,o,h,w] = sum X[n, g*Cg+c, h+kh-1, w+kw-1] * Wt[g,o,c,kh,kw], with the groups' output channels side by side."""
+    b = Builder([("n", N), ("co", groups * Og), ("h", H), ("w", W)], name=f"grouped_conv3x3_g{groups}_{Cg}_to_{Og}_{H}x{W}_N{N}")
+    g, o = b.merge(1, Og)
+    gx, gw = b.share(g)
+    (cx, cw), (khx, khw), (kwx, kww) = (b.share(b.reduce(n)) for n in (Cg, 3, 3))
+    return b.finish([0, b.split(gx, cx), b.unfold(2, khx), b.unfold(3, kwx)], [gw, o, cw, khw, kww], BF16, out)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg,rows", ((0, 5), (1, 4), (2, 2)))
+@pytest.mark.parametrize("N,groups,Cg,Og,H,W,out,directions", [
+    (3, 2, 40, 48, 9, 7, F32, (0, 1)),       # a last chunk and last panels that are not full; blocks over two images
+    (4, 2, 64, 64, 14, 14, BF16, (0, 1)),    # a plane of tiles per group that is dealt to the XCDs (configurations 0 and 2)
+    (2, 3, 24, 37, 7, 10, F32, (0,)),        # an odd number of results of a group
+    (2, 3, 37, 24, 7, 10, BF16, (1,)),       # the same of backward-data: each group's last run of taps is read from one element before it
+    (3, 4, 3, 16, 6, 8, F32, (1,)), (3, 5, 2, 8, 5, 9, F32, (1,)),
+])
+def test_groups(syno, oracle, N, groups, Cg, Og, H, W, out, directions, cfg, rows):  # noqa: F811
+    d = grouped_conv(N, groups, Cg, Og, H, W, out)
+    xs, ws, os_ = (N, groups * Cg, H, W), (groups, Og, Cg, 3, 3), (N, groups * Og, H, W)
+    st = wl.Stream(85)
+    w = wl._finish(d, xs, ws, os_, st.normal(xs), st.uniform_pm(1.0 / (9 * Cg) ** 0.5, ws), st.normal(os_), Cg * 9)
+    plan = syno.Plan(d, mfma_variant=-2 - cfg, mfma_rows=rows)
+    assert plan.x_shape == xs and plan.out_shape == os_
+    for which in directions:
+        assert f"in-chunks tiles={cfg} rows/block={rows} " in plan.describe(which), plan.describe(which)
     run_all(syno, oracle, w, 0, directions=directions, mfma_variant=-2 - cfg, mfma_rows=rows)
 
 
